@@ -734,7 +734,7 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
     if ((st = hip_ok(hipHostMalloc((void **)&rm->h_stage, sizeof(rgg_box) * std::max<int64_t>(2 * M, 1)), "pinned staging")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipHostMalloc((void **)&rm->h_res, sizeof(rgg_update_result)), "pinned result")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipStreamCreateWithFlags(&rm->stream, hipStreamNonBlocking), "stream")) != RGG_OK) return guard(st);
-    if ((st = hip_ok(hipEventCreateWithFlags(&rm->done, hipEventDisableTiming), "event")) != RGG_OK) return guard(st);
+    if ((st = hip_ok(hipEventCreateWithFlags(&rm->done, kOrderEventFlags), "event")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipDeviceSynchronize(), "build upload")) != RGG_OK) return guard(st);
 
     rgg_roadmap_info &in = rm->info;
@@ -807,11 +807,16 @@ rgg_status order_after_previous(rgg_roadmap *rm, hipStream_t s)
     return RGG_OK;
 }
 
+void mark_update(rgg_roadmap *rm, hipStream_t s)
+{
+    rm->wait_ev = rm->done;
+    rm->last_stream = s;
+}
+
 rgg_status finish_update(rgg_roadmap *rm, hipStream_t s)
 {
     HIP_OR_FAIL(hipEventRecord(rm->done, s), "hipEventRecord");
-    rm->wait_ev = rm->done;
-    rm->last_stream = s;
+    mark_update(rm, s);
     return RGG_OK;
 }
 
@@ -834,8 +839,12 @@ rgg_status enqueue(rgg_roadmap *rm, hipStream_t s, const UpdateArgs &a)
         rm->pool.pop_back();
         ev = rm->pending.back().data();
     }
-    HIP_OR_FAIL(launch_update(rm->dv, a, s, ev), "update launch");
-    return finish_update(rm, s);
+    // a timed update's last event record follows its last kernel, and the
+    // end mark follows that
+    HIP_OR_FAIL(launch_update(rm->dv, a, s, ev, ev ? nullptr : rm->done), "update launch");
+    if (ev) return finish_update(rm, s);
+    mark_update(rm, s);
+    return RGG_OK;
 }
 
 }  // namespace
@@ -920,9 +929,10 @@ rgg_status rgg_validate_async(rgg_roadmap *rm, void *stream, const int64_t *d_id
     hipStream_t s = (hipStream_t)stream;
     if ((st = order_after_previous(rm, s)) != RGG_OK) return st;
     HIP_OR_FAIL(launch_validate(rm->val, d_ids, n, d_count, max_level, max_active, d_verdict, d_level, d_witness,
-                                d_labels, s),
+                                d_labels, s, rm->done),
                 "validate launch");
-    return finish_update(rm, s);
+    mark_update(rm, s);
+    return RGG_OK;
 }
 
 rgg_status rgg_validate(rgg_roadmap *rm, const int64_t *ids, int64_t n, int32_t max_level, int32_t max_active,
@@ -1149,7 +1159,7 @@ rgg_status rgg_batch_create(rgg_context *ctx, int32_t n, rgg_roadmap *const *rms
     HIP_OR_FAIL(hipMemcpy(b->d_grp, grp.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice), "batch groups");
     for (int k = 0; k < rgg_batch::kRing; ++k) {
         HIP_OR_FAIL(hipHostMalloc((void **)&b->h_tab[k], sizeof(BatchReq) * n, hipHostMallocDefault), "pinned table");
-        HIP_OR_FAIL(hipEventCreateWithFlags(&b->done[k], hipEventDisableTiming), "hipEventCreate");
+        HIP_OR_FAIL(hipEventCreateWithFlags(&b->done[k], kOrderEventFlags), "hipEventCreate");
     }
     rgg_status st = build_batch_graphs(b.get());
     if (st != RGG_OK) return st;
@@ -1203,9 +1213,9 @@ static rgg_status batch_launch(rgg_batch *b, const rgg_update_req *reqs, void *s
         HIP_OR_FAIL(hipGraphLaunch(b->exec[slot], s), "hipGraphLaunch");
     else
         HIP_OR_FAIL(launch_batch(s, b->d_tab, h, b->d_grp, b->n, b->groups.data(), (int)b->groups.size(),
-                                 b->any_grid, b->tiles, b->wtiles, tm),
+                                 b->any_grid, b->tiles, b->wtiles, tm, tm ? nullptr : b->done[slot]),
                     "batch launch");
-    HIP_OR_FAIL(hipEventRecord(b->done[slot], s), "hipEventRecord");
+    if (graph || tm) HIP_OR_FAIL(hipEventRecord(b->done[slot], s), "hipEventRecord");
     b->used[slot] = true;
     for (rgg_roadmap *rm : b->rms) {   // one event stands for every roadmap's update
         rm->wait_ev = b->done[slot];

@@ -127,6 +127,9 @@ namespace rgg {
 // Stream ordering of a roadmap's updates: the next update waits for the
 // previous one when it is queued on another stream.
 rgg_status order_after_previous(rgg_roadmap *rm, hipStream_t s);
+// finish_update records the end of the queued work; mark_update only notes it
+// (the last launch carried rm->done).
 rgg_status finish_update(rgg_roadmap *rm, hipStream_t s);
+void mark_update(rgg_roadmap *rm, hipStream_t s);
 
 }  // namespace rgg

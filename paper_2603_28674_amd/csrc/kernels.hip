@@ -35,6 +35,7 @@
 // single-address counters are k_labels' tickets (one per 4096-edge tile),
 // the batched item kernel's claims (one per item past two per block) and
 // the rare appends to a roadmap's list of items left whole.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -2646,7 +2647,19 @@ struct Args {
 
 }  // namespace
 
-hipError_t launch_update(const RmDev &rm, const UpdateArgs &a, hipStream_t s, hipEvent_t *ev)
+hipError_t launch_marked(const void *fn, dim3 grid, dim3 block, void **args, hipStream_t s, hipEvent_t done)
+{
+    if (!done) return hipLaunchKernel(fn, grid, block, args, 0, s);
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const hipError_t q = hipStreamIsCapturing(s, &cs);
+    if (q == hipSuccess && cs == hipStreamCaptureStatusNone)
+        return hipExtLaunchKernel(fn, grid, block, args, 0, s, nullptr, done, 0);
+    if (q != hipSuccess) (void)hipGetLastError();
+    const hipError_t err = hipLaunchKernel(fn, grid, block, args, 0, s);
+    return err != hipSuccess ? err : hipEventRecord(done, s);
+}
+
+hipError_t launch_update(const RmDev &rm, const UpdateArgs &a, hipStream_t s, hipEvent_t *ev, hipEvent_t done)
 {
     if (rm.chunk < 1 || rm.chunk > kItemCap) return hipErrorInvalidValue;   // at most kSlots edges of an item per thread
     Node nodes[7];
@@ -2656,7 +2669,8 @@ hipError_t launch_update(const RmDev &rm, const UpdateArgs &a, hipStream_t s, hi
     if (ev && (err = hipEventRecord(ev[0], s)) != hipSuccess) return err;
     for (int k = 0; k < n; ++k) {
         const Node &nd = nodes[k];
-        if ((err = hipLaunchKernel(nd.fn, nd.grid, args.block(nd.kind), args.of(nd.kind), 0, s)) != hipSuccess)
+        if ((err = launch_marked(nd.fn, nd.grid, args.block(nd.kind), args.of(nd.kind), s,
+                                 k + 1 == n ? done : nullptr)) != hipSuccess)
             return err;
         if (ev && nd.ev0 >= 0)
             for (int m = nd.ev0; m <= nd.ev1; ++m)
@@ -2838,10 +2852,11 @@ hipError_t batch_scratch_address(void **ptr)
 
 hipError_t launch_batch(hipStream_t s, const BatchReq *tab, const BatchReq *h_tab, const int32_t *grp, int n,
                         const BatchGroup *groups, int n_groups, bool any_grid, int n_tiles, int n_wtiles,
-                        BatchTiming *timing)
+                        BatchTiming *timing, hipEvent_t done)
 {
     auto launch = [&](void *fn, dim3 grid, dim3 block, void **args) -> hipError_t {
-        return hipLaunchKernel(fn, grid, block, args, 0, s);
+        // the gray lists' kernel is the batch's last
+        return launch_marked(fn, grid, block, args, s, fn == (void *)k_write_batch ? done : nullptr);
     };
     if (!timing) {
         auto none = [](int) { return hipSuccess; };

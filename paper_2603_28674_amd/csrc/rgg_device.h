@@ -190,10 +190,11 @@ struct BatchTiming {
     int stage[kMax];
     int n;
 };
-// The same kernels launched on `s` (timed when `timing` is non-null).
+// The same kernels launched on `s` (timed when `timing` is non-null); `done`
+// (may be null) marks the end.
 hipError_t launch_batch(hipStream_t s, const BatchReq *tab, const BatchReq *h_tab, const int32_t *grp, int n,
                         const BatchGroup *groups, int n_groups, bool any_grid, int n_tiles, int n_wtiles,
-                        BatchTiming *timing = nullptr);
+                        BatchTiming *timing = nullptr, hipEvent_t done = nullptr);
 
 // Full validation of listed edges (rgg_validate): the robot, each edge's
 // motion parameters and chord-deviation bounds, and the resident slots.
@@ -223,14 +224,28 @@ struct ValDev {
 // count is non-null, and zero when count->status is not RGG_OK) on `s`.
 // When labels is non-null, each validated edge's entry becomes GREEN (FREE)
 // or RED (COLLIDES, UNRESOLVED).  verdict, level and witness may be null.
+// `done` (may be null) marks the end, also when nothing is launched (n <= 0).
 hipError_t launch_validate(const ValDev &v, const int64_t *ids, int64_t n, const rgg_update_result *count,
                            int32_t max_level, int32_t max_active, uint8_t *verdict, int32_t *level,
-                           double *witness, uint8_t *labels, hipStream_t s);
+                           double *witness, uint8_t *labels, hipStream_t s, hipEvent_t done = nullptr);
+
+// Flags of the events that mark the end of a roadmap's queued work: they order
+// work of one device, so their record needs no flush of the device's caches to
+// the host.
+constexpr unsigned kOrderEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
+
+// Launches a kernel as the last one before `done` (may be null: a plain
+// launch).  The event rides on the kernel's own completion: a separate event
+// record is a packet of its own in the stream, which the next kernel waits
+// behind (a chain of four 8-us kernels took 38.4 us this way, 39.4 us with a
+// record of kOrderEventFlags behind it and 41.1 us with an ordinary event's).
+// A stream under capture gets the record, which the capture understands.
+hipError_t launch_marked(const void *fn, dim3 grid, dim3 block, void **args, hipStream_t s, hipEvent_t done);
 
 // Queues the kernels of one update on `s`.  When `ev` is non-null, ev[0..6]
 // are recorded before, between and after the stages (diff, cells, grid scan,
-// classify, re-test, labels).
-hipError_t launch_update(const RmDev &rm, const UpdateArgs &a, hipStream_t s, hipEvent_t *ev);
+// classify, re-test, labels).  `done` (may be null) marks the end.
+hipError_t launch_update(const RmDev &rm, const UpdateArgs &a, hipStream_t s, hipEvent_t *ev, hipEvent_t done = nullptr);
 
 // Appends the same kernels to `g` as a chain; `dep` (may be null) is the
 // node they wait for, *last receives the final node.

@@ -459,15 +459,14 @@ __global__ __launch_bounds__(kVT) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 hipError_t launch_validate(const ValDev &v, const int64_t *ids, int64_t n, const rgg_update_result *count,
                            int32_t max_level, int32_t max_active, uint8_t *verdict, int32_t *level,
-                           double *witness, uint8_t *labels, hipStream_t s)
+                           double *witness, uint8_t *labels, hipStream_t s, hipEvent_t done)
 {
-    if (n <= 0) return hipSuccess;
+    if (n <= 0) return done ? hipEventRecord(done, s) : hipSuccess;
     const int grid = (int)(n < kVGrid ? n : kVGrid);
-    if (v.D == 3)
-        k_validate<3><<<grid, kVT, 0, s>>>(v, ids, n, count, max_level, max_active, verdict, level, witness, labels);
-    else
-        k_validate<2><<<grid, kVT, 0, s>>>(v, ids, n, count, max_level, max_active, verdict, level, witness, labels);
-    return hipGetLastError();
+    void *args[] = {(void *)&v,         (void *)&ids,     (void *)&n,     (void *)&count,   (void *)&max_level,
+                    (void *)&max_active, (void *)&verdict, (void *)&level, (void *)&witness, (void *)&labels};
+    return launch_marked(v.D == 3 ? (void *)k_validate<3> : (void *)k_validate<2>, dim3(grid), dim3(kVT), args, s,
+                         done);
 }
 
 }  // namespace rgg
