@@ -704,6 +704,10 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
         vd.D = D;
         vd.B = B;
         vd.dof = g.dof;
+        vd.kind = g.kind;
+        vd.L = g.L;
+        vd.base[0] = g.rob_base[0];
+        vd.base[1] = g.rob_base[1];
         vd.vstride = 2 * g.dof + 3;
         vd.E = E;
         vd.M = M;

@@ -2647,15 +2647,16 @@ struct Args {
 
 }  // namespace
 
-hipError_t launch_marked(const void *fn, dim3 grid, dim3 block, void **args, hipStream_t s, hipEvent_t done)
+hipError_t launch_marked(const void *fn, dim3 grid, dim3 block, void **args, hipStream_t s, hipEvent_t done,
+                         unsigned lds_bytes)
 {
-    if (!done) return hipLaunchKernel(fn, grid, block, args, 0, s);
+    if (!done) return hipLaunchKernel(fn, grid, block, args, lds_bytes, s);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     const hipError_t q = hipStreamIsCapturing(s, &cs);
     if (q == hipSuccess && cs == hipStreamCaptureStatusNone)
-        return hipExtLaunchKernel(fn, grid, block, args, 0, s, nullptr, done, 0);
+        return hipExtLaunchKernel(fn, grid, block, args, lds_bytes, s, nullptr, done, 0);
     if (q != hipSuccess) (void)hipGetLastError();
-    const hipError_t err = hipLaunchKernel(fn, grid, block, args, 0, s);
+    const hipError_t err = hipLaunchKernel(fn, grid, block, args, lds_bytes, s);
     return err != hipSuccess ? err : hipEventRecord(done, s);
 }
 

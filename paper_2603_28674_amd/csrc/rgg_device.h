@@ -212,6 +212,8 @@ struct VRobot {
 
 struct ValDev {
     int32_t D, B, dof, vstride;      // vstride = 2 dof + 3
+    int32_t kind, L;                 // robot kind, arm links (else 0)
+    double base[2];                  // arm base
     int64_t E, M;
     const VRobot *rob;
     const double *motion;      // [E][vstride]: a[dof], b[dof] (SE3: short-arc sign), turn, half, sin_half
@@ -240,7 +242,8 @@ constexpr unsigned kOrderEventFlags = hipEventDisableTiming | hipEventDisableSys
 // behind (a chain of four 8-us kernels took 38.4 us this way, 39.4 us with a
 // record of kOrderEventFlags behind it and 41.1 us with an ordinary event's).
 // A stream under capture gets the record, which the capture understands.
-hipError_t launch_marked(const void *fn, dim3 grid, dim3 block, void **args, hipStream_t s, hipEvent_t done);
+hipError_t launch_marked(const void *fn, dim3 grid, dim3 block, void **args, hipStream_t s, hipEvent_t done,
+                         unsigned lds_bytes = 0);
 
 // Queues the kernels of one update on `s`.  When `ev` is non-null, ev[0..6]
 // are recorded before, between and after the stages (diff, cells, grid scan,

@@ -41,6 +41,7 @@ namespace rgg {
 namespace {
 
 constexpr int kVT = 64;            // threads per block
+static_assert(kValBoxes <= 64, "a lane marks a page's boxes in 64 bits");
 constexpr int kVGrid = 16384;      // blocks at most (the hardware balances them)
 constexpr int kNoHit = 0x7fffffff;
 
@@ -99,295 +100,411 @@ __device__ inline void vsincos(double x, double *sn, double *cs)
     }
 }
 
-// centre of sphere i at parameter t of the motion `mot` (a, b, turn, half,
-// sin_half), in the build's expression order
-template <int D>
-__device__ inline void centre_at(const VRobot &rb, const double *mot, double t, int i, double *c)
-{
-    const int dof = rb.dof;
-    const double *a = mot, *b = mot + dof;
-    if (rb.kind == RGG_SE2) {
-        const double q0 = a[0] + t * (b[0] - a[0]);
-        const double q1 = a[1] + t * (b[1] - a[1]);
-        const double q2 = a[2] + t * mot[2 * dof];
-        double s, co;
-        vsincos(q2, &s, &co);
-        const double ox = rb.pos[2 * i], oy = rb.pos[2 * i + 1];
-        c[0] = q0 + (co * ox - s * oy);
-        c[1] = q1 + (s * ox + co * oy);
-    } else if (rb.kind == RGG_SE3) {
-        const double q0 = a[0] + t * (b[0] - a[0]);
-        const double q1 = a[1] + t * (b[1] - a[1]);
-        const double q2 = a[2] + t * (b[2] - a[2]);
-        const double half = mot[2 * dof + 1], sh = mot[2 * dof + 2];
-        double w, ux, uy, uz;
-        if (sh < 1e-12) {
-            w = a[3];
-            ux = a[4];
-            uy = a[5];
-            uz = a[6];
-        } else {
-            double sa, ca, sb, cb;
-            vsincos((1.0 - t) * half, &sa, &ca);
-            vsincos(t * half, &sb, &cb);
-            const double wa = sa / sh;
-            const double wb = sb / sh;
-            w = wa * a[3] + wb * b[3];
-            ux = wa * a[4] + wb * b[4];
-            uy = wa * a[5] + wb * b[5];
-            uz = wa * a[6] + wb * b[6];
-        }
-        const double vx = rb.pos[3 * i], vy = rb.pos[3 * i + 1], vz = rb.pos[3 * i + 2];
-        const double tx = 2.0 * (uy * vz - uz * vy);
-        const double ty = 2.0 * (uz * vx - ux * vz);
-        const double tz = 2.0 * (ux * vy - uy * vx);
-        const double rx = (vx + w * tx) + (uy * tz - uz * ty);
-        const double ry = (vy + w * ty) + (uz * tx - ux * tz);
-        const double rz = (vz + w * tz) + (ux * ty - uy * tx);
-        c[0] = q0 + rx;
-        c[1] = q1 + ry;
-        if (D == 3) c[D - 1] = q2 + rz;
-    } else {
-        // planar chain up to the sphere's link
-        const int link = rb.link[i];
-        double jx = rb.base[0], jy = rb.base[1], phi = 0.0, sph = 0.0, cph = 1.0;
-        for (int m = 0; m <= link; ++m) {
-            const double qm = a[m] + t * (b[m] - a[m]);
-            phi = m == 0 ? qm : phi + qm;
-            vsincos(phi, &sph, &cph);
-            if (m < link) {
-                jx = jx + rb.len[m] * cph;
-                jy = jy + rb.len[m] * sph;
-            }
-        }
-        c[0] = jx + rb.pos[i] * cph;
-        c[1] = jy + rb.pos[i] * sph;
-    }
-}
-
 // ---- the kernel ------------------------------------------------------------
 
-struct ValShared {
-    VRobot rob;
-    double mot[2 * 32 + 3];
-    double del[64];
-    double ebox[6];                 // lo[3], hi[3] of the candidate region
-    double box[kValBoxes][6];       // staged candidate boxes: lo[3], hi[3]
-    int32_t act[kValMaxActive];
-    int32_t nxt[2 * kValMaxActive];
-    uint8_t flag[2 * kValMaxActive];
-    int32_t wave_cnt[kVT / 64];
-    int32_t n_cand, n_page, hit, n_next, nonfree;
+// LDS of one block, laid out by the host for the robot and the limits of the
+// call (offsets in doubles, then in 32-bit words after them): a planar robot
+// of few spheres then leaves room for more edges in flight.
+struct ValLds {
+    int mot, del, pos, rad, len, box, cen, fk;   // doubles
+    int link, act, nxt;                          // 32-bit words
+    int bytes;
+    int chunk;       // intervals refined together
+    int fkw;         // doubles per configuration at fk
+    int box_n;       // candidate boxes per page
 };
 
-// Threads per (point or interval, sphere) item: the block's threads are
-// spread over the items and then over the staged boxes, so few items with
-// many boxes still use the whole block (each group recomputes the centres).
-__device__ inline int groups(int items, int nb)
+constexpr int kVChunkMax = 8;        // intervals per chunk at most (16 child flags in one word)
+constexpr int kVCenDoubles = 768;    // sphere centres of a chunk (more when one interval needs it)
+
+inline ValLds val_lds(const ValDev &v, int max_active)
 {
-    int g = items > 0 ? kVT / items : 1;
-    if (g > nb) g = nb;
-    return g < 1 ? 1 : g;
+    ValLds l = {};
+    const int sincos = v.kind == RGG_PLANAR_ARM ? v.L : (v.kind == RGG_SE3 ? 2 : 1);
+    l.fkw = v.kind == RGG_PLANAR_ARM ? 4 * v.L : 2;
+    // as many intervals as keep one lane per sine-cosine pair of their three
+    // configurations, within the room for their centres
+    int c = 64 / (3 * sincos);
+    if (c > kVChunkMax) c = kVChunkMax;
+    if (c > kVCenDoubles / (3 * v.B * v.D)) c = kVCenDoubles / (3 * v.B * v.D);
+    l.chunk = c < 1 ? 1 : c;
+    l.box_n = (int)(v.M < kValBoxes ? (v.M > 0 ? v.M : 1) : kValBoxes);
+    int d = 0;
+    auto take = [&](int n) {
+        const int at = d;
+        d += n;
+        return at;
+    };
+    l.mot = take(v.vstride);
+    l.del = take(v.B);
+    l.pos = take(v.B * (v.kind == RGG_SE2 ? 2 : (v.kind == RGG_SE3 ? 3 : 1)));
+    l.rad = take(v.B);
+    l.len = take(v.L);
+    l.box = take(l.box_n * 2 * v.D);
+    l.cen = take(3 * l.chunk * v.B * v.D);
+    l.fk = take(3 * l.chunk * l.fkw);
+    d *= 2;
+    l.link = take(v.kind == RGG_PLANAR_ARM ? v.B : 0);
+    l.act = take(max_active);
+    l.nxt = take(max_active);
+    l.bytes = 4 * d;
+    return l;
 }
 
-__device__ inline bool present_near(const rgg_box &b, const double *ebox, int D)
-{
-    bool ok = true;
-    for (int k = 0; k < D; ++k) {
-        ok = ok && b.lo[k] <= b.hi[k];
-        ok = ok && b.lo[k] <= ebox[3 + k] && b.hi[k] >= ebox[k];
-    }
-    return ok;
-}
+// What one wavefront works on.
+struct ValCtx {
+    const ValDev &v;
+    const ValLds &l;
+    double *sd;          // LDS as doubles
+    int32_t *si;         // the same as words
+    int32_t *hit;        // LDS: smallest key of a colliding point of the step
+    uint32_t *flag;      // LDS: bit k: child k of the chunk is not free
+    int n_cand;          // present boxes near the edge
+};
 
-// Stages candidate boxes [page * kValBoxes, ...) into sh.box (in slot order)
-// and leaves their number in sh.n_page and the total in sh.n_cand.
+// Stages the candidate boxes [page * box_n, ...) in LDS (lo[D], hi[D], in slot
+// order); returns the number of candidates of all pages.  Four slots per lane
+// are requested together.
 template <int D>
-__device__ __forceinline__ void gather_page(ValShared &sh, const ValDev &v, int page)
+__device__ __forceinline__ int gather_page(const ValCtx &x, const double *elo, const double *ehi, int page)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t lo_rank = (int64_t)page * kValBoxes;
-    int32_t base = 0;
-    for (int64_t s0 = 0; s0 < v.M; s0 += kVT) {
-        const int64_t s = s0 + tid;
-        bool cand = false;
-        if (s < v.M) cand = present_near(v.resident[s], sh.ebox, D);
-        const unsigned long long bal = __ballot(cand);
-        if (lane == 0) sh.wave_cnt[wave] = __popcll(bal);
-        __syncthreads();
-        int32_t before = base;
-        for (int w = 0; w < wave; ++w) before += sh.wave_cnt[w];
-        int32_t total = 0;
-        for (int w = 0; w < kVT / 64; ++w) total += sh.wave_cnt[w];
-        const int32_t rank = before + __popcll(bal & ((1ull << lane) - 1ull));
-        if (cand && rank >= lo_rank && rank < lo_rank + kValBoxes) {
-            const rgg_box &b = v.resident[s];
-            double *dst = sh.box[rank - lo_rank];
-            for (int k = 0; k < 3; ++k) {
-                dst[k] = b.lo[k];
-                dst[3 + k] = b.hi[k];
+    constexpr int kU = 4;
+    const int lane = threadIdx.x;
+    const int lo_rank = page * x.l.box_n;
+    const int M = (int)x.v.M;
+    int base = 0;
+    for (int s0 = 0; s0 < M; s0 += 64 * kU) {
+        double lo[kU][D], hi[kU][D];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int s = s0 + u * 64 + lane;
+            const rgg_box &b = x.v.resident[s < M ? s : M - 1];
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                lo[u][k] = b.lo[k];
+                hi[u][k] = b.hi[k];
             }
         }
-        base += total;
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            bool cand = s0 + u * 64 + lane < M;
+#pragma unroll
+            for (int k = 0; k < D; ++k)
+                cand = cand && lo[u][k] <= hi[u][k] && lo[u][k] <= ehi[k] && hi[u][k] >= elo[k];
+            const unsigned long long bal = __ballot(cand);
+            const int rank = base + __popcll(bal & ((1ull << lane) - 1ull)) - lo_rank;
+            if (cand && rank >= 0 && rank < x.l.box_n) {
+                double *dst = x.sd + x.l.box + rank * 2 * D;
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    dst[k] = lo[u][k];
+                    dst[D + k] = hi[u][k];
+                }
+            }
+            base += __popcll(bal);
+        }
     }
-    if (tid == 0) {
-        sh.n_cand = base;
-        const int64_t left = (int64_t)base - lo_rank;
-        sh.n_page = (int32_t)(left < 0 ? 0 : (left > kValBoxes ? kValBoxes : left));
+    __syncthreads();
+    return base;
+}
+
+// The sphere centres of nc configurations, t(q) the parameter of the q-th, in
+// the build's expression order: at cen[(q B + i) D].  What the spheres of a
+// configuration share is computed once, one lane each: the sine and cosine of
+// every joint angle (arm) or of the heading, the two slerp weights (SE3), then
+// the arm's joint positions.
+template <int D, typename T>
+__device__ __forceinline__ void centres(const ValCtx &x, int nc, T &&t_of)
+{
+    const ValDev &v = x.v;
+    const int lane = threadIdx.x, B = v.B, dof = v.dof;
+    const double *mot = x.sd + x.l.mot, *a = mot, *b = mot + dof, *pos = x.sd + x.l.pos;
+    double *fk = x.sd + x.l.fk, *cen = x.sd + x.l.cen;
+    if (v.kind == RGG_PLANAR_ARM) {
+        const int L = v.L, W = x.l.fkw;
+        for (int w = lane; w < nc * L; w += 64) {
+            const int q = w / L, m = w - q * L;
+            const double t = t_of(q);
+            double phi = a[0] + t * (b[0] - a[0]);
+            for (int k = 1; k <= m; ++k) phi = phi + (a[k] + t * (b[k] - a[k]));
+            double sn, cs;
+            vsincos(phi, &sn, &cs);
+            fk[q * W + m] = cs;
+            fk[q * W + L + m] = sn;
+        }
+        __syncthreads();
+        const double *len = x.sd + x.l.len;
+        for (int w = lane; w < nc * L; w += 64) {
+            const int q = w / L, m = w - q * L;
+            double jx = v.base[0], jy = v.base[1];
+            for (int k = 0; k < m; ++k) {
+                jx = jx + len[k] * fk[q * W + k];
+                jy = jy + len[k] * fk[q * W + L + k];
+            }
+            fk[q * W + 2 * L + m] = jx;
+            fk[q * W + 3 * L + m] = jy;
+        }
+        __syncthreads();
+        const int32_t *link = x.si + x.l.link;
+        for (int w = lane; w < nc * B; w += 64) {
+            const int q = w / B, i = w - q * B, m = link[i];
+            const double *f = fk + q * W + m;
+            cen[w * D] = f[2 * L] + pos[i] * f[0];
+            cen[w * D + 1] = f[3 * L] + pos[i] * f[L];
+        }
+    } else if (v.kind == RGG_SE2) {
+        for (int q = lane; q < nc; q += 64) {
+            double sn, cs;
+            vsincos(a[2] + t_of(q) * mot[2 * dof], &sn, &cs);
+            fk[2 * q] = cs;
+            fk[2 * q + 1] = sn;
+        }
+        __syncthreads();
+        for (int w = lane; w < nc * B; w += 64) {
+            const int q = w / B, i = w - q * B;
+            const double t = t_of(q), co = fk[2 * q], s = fk[2 * q + 1];
+            const double q0 = a[0] + t * (b[0] - a[0]);
+            const double q1 = a[1] + t * (b[1] - a[1]);
+            const double ox = pos[2 * i], oy = pos[2 * i + 1];
+            cen[w * D] = q0 + (co * ox - s * oy);
+            cen[w * D + 1] = q1 + (s * ox + co * oy);
+        }
+    } else if constexpr (D == 3) {
+        const double half = mot[2 * dof + 1], sh = mot[2 * dof + 2];
+        const bool turn = !(sh < 1e-12);
+        if (turn) {
+            for (int w = lane; w < 2 * nc; w += 64) {
+                const double t = t_of(w >> 1);
+                double sn, cs;
+                vsincos((w & 1 ? t : 1.0 - t) * half, &sn, &cs);
+                fk[w] = sn / sh;
+            }
+        }
+        __syncthreads();
+        for (int w = lane; w < nc * B; w += 64) {
+            const int q = w / B, i = w - q * B;
+            const double t = t_of(q);
+            const double q0 = a[0] + t * (b[0] - a[0]);
+            const double q1 = a[1] + t * (b[1] - a[1]);
+            const double q2 = a[2] + t * (b[2] - a[2]);
+            double qw = a[3], ux = a[4], uy = a[5], uz = a[6];
+            if (turn) {
+                const double wa = fk[2 * q], wb = fk[2 * q + 1];
+                qw = wa * a[3] + wb * b[3];
+                ux = wa * a[4] + wb * b[4];
+                uy = wa * a[5] + wb * b[5];
+                uz = wa * a[6] + wb * b[6];
+            }
+            const double vx = pos[3 * i], vy = pos[3 * i + 1], vz = pos[3 * i + 2];
+            const double tx = 2.0 * (uy * vz - uz * vy);
+            const double ty = 2.0 * (uz * vx - ux * vz);
+            const double tz = 2.0 * (ux * vy - uy * vx);
+            const double rx = (vx + qw * tx) + (uy * tz - uz * ty);
+            const double ry = (vy + qw * ty) + (uz * tx - ux * tz);
+            const double rz = (vz + qw * tz) + (ux * ty - uy * tx);
+            cen[w * D] = q0 + rx;
+            cen[w * D + 1] = q1 + ry;
+            cen[w * D + 2] = q2 + rz;
+        }
     }
     __syncthreads();
 }
 
-// Runs `test(n_boxes)` over every page of candidate boxes (the staged page
-// when there is only one).
-template <int D, typename F>
-__device__ __forceinline__ void over_pages(ValShared &sh, const ValDev &v, int n_pages, F &&test)
+// One step of the search over the staged configurations: three tests per
+// interval and sphere.  kLevel0: the points t = 0 (key 0) and t = 1 (key 1)
+// and the whole edge's capsule (flag bit 0), configurations 0, 1, 2 being
+// t = 0, 1/2, 1.  Otherwise interval c of the chunk has its start, midpoint
+// and end at configurations 3c .. 3c + 2: the midpoint (key 2 act + 1) and the
+// two children's capsules (flag bits 2c, 2c + 1), wl the children's length.
+// *hit receives the smallest key whose point collides (kNoHit if none), *flag
+// the children that are not free (not to be used when a point collides; not
+// computed when `points_only`).
+//
+// A lane first marks the staged boxes that its test's own bounding box meets
+// (widened far beyond rounding, so a box left out cannot meet the test), then
+// runs the exact test on the marked ones: the wavefront runs the expensive
+// segment-box minimum as often as the lane with the most near boxes needs it,
+// not once for every box that any lane is near.
+template <int D, bool kLevel0>
+__device__ __forceinline__ void run_tests(const ValCtx &x, const double *elo, const double *ehi, int n_int, double wl,
+                                          const int32_t *act, bool points_only)
 {
-    if (n_pages <= 1) {
-        test(sh.n_page);
-        __syncthreads();
-        return;
+    const int lane = threadIdx.x, B = x.v.B;
+    const double *cen = x.sd + x.l.cen, *rad = x.sd + x.l.rad, *del = x.sd + x.l.del;
+    if (lane == 0) {
+        *x.hit = kNoHit;
+        *x.flag = 0u;
     }
+    __syncthreads();
+    const int tasks = n_int * 3 * B;
+    const int n_pages = (x.n_cand + x.l.box_n - 1) / x.l.box_n;
     for (int p = 0; p < n_pages; ++p) {
-        gather_page<D>(sh, v, p);
-        test(sh.n_page);
-        __syncthreads();
+        if (n_pages > 1) gather_page<D>(x, elo, ehi, p);
+        const int nb = min(x.l.box_n, x.n_cand - p * x.l.box_n);
+        // few tasks: several lanes per task, each taking every G-th box
+        int G = tasks < 64 ? 64 / tasks : 1;
+        if (G > nb) G = nb;
+        for (int w0 = 0; w0 < tasks * G; w0 += 64) {
+            const int w = w0 + lane;
+            const int task = G == 1 ? w : w / G, grp = G == 1 ? 0 : w - task * G;
+            const int r = task / B, i = task - r * B;
+            const int c = r / 3, part = r - 3 * c;
+            const bool live = w < tasks * G;
+            const bool point = kLevel0 ? part < 2 : part == 0;
+            const int qa = kLevel0 ? (part == 1 ? 2 : 0) : 3 * c + (part == 1 ? 0 : 1);
+            const int qb = kLevel0 ? (part == 0 ? 0 : 2) : 3 * c + (part == 2 ? 2 : 1);
+            double ca[D], cb[D], R = 0.0;
+            unsigned long long m = 0;
+            if (live && (point || !points_only)) {
+                R = point ? rad[i] : rad[i] + del[i] * (wl * wl);
+                double clo[D], chi[D];
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    ca[d] = cen[(qa * B + i) * D + d];
+                    cb[d] = cen[(qb * B + i) * D + d];
+                    const double mn = ca[d] < cb[d] ? ca[d] : cb[d], mx = ca[d] < cb[d] ? cb[d] : ca[d];
+                    clo[d] = mn - (R * 1.000001 + 1e-9 * (1.0 + fabs(mn)));
+                    chi[d] = mx + (R * 1.000001 + 1e-9 * (1.0 + fabs(mx)));
+                }
+                for (int b = grp; b < nb; b += G) {
+                    const double *bx = x.sd + x.l.box + b * 2 * D;
+                    bool near = true;
+#pragma unroll
+                    for (int d = 0; d < D; ++d) near = near && bx[d] <= chi[d] && bx[D + d] >= clo[d];
+                    m |= (unsigned long long)near << b;
+                }
+            }
+            if (point) {
+                while (m) {
+                    const int b = __ffsll(m) - 1;
+                    m &= m - 1;
+                    const double *bx = x.sd + x.l.box + b * 2 * D;
+                    if (point_box64<D>(ca, bx, bx + D) <= R * R) {
+                        atomicMin(x.hit, kLevel0 ? part : 2 * act[c] + 1);
+                        m = 0;
+                    }
+                }
+            }
+            __syncthreads();
+            // a colliding point ends the search: the children do not matter
+            if (*x.hit != kNoHit) points_only = true;
+            if (points_only || point) m = 0;
+            const uint32_t bit = kLevel0 ? 1u : 1u << (2 * c + part - 1);
+            while (m) {
+                const int b = __ffsll(m) - 1;
+                m &= m - 1;
+                const double *bx = x.sd + x.l.box + b * 2 * D;
+                if (segbox64<D>(ca, cb, bx, bx + D) <= R * R) {
+                    atomicOr(x.flag, bit);
+                    m = 0;
+                }
+            }
+        }
     }
+    __syncthreads();
 }
 
 template <int D>
-__device__ __forceinline__ void validate_one(ValShared &sh, const ValDev &v, int64_t e, int max_level, int max_active,
-                             uint8_t *verdict, int32_t *level, double *witness, uint8_t *labels)
+__device__ __forceinline__ void validate_one(ValCtx &x, int64_t e, int max_level, int max_active, uint8_t *verdict,
+                                             int32_t *level, double *witness, uint8_t *labels)
 {
-    const int tid = threadIdx.x;
-    const int B = v.B;
-    for (int k = tid; k < v.vstride; k += kVT) sh.mot[k] = v.motion[e * v.vstride + k];
-    for (int k = tid; k < B; k += kVT) sh.del[k] = v.delta[e * B + k];
-    __syncthreads();
-    if (tid < D) {
-        // the candidate region: chords widened by r_i + 2 delta_i, plus margin
+    const ValDev &v = x.v;
+    const int lane = threadIdx.x, B = v.B;
+    // the edge's motion and chord deviations, and its capsules for the
+    // candidate region: one round of loads
+    for (int k = lane; k < v.vstride; k += 64) x.sd[x.l.mot + k] = v.motion[e * v.vstride + k];
+    double elo[D], ehi[D];
+    {
+        // the chords widened by r_i + 2 delta_i, plus a margin
         const double *cp = v.cap64 + e * (2 * D + 1) * B;
-        double lo = INFINITY, hi = -INFINITY;
-        for (int i = 0; i < B; ++i) {
-            const double A = cp[tid * B + i], Bv = cp[(D + tid) * B + i];
-            const double w = cp[2 * D * B + i] + sh.del[i];
+        const double dl = lane < B ? v.delta[e * B + lane] : 0.0;
+        if (lane < B) x.sd[x.l.del + lane] = dl;
+        const double wd = lane < B ? cp[2 * D * B + lane] + dl : 0.0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const double A = lane < B ? cp[d * B + lane] : 0.0, Bv = lane < B ? cp[(D + d) * B + lane] : 0.0;
             const double mn = A < Bv ? A : Bv, mx = A < Bv ? Bv : A;
-            if (mn - w < lo) lo = mn - w;
-            if (mx + w > hi) hi = mx + w;
+            elo[d] = lane < B ? mn - wd : INFINITY;
+            ehi[d] = lane < B ? mx + wd : -INFINITY;
         }
-        sh.ebox[tid] = lo - 1e-6 * (1.0 + fabs(lo));
-        sh.ebox[3 + tid] = hi + 1e-6 * (1.0 + fabs(hi));
+        for (int o = 1; o < B; o <<= 1) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const double l2 = __shfl_xor(elo[d], o), h2 = __shfl_xor(ehi[d], o);
+                elo[d] = l2 < elo[d] ? l2 : elo[d];
+                ehi[d] = h2 > ehi[d] ? h2 : ehi[d];
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const double lo = __shfl(elo[d], 0), hi = __shfl(ehi[d], 0);
+            elo[d] = lo - 1e-6 * (1.0 + fabs(lo));
+            ehi[d] = hi + 1e-6 * (1.0 + fabs(hi));
+        }
     }
-    __syncthreads();
-    gather_page<D>(sh, v, 0);
-    const int n_pages = (int)((sh.n_cand + kValBoxes - 1) / kValBoxes);
+    x.n_cand = v.M > 0 ? gather_page<D>(x, elo, ehi, 0) : 0;
 
     uint8_t out = kUnresolved;
     int32_t out_level = 0;
     double out_t = NAN;
-
-    // One phase of the search: hit(t) at the points ldexp(key(k), -ex),
-    // k < n_pts (sh.hit = the smallest key that hits, kNoHit if none), and
-    // free(lc, child(k)) for k < n_children (sh.flag[k] = 1 when not free).
-    // The children's tests only matter when no point hits; computing both in
-    // one pass saves a barrier-separated phase per level.
-    auto step = [&](int n_pts, int ex, auto &&key, int lc, int n_children, auto &&child) {
-        if (tid == 0) sh.hit = kNoHit;
-        for (int k = tid; k < n_children; k += kVT) sh.flag[k] = 0;
-        __syncthreads();
-        const double wl = ldexp(1.0, -lc);
-        const int hit_items = n_pts * B, all_items = (n_pts + n_children) * B;
-        over_pages<D>(sh, v, n_pages, [&](int nb) {
-            const int G = groups(all_items, nb);
-            for (int w = tid; w < all_items * G; w += kVT) {
-                const int item = w / G, grp = w - item * G;
-                if (item < hit_items) {
-                    const int k = item / B, i = item - k * B;
-                    const int32_t kk = key(k);
-                    if (kk >= sh.hit) continue;
-                    double c[D];
-                    centre_at<D>(sh.rob, sh.mot, ldexp((double)kk, -ex), i, c);
-                    const double r2 = sh.rob.rad[i] * sh.rob.rad[i];
-                    for (int b = grp; b < nb; b += G) {
-                        if (point_box64<D>(c, sh.box[b], sh.box[b] + 3) <= r2) {
-                            atomicMin(&sh.hit, kk);
-                            break;
-                        }
-                    }
-                } else {
-                    const int it = item - hit_items;
-                    const int k = it / B, i = it - k * B;
-                    if (sh.flag[k] || sh.hit != kNoHit) continue;
-                    const int32_t j = child(k);
-                    double ca[D], cb[D];
-                    centre_at<D>(sh.rob, sh.mot, ldexp((double)j, -lc), i, ca);
-                    centre_at<D>(sh.rob, sh.mot, ldexp((double)(j + 1), -lc), i, cb);
-                    const double R = sh.rob.rad[i] + sh.del[i] * (wl * wl);
-                    // the capsule's bounding box, widened far beyond rounding:
-                    // a box outside it is farther than R from the segment
-                    double clo[D], chi[D];
-#pragma unroll
-                    for (int d = 0; d < D; ++d) {
-                        const double mn = ca[d] < cb[d] ? ca[d] : cb[d], mx = ca[d] < cb[d] ? cb[d] : ca[d];
-                        clo[d] = mn - (R * 1.000001 + 1e-9 * (1.0 + fabs(mn)));
-                        chi[d] = mx + (R * 1.000001 + 1e-9 * (1.0 + fabs(mx)));
-                    }
-                    for (int b = grp; b < nb; b += G) {
-                        bool apart = false;
-#pragma unroll
-                        for (int d = 0; d < D; ++d)
-                            apart = apart || sh.box[b][d] > chi[d] || sh.box[b][3 + d] < clo[d];
-                        if (apart) continue;
-                        if (segbox64<D>(ca, cb, sh.box[b], sh.box[b] + 3) <= R * R) {
-                            sh.flag[k] = 1;
-                            break;
-                        }
-                    }
-                }
-            }
-        });
-        return sh.hit;
-    };
-
     do {
-        // t = 0, then t = 1 (key = t), and the whole edge's capsules
-        const int h0 = step(2, 0, [](int k) { return (int32_t)k; }, 0, 1, [](int) { return 0; });
+        // t = 0, then t = 1, and the whole edge's capsules; the first
+        // interval's midpoint comes along
+        if (x.n_cand == 0) {
+            out = kFree;
+            break;
+        }
+        centres<D>(x, 3, [](int q) { return ldexp((double)q, -1); });
+        run_tests<D, true>(x, elo, ehi, 1, 1.0, nullptr, false);
+        const int h0 = *x.hit;
         if (h0 != kNoHit) {
             out = kCollides;
             out_t = (double)h0;
             break;
         }
-        if (!sh.flag[0]) {
+        if (!*x.flag) {
             out = kFree;
             break;
         }
         int na = 1;
-        if (tid == 0) sh.act[0] = 0;
+        int32_t *act = x.si + x.l.act, *nxt = x.si + x.l.nxt;
+        if (lane == 0) act[0] = 0;
         __syncthreads();
         bool done = false;
-        for (int l = 0; l < max_level && !done; ++l) {
+        for (int l = 0; l < max_level; ++l) {
             out_level = l;
             if (na > max_active) {
                 out = kUnresolved;
                 done = true;
                 break;
             }
-            const int h = step(na, l + 1, [&](int k) { return 2 * sh.act[k] + 1; }, l + 1, 2 * na,
-                               [&](int k) { return 2 * sh.act[k >> 1] + (k & 1); });
-            if (h != kNoHit) {
+            const double wl = ldexp(1.0, -(l + 1));
+            int best = kNoHit, nn = 0;
+            for (int c0 = 0; c0 < na; c0 += x.l.chunk) {
+                const int n_int = min(x.l.chunk, na - c0);
+                const int32_t *ac = act + c0;
+                if (l > 0)
+                    centres<D>(x, 3 * n_int, [&](int q) {
+                        const int c = q / 3;
+                        return ldexp((double)(2 * ac[c] + (q - 3 * c)), -(l + 1));
+                    });
+                run_tests<D, false>(x, elo, ehi, n_int, wl, ac, best != kNoHit);
+                best = min(best, *x.hit);
+                // the children that are not free, in order
+                const bool open = lane < 2 * n_int && ((*x.flag >> lane) & 1u);
+                const unsigned long long bal = __ballot(open);
+                const int at = nn + __popcll(bal & ((1ull << lane) - 1ull));
+                if (open && at < max_active) nxt[at] = 2 * ac[lane >> 1] + (lane & 1);
+                nn += __popcll(bal);
+                __syncthreads();
+            }
+            if (best != kNoHit) {
                 out = kCollides;
                 out_level = l + 1;
-                out_t = ldexp((double)h, -(l + 1));
+                out_t = ldexp((double)best, -(l + 1));
                 done = true;
                 break;
             }
-            if (tid == 0) sh.n_next = 0;
-            __syncthreads();
-            for (int k = tid; k < 2 * na; k += kVT)
-                if (sh.flag[k]) sh.nxt[atomicAdd(&sh.n_next, 1)] = 2 * sh.act[k >> 1] + (k & 1);
-            __syncthreads();
-            const int nn = sh.n_next;
             out_level = l + 1;
             if (nn == 0) {
                 out = kFree;
@@ -395,10 +512,10 @@ __device__ __forceinline__ void validate_one(ValShared &sh, const ValDev &v, int
                 break;
             }
             // more than max_active stops the search at the next level (or
-            // after the last one) before act is read again
-            if (nn <= max_active)
-                for (int k = tid; k < nn; k += kVT) sh.act[k] = sh.nxt[k];
-            __syncthreads();
+            // after the last one) before the list is read again
+            int32_t *const swap = act;
+            act = nxt;
+            nxt = swap;
             na = nn;
         }
         if (!done) {
@@ -407,7 +524,7 @@ __device__ __forceinline__ void validate_one(ValShared &sh, const ValDev &v, int
         }
     } while (false);
     __syncthreads();
-    if (tid == 0) {
+    if (lane == 0) {
         if (verdict) verdict[0] = out;
         if (level) level[0] = out_level;
         if (witness) witness[0] = out_t;
@@ -416,16 +533,23 @@ __device__ __forceinline__ void validate_one(ValShared &sh, const ValDev &v, int
     __syncthreads();
 }
 
-// One wavefront per edge with 14 KB of LDS: about eleven edges are in
-// flight per CU.  The search is a chain of dependent phases per edge, so
-// edges in flight matter more than threads per edge.
+// One wavefront per edge.  The search is a chain of dependent binary64 phases
+// per edge, so edges in flight matter more than threads per edge.  A step
+// used to place every sphere of every test from the joint angles anew (an
+// arm's sphere on its last link took all seven sine-cosine pairs, 84 per
+// configuration of a 21-sphere arm instead of 7); with the shared centres and
+// the marked boxes the update + validation of the arm with 56k edges (14.6k of
+// them gray) went from 606 to 289 us, of the spatial body with 116k edges
+// (1.5k gray) from 148 to 119 us.
 template <int D>
 __global__ __launch_bounds__(kVT) __attribute__((amdgpu_waves_per_eu(4))) void k_validate(
-    ValDev v, const int64_t *ids, int64_t n, const rgg_update_result *count, int max_level, int max_active,
+    ValDev v, ValLds l, const int64_t *ids, int64_t n, const rgg_update_result *count, int max_level, int max_active,
     uint8_t *verdict, int32_t *level, double *witness, uint8_t *labels)
 {
-    __shared__ ValShared sh;
-    const int tid = threadIdx.x;
+    extern __shared__ double sh[];
+    __shared__ int32_t s_hit;
+    __shared__ uint32_t s_flag;
+    const int lane = threadIdx.x;
     int64_t nn = n;
     if (count) {
         const int64_t g = count->status == RGG_OK ? count->n_gray : 0;
@@ -434,23 +558,26 @@ __global__ __launch_bounds__(kVT) __attribute__((amdgpu_waves_per_eu(4))) void k
     // blocks beyond the list (the grid is sized for its capacity when the
     // count comes from the device) leave at once
     if ((int64_t)blockIdx.x >= nn) return;
+    ValCtx x = {v, l, sh, reinterpret_cast<int32_t *>(sh), &s_hit, &s_flag, 0};
     {
-        const int32_t *src = reinterpret_cast<const int32_t *>(v.rob);
-        int32_t *dst = reinterpret_cast<int32_t *>(&sh.rob);
-        for (int k = tid; k < (int)(sizeof(VRobot) / 4); k += kVT) dst[k] = src[k];
+        const VRobot &rb = *v.rob;
+        const int per = v.kind == RGG_SE2 ? 2 : (v.kind == RGG_SE3 ? 3 : 1);
+        for (int k = lane; k < v.B * per; k += 64) x.sd[l.pos + k] = rb.pos[k];
+        if (lane < v.B) x.sd[l.rad + lane] = rb.rad[lane];
+        if (lane < v.L) x.sd[l.len + lane] = rb.len[lane];
+        if (v.kind == RGG_PLANAR_ARM && lane < v.B) x.si[l.link + lane] = rb.link[lane];
     }
-    __syncthreads();
     for (int64_t i = blockIdx.x; i < nn; i += gridDim.x) {
         const int64_t e = ids[i];
         if (e < 0 || e >= v.E) {
-            if (tid == 0) {
+            if (lane == 0) {
                 if (verdict) verdict[i] = RGG_VERDICT_BAD_ID;
                 if (level) level[i] = 0;
                 if (witness) witness[i] = NAN;
             }
             continue;
         }
-        validate_one<D>(sh, v, e, max_level, max_active, verdict ? verdict + i : nullptr, level ? level + i : nullptr,
+        validate_one<D>(x, e, max_level, max_active, verdict ? verdict + i : nullptr, level ? level + i : nullptr,
                         witness ? witness + i : nullptr, labels);
     }
 }
@@ -463,10 +590,11 @@ hipError_t launch_validate(const ValDev &v, const int64_t *ids, int64_t n, const
 {
     if (n <= 0) return done ? hipEventRecord(done, s) : hipSuccess;
     const int grid = (int)(n < kVGrid ? n : kVGrid);
-    void *args[] = {(void *)&v,         (void *)&ids,     (void *)&n,     (void *)&count,   (void *)&max_level,
+    const ValLds l = val_lds(v, max_active);
+    void *args[] = {(void *)&v,         (void *)&l,       (void *)&ids,     (void *)&n,     (void *)&count,   (void *)&max_level,
                     (void *)&max_active, (void *)&verdict, (void *)&level, (void *)&witness, (void *)&labels};
     return launch_marked(v.D == 3 ? (void *)k_validate<3> : (void *)k_validate<2>, dim3(grid), dim3(kVT), args, s,
-                         done);
+                         done, (unsigned)l.bytes);
 }
 
 }  // namespace rgg
