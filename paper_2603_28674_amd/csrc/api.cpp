@@ -705,6 +705,11 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
         vd.B = B;
         vd.dof = g.dof;
         vd.kind = g.kind;
+        int n_cu = 0;
+        if ((st = hip_ok(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device),
+                         "compute units")) != RGG_OK)
+            return guard(st);
+        vd.n_cu = n_cu;
         vd.L = g.L;
         vd.base[0] = g.rob_base[0];
         vd.base[1] = g.rob_base[1];

@@ -124,6 +124,63 @@ __device__ inline double segbox64(const double *A, const double *Bp, const doubl
     return fmin;
 }
 
+// Whether segbox64(A, Bp, lo, hi) <= R R, the capsule test's decision, mostly
+// without evaluating it.  F(t), the squared distance of the segment's point t
+// to the box, is convex: F at any t bounds its minimum from above, and the
+// tangent there bounds it from below over [0, 1].  A few Newton steps on the
+// current quadratic piece bring t near the minimiser; a pair whose bounds leave
+// no doubt is decided, any other one by segbox64.  "No doubt" is a margin of
+// 1e-12 (about 9,000 roundings) of every term the values are made of: A and d
+// below s and L in size, the gaps (their squares are F) and R.  A step costs
+// no division; segbox64 holds 2 D + 1 of them in one dependent chain.
+template <int D>
+struct Capsule64 {
+    double A[D], B[D], d[D];
+    double R, scale;
+    bool quick;
+
+    __device__ void set(double r)
+    {
+        R = r;
+        double s = 0.0, L = 0.0;
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            d[k] = B[k] - A[k];
+            s = fmax(s, fmax(fabs(A[k]), fabs(B[k])));
+            L = L + fabs(d[k]);
+        }
+        scale = 1e-12 * ((s + R) * (R + L) + L * L);
+        quick = s <= 1048576.0 * R;
+    }
+
+    __device__ bool meets(const double *lo, const double *hi) const
+    {
+        const double RR = R * R;
+        if (quick) {
+            double t = 0.5;
+#pragma unroll 1
+            for (int step = 0; step < 3; ++step) {
+                double F = 0.0, G = 0.0, W = 0.0;
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    const double p = __builtin_fma(t, d[k], A[k]);
+                    const double ex = fmin(p - lo[k], 0.0) + fmax(p - hi[k], 0.0);
+                    const double w = ex != 0.0 ? d[k] : 0.0;
+                    F = __builtin_fma(ex, ex, F);
+                    G = __builtin_fma(d[k], ex, G);
+                    W = __builtin_fma(w, w, W);
+                }
+                const double m = __builtin_fma(1e-12, F, scale);
+                if (F < RR - m) return true;
+                if (__builtin_fma(2.0 * G, G > 0.0 ? -t : 1.0 - t, F) > RR + m) return false;
+                if (!(W > 0.0)) break;
+                t = fmin(fmax(__builtin_fma(-G, __builtin_amdgcn_rcp(W), t), 0.0), 1.0);
+            }
+        }
+        return segbox64<D>(A, B, lo, hi) <= RR;
+    }
+};
+
 // Oriented box o = (centre[D], axes[D][D] as rows, half-extents[D]) against
 // the closed box [lo, hi]: true when they share a point.  Separating-axis
 // theorem for two boxes: the candidate axes are the box's face normals e_d,

@@ -213,6 +213,7 @@ struct VRobot {
 struct ValDev {
     int32_t D, B, dof, vstride;      // vstride = 2 dof + 3
     int32_t kind, L;                 // robot kind, arm links (else 0)
+    int32_t n_cu, pad;               // compute units of the device
     double base[2];                  // arm base
     int64_t E, M;
     const VRobot *rob;

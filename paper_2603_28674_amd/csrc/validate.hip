@@ -24,12 +24,12 @@
 // verdicts.  The distance predicates are the binary64 definitions of the
 // update kernels (predicates64.h).
 //
-// One wavefront (a 64-thread block) validates one listed edge at a time (grid-stride
-// over the list).  Its present boxes near the edge are staged in LDS: a box
+// One wavefront validates one listed edge at a time (grid-stride over the
+// list).  Its present boxes near the edge are staged in LDS: a box
 // can matter only if it meets the box around the edge's chords widened by
 // r_i + 2 delta_i (each sub-chord stays within delta_i of the edge's chord,
 // each sub-capsule adds at most r_i + delta_i), plus a rounding margin.  More
-// than kValBoxes such boxes are handled in pages.
+// than 64 such boxes are handled in pages.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -40,10 +40,17 @@ namespace rgg {
 
 namespace {
 
-constexpr int kVT = 64;            // threads per block
-static_assert(kValBoxes <= 64, "a lane marks a page's boxes in 64 bits");
-constexpr int kVGrid = 16384;      // blocks at most (the hardware balances them)
+constexpr int kVWaves = 4;         // wavefronts per block, an edge each
+constexpr int kVT = 64 * kVWaves;  // threads per block
+static_assert(kValBoxes == 64, "a lane marks a page's boxes in 64 bits, and stages one of them");
 constexpr int kNoHit = 0x7fffffff;
+
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 constexpr uint8_t kFree = RGG_VERDICT_FREE;
 constexpr uint8_t kCollides = RGG_VERDICT_COLLIDES;
@@ -103,19 +110,25 @@ __device__ inline void vsincos(double x, double *sn, double *cs)
 // ---- the kernel ------------------------------------------------------------
 
 // LDS of one block, laid out by the host for the robot and the limits of the
-// call (offsets in doubles, then in 32-bit words after them): a planar robot
-// of few spheres then leaves room for more edges in flight.
+// call: a planar robot of few spheres then leaves room for more edges in
+// flight.  The robot and the resident boxes come first, then one region per
+// wavefront (offsets within the region: doubles, then 32-bit words).
 struct ValLds {
-    int mot, del, pos, rad, len, box, cen, fk;   // doubles
-    int link, act, nxt;                          // 32-bit words
+    int pos, rad, len, link, tile;                // block: robot (doubles; link: words), boxes
+    int region0, region;                          // first region, doubles per region
+    int mot, del, box, box32, list, cen, fk;      // doubles (list: 16-bit slots)
+    int act, nxt;                                 // 32-bit words
     int bytes;
     int chunk;       // intervals refined together
     int fkw;         // doubles per configuration at fk
-    int box_n;       // candidate boxes per page
 };
 
 constexpr int kVChunkMax = 8;        // intervals per chunk at most (16 child flags in one word)
-constexpr int kVCenDoubles = 768;    // sphere centres of a chunk (more when one interval needs it)
+constexpr int kVCenDoubles = 400;    // sphere centres of a chunk (more when one interval needs it)
+constexpr int kVTile = 512;          // resident boxes kept in LDS; more are scanned in memory
+constexpr int kVCull = 16;        // candidates from which a step looks for ones to drop
+constexpr int kVList = 256;          // candidate slots listed; more are found again page by page
+static_assert(kVList % kValBoxes == 0 && kMaxSlots <= 65536, "whole pages are listed, as 16-bit slots");
 
 inline ValLds val_lds(const ValDev &v, int max_active)
 {
@@ -128,26 +141,33 @@ inline ValLds val_lds(const ValDev &v, int max_active)
     if (c > kVChunkMax) c = kVChunkMax;
     if (c > kVCenDoubles / (3 * v.B * v.D)) c = kVCenDoubles / (3 * v.B * v.D);
     l.chunk = c < 1 ? 1 : c;
-    l.box_n = (int)(v.M < kValBoxes ? (v.M > 0 ? v.M : 1) : kValBoxes);
     int d = 0;
     auto take = [&](int n) {
         const int at = d;
-        d += n;
+        d += n + (n & 1);                         // 16-byte steps
         return at;
     };
-    l.mot = take(v.vstride);
-    l.del = take(v.B);
     l.pos = take(v.B * (v.kind == RGG_SE2 ? 2 : (v.kind == RGG_SE3 ? 3 : 1)));
     l.rad = take(v.B);
     l.len = take(v.L);
-    l.box = take(l.box_n * 2 * v.D);
+    l.link = 2 * take((v.B + 1) / 2);
+    l.tile = take(v.M <= kVTile ? (int)v.M * v.D : 0);   // 2 D floats a box
+    l.region0 = d;
+    d = 0;
+    const int page = (int)(v.M < kValBoxes ? (v.M > 0 ? v.M : 1) : kValBoxes);
     l.cen = take(3 * l.chunk * v.B * v.D);
     l.fk = take(3 * l.chunk * l.fkw);
-    d *= 2;
-    l.link = take(v.kind == RGG_PLANAR_ARM ? v.B : 0);
-    l.act = take(max_active);
-    l.nxt = take(max_active);
-    l.bytes = 4 * d;
+    l.box32 = take(page * v.D);
+    l.box = take(page * 2 * v.D);
+    l.list = take((int)(v.M < kVList ? v.M : kVList) / 4 + 1);
+    l.mot = take(v.vstride);
+    l.del = take(v.B);
+    l.act = 2 * d;
+    l.nxt = l.act + max_active;
+    d += max_active;
+    d += d & 1;
+    l.region = d;
+    l.bytes = 8 * (l.region0 + kVWaves * l.region);
     return l;
 }
 
@@ -155,57 +175,134 @@ inline ValLds val_lds(const ValDev &v, int max_active)
 struct ValCtx {
     const ValDev &v;
     const ValLds &l;
-    double *sd;          // LDS as doubles
+    const double *rob;   // LDS: the robot and the resident boxes
+    double *sd;          // LDS: this wavefront's region as doubles
     int32_t *si;         // the same as words
     int32_t *hit;        // LDS: smallest key of a colliding point of the step
     uint32_t *flag;      // LDS: bit k: child k of the chunk is not free
+    unsigned long long *keep;   // LDS: boxes of each listed page that the next level's tests can reach
     int n_cand;          // present boxes near the edge
+    bool cull;           // this step's tests fill keep
 };
 
-// Stages the candidate boxes [page * box_n, ...) in LDS (lo[D], hi[D], in slot
-// order); returns the number of candidates of all pages.  Four slots per lane
-// are requested together.
-template <int D>
-__device__ __forceinline__ int gather_page(const ValCtx &x, const double *elo, const double *ehi, int page)
+// Rounds outward for the near tests.  A lower bound above binary32's range, or
+// an upper one below it, becomes NaN, which meets no box: no box lies out
+// there (boxes are at most 1e30 in size).
+__device__ inline float f32_below(double x) { return (float)x - fabsf((float)x) * 0x1p-22f - 0x1p-140f; }
+__device__ inline float f32_above(double x) { return (float)x + fabsf((float)x) * 0x1p-22f + 0x1p-140f; }
+
+// The box around a segment from a to b widened by R, and far beyond rounding:
+// what lies outside it is farther than R from the segment.
+__device__ inline double below(double a, double b, double R)
 {
-    constexpr int kU = 4;
-    const int lane = threadIdx.x;
-    const int lo_rank = page * x.l.box_n;
-    const int M = (int)x.v.M;
-    int base = 0;
-    for (int s0 = 0; s0 < M; s0 += 64 * kU) {
-        double lo[kU][D], hi[kU][D];
+    const double mn = a < b ? a : b;
+    return mn - (R * 1.000001 + 1e-9 * (1.0 + fabs(mn)));
+}
+__device__ inline double above(double a, double b, double R)
+{
+    const double mx = a < b ? b : a;
+    return mx + (R * 1.000001 + 1e-9 * (1.0 + fabs(mx)));
+}
+
+// Binary32 boxes, 2 D floats each: a float4 in 2-D, three (lo, hi) pairs in
+// 3-D.
+template <int D>
+__device__ __forceinline__ void put_box32(double *at, int k, const float *lo, const float *hi)
+{
+    if constexpr (D == 2) {
+        reinterpret_cast<float4 *>(at)[k] = make_float4(lo[0], lo[1], hi[0], hi[1]);
+    } else {
+        float2 *g = reinterpret_cast<float2 *>(at) + 3 * k;
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int s = s0 + u * 64 + lane;
-            const rgg_box &b = x.v.resident[s < M ? s : M - 1];
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-                lo[u][k] = b.lo[k];
-                hi[u][k] = b.hi[k];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            bool cand = s0 + u * 64 + lane < M;
-#pragma unroll
-            for (int k = 0; k < D; ++k)
-                cand = cand && lo[u][k] <= hi[u][k] && lo[u][k] <= ehi[k] && hi[u][k] >= elo[k];
-            const unsigned long long bal = __ballot(cand);
-            const int rank = base + __popcll(bal & ((1ull << lane) - 1ull)) - lo_rank;
-            if (cand && rank >= 0 && rank < x.l.box_n) {
-                double *dst = x.sd + x.l.box + rank * 2 * D;
-#pragma unroll
-                for (int k = 0; k < D; ++k) {
-                    dst[k] = lo[u][k];
-                    dst[D + k] = hi[u][k];
-                }
-            }
-            base += __popcll(bal);
-        }
+        for (int d = 0; d < D; ++d) g[d] = make_float2(lo[d], hi[d]);
     }
-    __syncthreads();
+}
+
+template <int D>
+__device__ __forceinline__ bool meets32(const double *at, int k, const float *clo, const float *chi)
+{
+    if constexpr (D == 2) {
+        const float4 q = reinterpret_cast<const float4 *>(at)[k];
+        return (q.x <= chi[0]) & (q.y <= chi[1]) & (q.z >= clo[0]) & (q.w >= clo[1]);
+    } else {
+        const float2 *g = reinterpret_cast<const float2 *>(at) + 3 * k;
+        bool r = true;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const float2 q = g[d];
+            r = r & (q.x <= chi[d]) & (q.y >= clo[d]);
+        }
+        return r;
+    }
+}
+
+// A resident box rounded outward; an ABSENT one (lo > hi on some axis) becomes
+// one that meets nothing.
+template <int D>
+__device__ __forceinline__ void outward(const rgg_box &b, float *lo, float *hi)
+{
+    bool there = true;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        there = there && b.lo[d] <= b.hi[d];
+        lo[d] = f32_below(b.lo[d]);
+        hi[d] = f32_above(b.hi[d]);
+    }
+    if (!there) lo[0] = NAN;
+}
+
+// Lists the slots of the present boxes that meet [clo, chi], in slot order from
+// the lo_rank-th on, kVList at most; returns the number of all of them.
+template <int D>
+__device__ __forceinline__ int list_candidates(const ValCtx &x, const float *clo, const float *chi, int lo_rank)
+{
+    const int lane = threadIdx.x & 63;
+    const int M = (int)x.v.M;
+    const bool tiled = M <= kVTile;
+    uint16_t *list = reinterpret_cast<uint16_t *>(x.sd + x.l.list);
+    int base = 0;
+    for (int s0 = 0; s0 < M; s0 += 64) {
+        const int s = min(s0 + lane, M - 1);
+        bool cand;
+        if (tiled) {
+            cand = meets32<D>(x.rob + x.l.tile, s, clo, chi);
+        } else {
+            float lo[D], hi[D];
+            outward<D>(x.v.resident[s], lo, hi);
+            cand = true;
+#pragma unroll
+            for (int d = 0; d < D; ++d) cand = cand & (lo[d] <= chi[d]) & (hi[d] >= clo[d]);
+        }
+        cand = cand && s0 + lane < M;
+        const unsigned long long bal = __ballot(cand);
+        const int rank = base + __popcll(bal & ((1ull << lane) - 1ull)) - lo_rank;
+        if (cand && rank >= 0 && rank < kVList) list[rank] = (uint16_t)s;
+        base += __popcll(bal);
+    }
+    wave_sync();
     return base;
+}
+
+// Puts the listed boxes l0 .. l0 + n (n <= kValBoxes) into LDS: the exact
+// boxes, and their outward-rounded binary32 copies for the near tests.
+template <int D>
+__device__ __forceinline__ void stage_page(const ValCtx &x, int l0, int n)
+{
+    const int lane = threadIdx.x & 63;
+    if (lane < n) {
+        const uint16_t *list = reinterpret_cast<const uint16_t *>(x.sd + x.l.list);
+        const rgg_box &b = x.v.resident[list[l0 + lane]];
+        double *dst = x.sd + x.l.box + lane * 2 * D;
+        float lo[D], hi[D];
+        outward<D>(b, lo, hi);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            dst[d] = b.lo[d];
+            dst[D + d] = b.hi[d];
+        }
+        put_box32<D>(x.sd + x.l.box32, lane, lo, hi);
+    }
+    wave_sync();
 }
 
 // The sphere centres of nc configurations, t(q) the parameter of the q-th, in
@@ -217,8 +314,8 @@ template <int D, typename T>
 __device__ __forceinline__ void centres(const ValCtx &x, int nc, T &&t_of)
 {
     const ValDev &v = x.v;
-    const int lane = threadIdx.x, B = v.B, dof = v.dof;
-    const double *mot = x.sd + x.l.mot, *a = mot, *b = mot + dof, *pos = x.sd + x.l.pos;
+    const int lane = threadIdx.x & 63, B = v.B, dof = v.dof;
+    const double *mot = x.sd + x.l.mot, *a = mot, *b = mot + dof, *pos = x.rob + x.l.pos;
     double *fk = x.sd + x.l.fk, *cen = x.sd + x.l.cen;
     if (v.kind == RGG_PLANAR_ARM) {
         const int L = v.L, W = x.l.fkw;
@@ -226,17 +323,19 @@ __device__ __forceinline__ void centres(const ValCtx &x, int nc, T &&t_of)
             const int q = w / L, m = w - q * L;
             const double t = t_of(q);
             double phi = a[0] + t * (b[0] - a[0]);
+#pragma unroll 4
             for (int k = 1; k <= m; ++k) phi = phi + (a[k] + t * (b[k] - a[k]));
             double sn, cs;
             vsincos(phi, &sn, &cs);
             fk[q * W + m] = cs;
             fk[q * W + L + m] = sn;
         }
-        __syncthreads();
-        const double *len = x.sd + x.l.len;
+        wave_sync();
+        const double *len = x.rob + x.l.len;
         for (int w = lane; w < nc * L; w += 64) {
             const int q = w / L, m = w - q * L;
             double jx = v.base[0], jy = v.base[1];
+#pragma unroll 4
             for (int k = 0; k < m; ++k) {
                 jx = jx + len[k] * fk[q * W + k];
                 jy = jy + len[k] * fk[q * W + L + k];
@@ -244,8 +343,8 @@ __device__ __forceinline__ void centres(const ValCtx &x, int nc, T &&t_of)
             fk[q * W + 2 * L + m] = jx;
             fk[q * W + 3 * L + m] = jy;
         }
-        __syncthreads();
-        const int32_t *link = x.si + x.l.link;
+        wave_sync();
+        const int32_t *link = reinterpret_cast<const int32_t *>(x.rob) + x.l.link;
         for (int w = lane; w < nc * B; w += 64) {
             const int q = w / B, i = w - q * B, m = link[i];
             const double *f = fk + q * W + m;
@@ -259,7 +358,7 @@ __device__ __forceinline__ void centres(const ValCtx &x, int nc, T &&t_of)
             fk[2 * q] = cs;
             fk[2 * q + 1] = sn;
         }
-        __syncthreads();
+        wave_sync();
         for (int w = lane; w < nc * B; w += 64) {
             const int q = w / B, i = w - q * B;
             const double t = t_of(q), co = fk[2 * q], s = fk[2 * q + 1];
@@ -280,7 +379,7 @@ __device__ __forceinline__ void centres(const ValCtx &x, int nc, T &&t_of)
                 fk[w] = sn / sh;
             }
         }
-        __syncthreads();
+        wave_sync();
         for (int w = lane; w < nc * B; w += 64) {
             const int q = w / B, i = w - q * B;
             const double t = t_of(q);
@@ -307,40 +406,48 @@ __device__ __forceinline__ void centres(const ValCtx &x, int nc, T &&t_of)
             cen[w * D + 2] = q2 + rz;
         }
     }
-    __syncthreads();
+    wave_sync();
 }
 
-// One step of the search over the staged configurations: three tests per
-// interval and sphere.  kLevel0: the points t = 0 (key 0) and t = 1 (key 1)
-// and the whole edge's capsule (flag bit 0), configurations 0, 1, 2 being
-// t = 0, 1/2, 1.  Otherwise interval c of the chunk has its start, midpoint
-// and end at configurations 3c .. 3c + 2: the midpoint (key 2 act + 1) and the
-// two children's capsules (flag bits 2c, 2c + 1), wl the children's length.
+// One step of the search over the staged configurations: a wavefront's tests
+// of points (a sphere at a configuration against the boxes) and of capsules (a
+// sphere's over a sub-interval).
+// kFirst: configurations 0, 1, 2 are t = 0, 1/2, 1.  Points t = 0 (key 0),
+// t = 1 (key 1), t = 1/2 (key 2); capsules of the two halves (flag bits 0, 1)
+// and of the whole edge (bit 2).
+// Otherwise interval c of the chunk has its start, midpoint and end at
+// configurations 3c .. 3c + 2: the midpoint (key 2 act + 1) and the two
+// children's capsules (bits 2c, 2c + 1).  wl is the children's length.
 // *hit receives the smallest key whose point collides (kNoHit if none), *flag
-// the children that are not free (not to be used when a point collides; not
-// computed when `points_only`).
+// the capsules that are not free; the children's bits are not complete when a
+// point collides, nor bit 2 when t = 0 or 1 does (they do not matter then),
+// and no capsule is tested when `points_only`.
 //
 // A lane first marks the staged boxes that its test's own bounding box meets
 // (widened far beyond rounding, so a box left out cannot meet the test), then
 // runs the exact test on the marked ones: the wavefront runs the expensive
-// segment-box minimum as often as the lane with the most near boxes needs it,
-// not once for every box that any lane is near.
-template <int D, bool kLevel0>
-__device__ __forceinline__ void run_tests(const ValCtx &x, const double *elo, const double *ehi, int n_int, double wl,
+// capsule test as often as the lane with the most near boxes needs it, not
+// once for every box that any lane is near.
+template <int D, bool kFirst>
+__device__ __forceinline__ void run_tests(const ValCtx &x, const float *elo, const float *ehi, int n_int, double wl,
                                           const int32_t *act, bool points_only)
 {
-    const int lane = threadIdx.x, B = x.v.B;
-    const double *cen = x.sd + x.l.cen, *rad = x.sd + x.l.rad, *del = x.sd + x.l.del;
+    constexpr int kParts = kFirst ? 6 : 3;
+    const int lane = threadIdx.x & 63, B = x.v.B;
+    const double *cen = x.sd + x.l.cen, *rad = x.rob + x.l.rad, *del = x.sd + x.l.del;
     if (lane == 0) {
         *x.hit = kNoHit;
         *x.flag = 0u;
     }
-    __syncthreads();
-    const int tasks = n_int * 3 * B;
-    const int n_pages = (x.n_cand + x.l.box_n - 1) / x.l.box_n;
-    for (int p = 0; p < n_pages; ++p) {
-        if (n_pages > 1) gather_page<D>(x, elo, ehi, p);
-        const int nb = min(x.l.box_n, x.n_cand - p * x.l.box_n);
+    wave_sync();
+    const int tasks = n_int * kParts * B;
+    for (int p0 = 0; p0 < x.n_cand; p0 += kValBoxes) {
+        const int nb = min(kValBoxes, x.n_cand - p0);
+        // one page stays staged; more come and go in every step
+        if (x.n_cand > kValBoxes) {
+            if (x.n_cand > kVList && p0 % kVList == 0) list_candidates<D>(x, elo, ehi, p0);
+            stage_page<D>(x, p0 % kVList, nb);
+        }
         // few tasks: several lanes per task, each taking every G-th box
         int G = tasks < 64 ? 64 / tasks : 1;
         if (G > nb) G = nb;
@@ -348,208 +455,281 @@ __device__ __forceinline__ void run_tests(const ValCtx &x, const double *elo, co
             const int w = w0 + lane;
             const int task = G == 1 ? w : w / G, grp = G == 1 ? 0 : w - task * G;
             const int r = task / B, i = task - r * B;
-            const int c = r / 3, part = r - 3 * c;
-            const bool live = w < tasks * G;
-            const bool point = kLevel0 ? part < 2 : part == 0;
-            const int qa = kLevel0 ? (part == 1 ? 2 : 0) : 3 * c + (part == 1 ? 0 : 1);
-            const int qb = kLevel0 ? (part == 0 ? 0 : 2) : 3 * c + (part == 2 ? 2 : 1);
-            double ca[D], cb[D], R = 0.0;
-            unsigned long long m = 0;
-            if (live && (point || !points_only)) {
-                R = point ? rad[i] : rad[i] + del[i] * (wl * wl);
-                double clo[D], chi[D];
+            const int c = kFirst ? 0 : r / kParts, part = kFirst ? r : r - kParts * c;
+            const bool point = kFirst ? part < 3 : part == 0;
+            int qa, qb;
+            if (kFirst) {
+                qa = part == 1 ? 2 : (part == 2 || part == 4 ? 1 : 0);
+                qb = part == 3 ? 1 : 2;
+            } else {
+                qa = 3 * c + (part == 1 ? 0 : 1);
+                qb = 3 * c + (part == 2 ? 2 : 1);
+            }
+            if (point) qb = qa;
+            const double cw = kFirst && part == 5 ? 1.0 : wl;
+            Capsule64<D> cap;
+            unsigned long long m = 0, far = 0;
+            double R = 0.0;
+            if (w < tasks * G && (point || !points_only)) {
+                R = point ? rad[i] : rad[i] + del[i] * (cw * cw);
+                float clo[D], chi[D];
 #pragma unroll
                 for (int d = 0; d < D; ++d) {
-                    ca[d] = cen[(qa * B + i) * D + d];
-                    cb[d] = cen[(qb * B + i) * D + d];
-                    const double mn = ca[d] < cb[d] ? ca[d] : cb[d], mx = ca[d] < cb[d] ? cb[d] : ca[d];
-                    clo[d] = mn - (R * 1.000001 + 1e-9 * (1.0 + fabs(mn)));
-                    chi[d] = mx + (R * 1.000001 + 1e-9 * (1.0 + fabs(mx)));
+                    cap.A[d] = cen[(qa * B + i) * D + d];
+                    cap.B[d] = cen[(qb * B + i) * D + d];
+                    clo[d] = f32_below(below(cap.A[d], cap.B[d], R));
+                    chi[d] = f32_above(above(cap.A[d], cap.B[d], R));
                 }
-                for (int b = grp; b < nb; b += G) {
-                    const double *bx = x.sd + x.l.box + b * 2 * D;
-                    bool near = true;
+                const double *b32 = x.sd + x.l.box32;
+                if (x.cull && !point && !(kFirst && part == 5)) {
+                    // this capsule's motion stays within delta of its chord,
+                    // its parts' tests within another r + delta of that
+                    const double W = R + del[i] * (cw * cw);
+                    float flo[D], fhi[D];
 #pragma unroll
-                    for (int d = 0; d < D; ++d) near = near && bx[d] <= chi[d] && bx[D + d] >= clo[d];
-                    m |= (unsigned long long)near << b;
+                    for (int d = 0; d < D; ++d) {
+                        flo[d] = f32_below(below(cap.A[d], cap.B[d], W));
+                        fhi[d] = f32_above(above(cap.A[d], cap.B[d], W));
+                    }
+                    int b = grp;
+                    for (; b + 3 * G < nb; b += 4 * G) {
+                        bool nr[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) nr[u] = meets32<D>(b32, b + u * G, flo, fhi);
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) far |= (unsigned long long)nr[u] << (b + u * G);
+                    }
+                    for (; b < nb; b += G) far |= (unsigned long long)meets32<D>(b32, b, flo, fhi) << b;
                 }
+                int b = grp;
+                for (; b + 7 * G < nb; b += 8 * G) {
+                    bool nr[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) nr[u] = meets32<D>(b32, b + u * G, clo, chi);
+                    if (G == 1) {
+                        uint32_t byte = 0;
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) byte |= nr[u] ? 1u << u : 0u;
+                        m |= (unsigned long long)byte << b;
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) m |= (unsigned long long)nr[u] << (b + u * G);
+                    }
+                }
+                for (; b < nb; b += G) m |= (unsigned long long)meets32<D>(b32, b, clo, chi) << b;
+            }
+            if (x.cull) {
+                for (int o = 32; o > 0; o >>= 1) far |= __shfl_xor(far, o);
+                if (lane == 0) x.keep[p0 / kValBoxes] |= far;
             }
             if (point) {
                 while (m) {
                     const int b = __ffsll(m) - 1;
                     m &= m - 1;
                     const double *bx = x.sd + x.l.box + b * 2 * D;
-                    if (point_box64<D>(ca, bx, bx + D) <= R * R) {
-                        atomicMin(x.hit, kLevel0 ? part : 2 * act[c] + 1);
+                    if (point_box64<D>(cap.A, bx, bx + D) <= R * R) {
+                        atomicMin(x.hit, kFirst ? part : 2 * act[c] + 1);
                         m = 0;
                     }
                 }
             }
-            __syncthreads();
+            wave_sync();
             // a colliding point ends the search: the children do not matter
-            if (*x.hit != kNoHit) points_only = true;
-            if (points_only || point) m = 0;
-            const uint32_t bit = kLevel0 ? 1u : 1u << (2 * c + part - 1);
-            while (m) {
-                const int b = __ffsll(m) - 1;
-                m &= m - 1;
-                const double *bx = x.sd + x.l.box + b * 2 * D;
-                if (segbox64<D>(ca, cb, bx, bx + D) <= R * R) {
-                    atomicOr(x.flag, bit);
-                    m = 0;
+            const int h = *x.hit;
+            const bool skip = points_only || (kFirst ? h < 2 || (h == 2 && part < 5) : h != kNoHit);
+            const uint32_t bit = kFirst ? 1u << (part >= 3 ? part - 3 : 0) : 1u << (2 * c + (part == 2 ? 1 : 0));
+            if (skip || point) m = 0;
+            if (__ballot(m != 0)) {
+                cap.set(R);
+                while (m) {
+                    const int b = __ffsll(m) - 1;
+                    m &= m - 1;
+                    const double *bx = x.sd + x.l.box + b * 2 * D;
+                    if (cap.meets(bx, bx + D)) {
+                        atomicOr(x.flag, bit);
+                        m = 0;
+                    }
+                    // another sphere of the same capsule set may have met a box
+                    if (__hip_atomic_load(x.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit) m = 0;
                 }
             }
         }
     }
-    __syncthreads();
+    wave_sync();
 }
 
+// After a level whose tests filled x.keep: the candidates that no later test
+// can reach leave the list.
 template <int D>
-__device__ __forceinline__ void validate_one(ValCtx &x, int64_t e, int max_level, int max_active, uint8_t *verdict,
-                                             int32_t *level, double *witness, uint8_t *labels)
+__device__ __forceinline__ void drop_candidates(ValCtx &x)
+{
+    const int lane = threadIdx.x & 63;
+    uint16_t *list = reinterpret_cast<uint16_t *>(x.sd + x.l.list);
+    wave_sync();
+    int n = 0;
+    for (int p0 = 0; p0 < x.n_cand; p0 += kValBoxes) {
+        const unsigned long long k = x.keep[p0 / kValBoxes];
+        const uint16_t s = list[p0 + lane < x.n_cand ? p0 + lane : p0];
+        wave_sync();
+        if ((k >> lane) & 1ull) list[n + __popcll(k & ((1ull << lane) - 1ull))] = s;   // moves down only
+        n += __popcll(k);
+    }
+    wave_sync();
+    if (n < x.n_cand) {
+        x.n_cand = n;
+        if (n <= kValBoxes) stage_page<D>(x, 0, n);
+    }
+}
+
+// The candidate region of edge e: its chords widened by r_i + 2 delta_i, plus
+// a margin, rounded outward.  Its motion and chord deviations go to LDS.
+template <int D>
+__device__ __forceinline__ void load_edge(const ValCtx &x, int64_t e, float *elo, float *ehi)
 {
     const ValDev &v = x.v;
-    const int lane = threadIdx.x, B = v.B;
-    // the edge's motion and chord deviations, and its capsules for the
-    // candidate region: one round of loads
+    const int lane = threadIdx.x & 63, B = v.B;
+    const int i = lane < B ? lane : 0;   // idle lanes repeat sphere 0
     for (int k = lane; k < v.vstride; k += 64) x.sd[x.l.mot + k] = v.motion[e * v.vstride + k];
-    double elo[D], ehi[D];
-    {
-        // the chords widened by r_i + 2 delta_i, plus a margin
-        const double *cp = v.cap64 + e * (2 * D + 1) * B;
-        const double dl = lane < B ? v.delta[e * B + lane] : 0.0;
-        if (lane < B) x.sd[x.l.del + lane] = dl;
-        const double wd = lane < B ? cp[2 * D * B + lane] + dl : 0.0;
+    const double *cp = v.cap64 + e * (2 * D + 1) * B;
+    const double dl = v.delta[e * B + i];
+    if (lane < B) x.sd[x.l.del + lane] = dl;
+    const double wd = cp[2 * D * B + i] + dl;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const double A = cp[d * B + i], Bv = cp[(D + d) * B + i];
+        const double lo = (A < Bv ? A : Bv) - wd, hi = (A < Bv ? Bv : A) + wd;
+        elo[d] = f32_below(lo - 1e-6 * (1.0 + fabs(lo)));
+        ehi[d] = f32_above(hi + 1e-6 * (1.0 + fabs(hi)));
+    }
+    for (int o = 1; o < B; o <<= 1) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            const double A = lane < B ? cp[d * B + lane] : 0.0, Bv = lane < B ? cp[(D + d) * B + lane] : 0.0;
-            const double mn = A < Bv ? A : Bv, mx = A < Bv ? Bv : A;
-            elo[d] = lane < B ? mn - wd : INFINITY;
-            ehi[d] = lane < B ? mx + wd : -INFINITY;
-        }
-        for (int o = 1; o < B; o <<= 1) {
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                const double l2 = __shfl_xor(elo[d], o), h2 = __shfl_xor(ehi[d], o);
-                elo[d] = l2 < elo[d] ? l2 : elo[d];
-                ehi[d] = h2 > ehi[d] ? h2 : ehi[d];
-            }
-        }
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const double lo = __shfl(elo[d], 0), hi = __shfl(ehi[d], 0);
-            elo[d] = lo - 1e-6 * (1.0 + fabs(lo));
-            ehi[d] = hi + 1e-6 * (1.0 + fabs(hi));
+            elo[d] = fminf(elo[d], __shfl_xor(elo[d], o));
+            ehi[d] = fmaxf(ehi[d], __shfl_xor(ehi[d], o));
         }
     }
-    x.n_cand = v.M > 0 ? gather_page<D>(x, elo, ehi, 0) : 0;
-
-    uint8_t out = kUnresolved;
-    int32_t out_level = 0;
-    double out_t = NAN;
-    do {
-        // t = 0, then t = 1, and the whole edge's capsules; the first
-        // interval's midpoint comes along
-        if (x.n_cand == 0) {
-            out = kFree;
-            break;
-        }
-        centres<D>(x, 3, [](int q) { return ldexp((double)q, -1); });
-        run_tests<D, true>(x, elo, ehi, 1, 1.0, nullptr, false);
-        const int h0 = *x.hit;
-        if (h0 != kNoHit) {
-            out = kCollides;
-            out_t = (double)h0;
-            break;
-        }
-        if (!*x.flag) {
-            out = kFree;
-            break;
-        }
-        int na = 1;
-        int32_t *act = x.si + x.l.act, *nxt = x.si + x.l.nxt;
-        if (lane == 0) act[0] = 0;
-        __syncthreads();
-        bool done = false;
-        for (int l = 0; l < max_level; ++l) {
-            out_level = l;
-            if (na > max_active) {
-                out = kUnresolved;
-                done = true;
-                break;
-            }
-            const double wl = ldexp(1.0, -(l + 1));
-            int best = kNoHit, nn = 0;
-            for (int c0 = 0; c0 < na; c0 += x.l.chunk) {
-                const int n_int = min(x.l.chunk, na - c0);
-                const int32_t *ac = act + c0;
-                if (l > 0)
-                    centres<D>(x, 3 * n_int, [&](int q) {
-                        const int c = q / 3;
-                        return ldexp((double)(2 * ac[c] + (q - 3 * c)), -(l + 1));
-                    });
-                run_tests<D, false>(x, elo, ehi, n_int, wl, ac, best != kNoHit);
-                best = min(best, *x.hit);
-                // the children that are not free, in order
-                const bool open = lane < 2 * n_int && ((*x.flag >> lane) & 1u);
-                const unsigned long long bal = __ballot(open);
-                const int at = nn + __popcll(bal & ((1ull << lane) - 1ull));
-                if (open && at < max_active) nxt[at] = 2 * ac[lane >> 1] + (lane & 1);
-                nn += __popcll(bal);
-                __syncthreads();
-            }
-            if (best != kNoHit) {
-                out = kCollides;
-                out_level = l + 1;
-                out_t = ldexp((double)best, -(l + 1));
-                done = true;
-                break;
-            }
-            out_level = l + 1;
-            if (nn == 0) {
-                out = kFree;
-                done = true;
-                break;
-            }
-            // more than max_active stops the search at the next level (or
-            // after the last one) before the list is read again
-            int32_t *const swap = act;
-            act = nxt;
-            nxt = swap;
-            na = nn;
-        }
-        if (!done) {
-            out = kUnresolved;
-            out_level = max_level;
-        }
-    } while (false);
-    __syncthreads();
-    if (lane == 0) {
-        if (verdict) verdict[0] = out;
-        if (level) level[0] = out_level;
-        if (witness) witness[0] = out_t;
-        if (labels) labels[e] = out == kFree ? (uint8_t)RGG_GREEN : (uint8_t)RGG_RED;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        elo[d] = __shfl(elo[d], 0);   // the first lanes hold every sphere's
+        ehi[d] = __shfl(ehi[d], 0);
     }
-    __syncthreads();
 }
 
-// One wavefront per edge.  The search is a chain of dependent binary64 phases
-// per edge, so edges in flight matter more than threads per edge.  A step
-// used to place every sphere of every test from the joint angles anew (an
-// arm's sphere on its last link took all seven sine-cosine pairs, 84 per
-// configuration of a 21-sphere arm instead of 7); with the shared centres and
-// the marked boxes the update + validation of the arm with 56k edges (14.6k of
-// them gray) went from 606 to 289 us, of the spatial body with 116k edges
-// (1.5k gray) from 148 to 119 us.
+// Whether a step looks for candidates to drop: from where a second bounding
+// test per box costs less than the boxes it spares the later levels (most
+// searches end after a level or two).  The whole list has to be known.
+__device__ inline bool culls(const ValCtx &x) { return x.n_cand >= kVCull && x.n_cand <= kVList; }
+
+// The search over an edge's motion; its region, boxes and motion are staged.
 template <int D>
-__global__ __launch_bounds__(kVT) __attribute__((amdgpu_waves_per_eu(4))) void k_validate(
-    ValDev v, ValLds l, const int64_t *ids, int64_t n, const rgg_update_result *count, int max_level, int max_active,
-    uint8_t *verdict, int32_t *level, double *witness, uint8_t *labels)
+__device__ __forceinline__ void search(ValCtx &x, const float *elo, const float *ehi, int max_level,
+                                       int max_active, uint8_t *out, int32_t *out_level, double *out_t)
 {
-    extern __shared__ double sh[];
-    __shared__ int32_t s_hit;
-    __shared__ uint32_t s_flag;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    *out = kFree;
+    *out_level = 0;
+    *out_t = NAN;
+    if (x.n_cand == 0) return;
+    // t = 0, then t = 1, then the whole edge's capsules, and with them the
+    // first level's midpoint and halves
+    if (lane < kVList / kValBoxes) x.keep[lane] = 0ull;
+    x.cull = culls(x);
+    centres<D>(x, 3, [](int q) { return ldexp((double)q, -1); });
+    run_tests<D, true>(x, elo, ehi, 1, 0.5, nullptr, false);
+    int best = *x.hit;
+    uint32_t fl = *x.flag;
+    if (best < 2) {
+        *out = kCollides;
+        *out_t = (double)best;
+        return;
+    }
+    if (!(fl & 4u)) return;
+    int32_t *act = x.si + x.l.act, *nxt = x.si + x.l.nxt;
+    int na = 1;
+    if (lane == 0) act[0] = 0;
+    if (best == 2) best = 1;   // the midpoint's key at level 0
+    wave_sync();
+    for (int l = 0; l < max_level; ++l) {
+        *out_level = l;
+        if (na > max_active) {
+            *out = kUnresolved;
+            return;
+        }
+        const double wl = ldexp(1.0, -(l + 1));
+        int nn = 0;
+        if (l > 0 && x.cull) {
+            drop_candidates<D>(x);
+            if (lane < kVList / kValBoxes) x.keep[lane] = 0ull;
+            x.cull = culls(x);
+        }
+        for (int c0 = 0; c0 < na; c0 += x.l.chunk) {
+            const int n_int = min(x.l.chunk, na - c0);
+            const int32_t *ac = act + c0;
+            if (l > 0) {
+                centres<D>(x, 3 * n_int, [&](int q) {
+                    const int c = q / 3;
+                    return ldexp((double)(2 * ac[c] + (q - 3 * c)), -(l + 1));
+                });
+                run_tests<D, false>(x, elo, ehi, n_int, wl, ac, best != kNoHit);
+                best = min(best, *x.hit);
+                fl = *x.flag;
+            }
+            // the children that are not free, in order
+            const bool open = lane < 2 * n_int && ((fl >> lane) & 1u);
+            const unsigned long long bal = __ballot(open);
+            const int at = nn + __popcll(bal & ((1ull << lane) - 1ull));
+            if (open && at < max_active) nxt[at] = 2 * ac[lane >> 1] + (lane & 1);
+            nn += __popcll(bal);
+            wave_sync();
+        }
+        *out_level = l + 1;
+        if (best != kNoHit) {
+            *out = kCollides;
+            *out_t = ldexp((double)best, -(l + 1));
+            return;
+        }
+        if (nn == 0) return;   // FREE
+        // more than max_active stops the search at the next level (or
+        // after the last one) before the list is read again
+        int32_t *const swap = act;
+        act = nxt;
+        nxt = swap;
+        na = nn;
+    }
+    *out = kUnresolved;
+}
+
+// One wavefront per edge, four to a block.  The search is a chain of dependent
+// binary64 phases per edge (10 us at the median, 30 to 60 for the deepest), so
+// edges in flight matter more than threads per edge.  The grid is what the
+// device holds at once, but no more than gives every wavefront an edge; each of
+// these G blocks takes every G-th edge of the list, its wavefronts claiming
+// them one at a time, so the robot and the resident boxes are staged once and a
+// long search keeps one wavefront, not its block.
+// What bounds it is the latency of the phases: on one update's gray lists,
+//   arm, 13.9k edges:      535 us with each test's centres placed anew and
+//     every box tested by every wavefront, 211 with a configuration's
+//     kinematics computed once, 160 with claimed edges and binary32 near
+//     tests, 117 with candidates dropped between levels (the deepest edges
+//     held 120 boxes through nine levels);
+//   spatial, 1.5k edges:   64, 46, 35, 32 us.
+// The 3-D kernel needs 185 registers: at three blocks per CU it spills (32 us
+// for 1,470 spatial edges against 31), the 2-D one does not (115 us for 13.9k
+// arm edges, 123 at four).
+constexpr int v_blocks_per_cu(int D) { return D == 3 ? 2 : 3; }
+
+template <int D>
+__global__ __launch_bounds__(kVT, v_blocks_per_cu(D)) void k_validate(ValDev v, ValLds l, const int64_t *ids, int64_t n,
+                                                     const rgg_update_result *count, int max_level, int max_active,
+                                                     uint8_t *verdict, int32_t *level, double *witness, uint8_t *labels)
+{
+    extern __shared__ __attribute__((aligned(16))) double sh[];
+    __shared__ int32_t s_hit[kVWaves];
+    __shared__ uint32_t s_flag[kVWaves];
+    __shared__ unsigned long long s_keep[kVWaves][kVList / kValBoxes];
+    __shared__ int32_t s_claim;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     int64_t nn = n;
     if (count) {
         const int64_t g = count->status == RGG_OK ? count->n_gray : 0;
@@ -557,28 +737,59 @@ __global__ __launch_bounds__(kVT) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
     // blocks beyond the list (the grid is sized for its capacity when the
     // count comes from the device) leave at once
-    if ((int64_t)blockIdx.x >= nn) return;
-    ValCtx x = {v, l, sh, reinterpret_cast<int32_t *>(sh), &s_hit, &s_flag, 0};
+    const int64_t full = (nn + kVWaves - 1) / kVWaves;
+    const int64_t G = full < gridDim.x ? full : gridDim.x;
+    if ((int64_t)blockIdx.x >= G) return;
+    double *const mine = sh + l.region0 + wv * l.region;
+    ValCtx x = {v, l, sh, mine, reinterpret_cast<int32_t *>(mine), &s_hit[wv], &s_flag[wv],
+                s_keep[wv], 0, false};
+    // the k-th edge of this block is list entry blockIdx + k G
+    auto entry = [&](int k) { return (int64_t)blockIdx.x + k * G; };
+    int64_t i = entry(wv);
+    int64_t e = i < nn ? ids[i] : -1;
     {
         const VRobot &rb = *v.rob;
         const int per = v.kind == RGG_SE2 ? 2 : (v.kind == RGG_SE3 ? 3 : 1);
-        for (int k = lane; k < v.B * per; k += 64) x.sd[l.pos + k] = rb.pos[k];
-        if (lane < v.B) x.sd[l.rad + lane] = rb.rad[lane];
-        if (lane < v.L) x.sd[l.len + lane] = rb.len[lane];
-        if (v.kind == RGG_PLANAR_ARM && lane < v.B) x.si[l.link + lane] = rb.link[lane];
-    }
-    for (int64_t i = blockIdx.x; i < nn; i += gridDim.x) {
-        const int64_t e = ids[i];
-        if (e < 0 || e >= v.E) {
-            if (lane == 0) {
-                if (verdict) verdict[i] = RGG_VERDICT_BAD_ID;
-                if (level) level[i] = 0;
-                if (witness) witness[i] = NAN;
+        if (tid < v.B * per) sh[l.pos + tid] = rb.pos[tid];
+        if (tid < v.B) sh[l.rad + tid] = rb.rad[tid];
+        if (tid < v.L) sh[l.len + tid] = rb.len[tid];
+        if (tid < v.B) reinterpret_cast<int32_t *>(sh)[l.link + tid] = rb.link[tid];
+        if (tid == 0) s_claim = kVWaves;
+        if (v.M <= kVTile) {
+            for (int k = tid; k < (int)v.M; k += kVT) {
+                float lo[D], hi[D];
+                outward<D>(v.resident[k], lo, hi);
+                put_box32<D>(sh + l.tile, k, lo, hi);
             }
-            continue;
         }
-        validate_one<D>(x, e, max_level, max_active, verdict ? verdict + i : nullptr, level ? level + i : nullptr,
-                        witness ? witness + i : nullptr, labels);
+    }
+    __syncthreads();
+    while (i < nn) {
+        // the next claim and its edge id are under way during this search
+        int k = 0;
+        if (lane == 0) k = atomicAdd(&s_claim, 1);
+        const int64_t i_next = entry(__builtin_amdgcn_readfirstlane(k));
+        const int64_t e_next = i_next < nn ? ids[i_next] : -1;
+        uint8_t out = RGG_VERDICT_BAD_ID;
+        int32_t out_level = 0;
+        double out_t = NAN;
+        const bool ok = e >= 0 && e < v.E;
+        if (ok) {
+            float elo[D], ehi[D];
+            load_edge<D>(x, e, elo, ehi);
+            x.n_cand = v.M > 0 ? list_candidates<D>(x, elo, ehi, 0) : 0;
+            if (x.n_cand <= kValBoxes) stage_page<D>(x, 0, x.n_cand);
+            search<D>(x, elo, ehi, max_level, max_active, &out, &out_level, &out_t);
+            wave_sync();
+        }
+        if (lane == 0) {
+            if (verdict) verdict[i] = out;
+            if (level) level[i] = out_level;
+            if (witness) witness[i] = out_t;
+            if (labels && ok) labels[e] = out == kFree ? (uint8_t)RGG_GREEN : (uint8_t)RGG_RED;
+        }
+        i = i_next;
+        e = e_next;
     }
 }
 
@@ -589,8 +800,12 @@ hipError_t launch_validate(const ValDev &v, const int64_t *ids, int64_t n, const
                            double *witness, uint8_t *labels, hipStream_t s, hipEvent_t done)
 {
     if (n <= 0) return done ? hipEventRecord(done, s) : hipSuccess;
-    const int grid = (int)(n < kVGrid ? n : kVGrid);
     const ValLds l = val_lds(v, max_active);
+    // the blocks that the device holds at once, by registers and by LDS
+    const int64_t fit = (160 * 1024) / (l.bytes + 256), most = v_blocks_per_cu(v.D);
+    const int64_t held = (int64_t)v.n_cu * (fit < 1 ? 1 : (fit > most ? most : fit));
+    const int64_t full = (n + kVWaves - 1) / kVWaves;
+    const int grid = (int)(full < held ? full : held);
     void *args[] = {(void *)&v,         (void *)&l,       (void *)&ids,     (void *)&n,     (void *)&count,   (void *)&max_level,
                     (void *)&max_active, (void *)&verdict, (void *)&level, (void *)&witness, (void *)&labels};
     return launch_marked(v.D == 3 ? (void *)k_validate<3> : (void *)k_validate<2>, dim3(grid), dim3(kVT), args, s,
