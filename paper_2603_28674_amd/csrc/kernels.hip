@@ -716,17 +716,20 @@ __device__ inline void retest_one(const RmDev &rm, int64_t e, int ci, int *lst, 
 //      box meets its edge's box, 32 per LDS word.  With several grid cells a
 //      pair is taken only by the cell holding the lower corner of the two
 //      boxes' intersection, so each (edge, entry) pair is tested once.
-//   2. outer test, lanes = (pair, sphere): separation and end-sphere tests
-//      first; the tests they leave open are queued in LDS and run densely
-//      with the exact segment-box minimum.  Each pair keeps the sphere whose
-//      capsule met deepest and the configuration nearest the capsule axis'
-//      closest point to the box.
-//   3. probe: that one copy is tested first.  S is an existence test, so a
-//      copy found to meet settles the pair and its other copies are not
-//      tested; the result is the same, only the order of the tests changes.
-//   4. inner test of the pairs the probe left open, rows = (pair, sphere
-//      whose capsule met), lanes = configurations: every copy of those
-//      spheres.
+//   2. outer test, lanes = (pair, sphere): the capsule's ends are two of the
+//      sphere's copies, and one that meets settles the pair (S is an existence
+//      test, and S implies C); separation and end-sphere tests settle most of
+//      the rest, and the tests left open are queued in LDS and run densely
+//      with the exact segment-box minimum.
+//   3. probe: a queued capsule that meets tests the copy nearest to where its
+//      axis came closest to the box.
+//   4. inner test of the pairs still open, rows = (pair, sphere whose capsule
+//      met), lanes = configurations: every copy of those spheres.
+//      The end copies settle most pairs that end RED before any exact test or
+//      copy: kernel 49 -> 43 us on 290k spatial edges with 100 changed boxes;
+//      the binary64 kernel, which ran the exact minimum (seven divisions) on
+//      every capsule, 35 -> 22 us on 11.6k planar edges, 49 -> 31 us on 46k
+//      spatial ones.
 //   5. per pair C and S; the edge's counter deltas are summed in LDS and
 //      added once per edge.  In FP32 a pair whose decision fell inside the
 //      rounding band goes to the block's re-test region, decided in binary64
@@ -784,7 +787,6 @@ struct ItemLds {
     int dC[kItemCap], dS[kItemCap];
     uint32_t pe[kPairCap];                // edge slot << 16 | staged entry
     unsigned long long hm[kPairCap], um[kPairCap];
-    uint32_t key[kPairCap];               // probe_key of the deepest capsule hit
     // the capsule-test queue is dead once the exact part has run; the rows
     // and their copy offsets live after it, in the same storage, and after
     // the decisions it is the scratch of a binary64 overflow re-test
@@ -839,20 +841,33 @@ __device__ inline int slab_of(const RmDev &rm, int d, float x, int n)
     return (int)fminf(fmaxf(f, 0.0f), (float)(n - 1));
 }
 
-// order-preserving map of a binary32 value to an unsigned key
-__device__ inline uint32_t ordered_key(float f)
+// Binary64 counterpart of the band, for the quick tests of the binary64
+// kernel: a decision farther than this from the threshold is what the binary64
+// definition computes, whatever its rounding (every term of a squared distance
+// is made of coordinates at most s + L in size and gaps; 1e-12 is about 9,000
+// roundings of each).  As wide as the capsule test's also where an end copy is
+// tested, so that a copy that meets implies its capsule does.
+__device__ inline double band64_of(double s, double R, double L)
 {
-    const uint32_t u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    if (!(s <= 1048576.0 * R)) return INFINITY;
+    return 1e-12 * ((s + R) * (R + L) + L * L);
 }
 
-// Probe key of a capsule hit: the margin's order (16 high bits), the
-// parameter of the closest point (10 bits) and the sphere (6 bits); the
-// minimum over a pair's hits names its deepest one.
-__device__ inline uint32_t probe_key(float mg, float t, int sphere)
+__device__ inline float fabs_of(float x) { return fabsf(x); }
+__device__ inline double fabs_of(double x) { return fabs(x); }
+__device__ inline float max_of(float a, float b) { return fmaxf(a, b); }
+__device__ inline double max_of(double a, double b) { return fmax(a, b); }
+__device__ inline float min_of(float a, float b) { return fminf(a, b); }
+__device__ inline double min_of(double a, double b) { return fmin(a, b); }
+template <int D>
+__device__ inline float point_box_of(const float *c, const float *lo, const float *hi)
 {
-    const uint32_t tq = (uint32_t)fminf(fmaxf(t, 0.0f) * 1023.0f + 0.5f, 1023.0f);
-    return (ordered_key(mg) & 0xFFFF0000u) | (tq << 6) | (uint32_t)sphere;
+    return point_box32<D>(c, lo, hi);
+}
+template <int D>
+__device__ inline double point_box_of(const double *c, const double *lo, const double *hi)
+{
+    return point_box64<D>(c, lo, hi);
 }
 
 // A step in [1, n) coprime with n, near n / 2 (1 for n <= 2): k * step % n
@@ -903,31 +918,20 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
         if constexpr (kF32) return k == 0 ? L.bhi[s].x : (k == 1 ? L.bhi[s].y : L.bhi[s].z);
         else return L.x.hi[k][s];
     };
-    // per-pair results start empty (kPairCap == kBlock: pair tid)
-    if (tid < np) {
-        L.hm[tid] = 0ull;
-        L.um[tid] = 0ull;
-        L.key[tid] = ~0u;
-    }
-    if (tid == 0) L.nopen = 0;
-    __syncthreads();
+    __syncthreads();   // the round's pairs are in L.pe
     n_pairs += np;
-    // a (pair, sphere) result: capsule hit bits, the deepest hit as
-    // the probe key, undecided bits
-    auto record = [&](int p, int i, int cls, float mg, float tpar) {
-        if (cls == kHit) {
-            atomicOr(&L.hm[p], 1ull << i);
-            atomicMin(&L.key[p], probe_key(mg, tpar, i));
-        } else if (cls == kUnsure) {
-            atomicOr(&L.um[p], 1ull << i);
-        }
-    };
-    // ---- outer test, quick part: lanes = (pair, sphere); each lane
-    // takes two pairs per step and issues both capsules' loads first.
-    // FP32 lanes the quick tests leave open are queued for the exact
-    // part, so the segment-box minimum runs on dense wavefronts.
+    // ---- outer test, quick part: lanes = (pair, sphere), the spheres of a
+    // pair on consecutive lanes; each lane takes two pairs per step and issues
+    // both capsules' loads first.  A capsule's ends are the sphere's first and
+    // last copies, so an end within the sphere's own radius of the box settles
+    // the whole pair (S, hence C): most pairs that end RED stop here, before
+    // any exact test, probe or copy.  A separating axis is a certain miss, an
+    // end within the capsule's radius a certain hit; what is left open is
+    // queued for the exact part, which runs it on dense wavefronts.  "Certain"
+    // is beyond the rounding band in both precisions.
     constexpr int kCapU = 2;
     const int slot = s_lane[lane] >> 8, ci = s_lane[lane] & 255;
+    const uint64_t gm = (B == 64 ? 0ull : 1ull << B) - 1ull;   // a pair's lanes, from lane slot * B on
     for (int p0 = 0; p0 < np; p0 += kWaves * Gw * kCapU) {
         T A[kCapU][D], Bq[kCapU][D], R2[kCapU];
         int pu[kCapU];
@@ -951,70 +955,83 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
             const int p = pu[u];
             const bool act = slot < Gw && p < np;
             int cls = kMiss;
-            T lo[D], hi[D];
-            float band = 0.0f, mg = 0.0f, tpar = 0.0f;
-            const T R = R2[u];
-            const T RR = R * R;
+            bool met = false;   // an end copy meets
             if (act) {
                 const int s = pe_entry(L.pe[p]);
+                T lo[D], hi[D];
 #pragma unroll
                 for (int k = 0; k < D; ++k) {
                     lo[k] = box_lo(k, s);
                     hi[k] = box_hi(k, s);
                 }
-                if constexpr (kF32) {
-                    const float sc = fmaxf(L.es[pe_slot(L.pe[p])], L.blo[s].w);
-                    float len = 0.0f;
+                const float sc = fmaxf(L.es[pe_slot(L.pe[p])], L.blo[s].w);
+                const T R = R2[u], RR = R * R;
+                T len = T(0), sep = T(0);
 #pragma unroll
-                    for (int k = 0; k < D; ++k) len += fabsf(Bq[u][k] - A[u][k]);
-                    band = band_of(band_rel, sc, R, len);
-                    float sep = 0.0f;
-#pragma unroll
-                    for (int k = 0; k < D; ++k)
-                        sep = fmaxf(sep, fmaxf(lo[k] - fmaxf(A[u][k], Bq[u][k]), fminf(A[u][k], Bq[u][k]) - hi[k]));
-                    const float dA = point_box32<D>(A[u], lo, hi), dB = point_box32<D>(Bq[u], lo, hi);
-                    mg = fminf(dA, dB) - RR;
-                    tpar = dA <= dB ? 0.0f : 1.0f;
-                    cls = (sep > 0.0f && sep * sep - RR > band) ? kMiss : (mg < -band ? kHit : kOpen);
-                } else {
-                    double ts;
-                    const double v = segbox64<D>(A[u], Bq[u], lo, hi, &ts);
-                    cls = v <= RR ? kHit : kMiss;
-                    mg = (float)(v - RR);
-                    tpar = (float)ts;
+                for (int k = 0; k < D; ++k) {
+                    len += fabs_of(Bq[u][k] - A[u][k]);
+                    sep = max_of(sep, max_of(lo[k] - max_of(A[u][k], Bq[u][k]), min_of(A[u][k], Bq[u][k]) - hi[k]));
                 }
+                T band, rband;
+                if constexpr (kF32) {
+                    band = band_of(band_rel, sc, R, len);
+                    rband = band_of(band_rel, sc, L.r.r32[ci], 0.0f);
+                } else {
+                    band = band64_of((double)sc, R, len);
+                    rband = band;
+                }
+                const T ends = min_of(point_box_of<D>(A[u], lo, hi), point_box_of<D>(Bq[u], lo, hi));
+                met = !kSpl && ends - s_rad2[ci] < -rband;
+                cls = (sep > T(0) && sep * sep - RR > band) ? kMiss : (ends - RR < -band ? kHit : kOpen);
             }
-            if constexpr (kF32) {
-                const bool op = cls == kOpen;
-                const uint64_t ob = __ballot(op);
-                if (ob) {
-                    int base = 0;
-                    if (lane == 0) base = atomicAdd(&L.nopen, __popcll(ob));
-                    base = __shfl(base, 0);
-                    if (op) {
-                        const int q = base + __popcll(ob & lanes_below());
-                        if (q < kOpenCap) {
-                            L.u.open[q] = ((uint32_t)p << 6) | (uint32_t)ci;
-                            cls = kMiss;     // decided by the exact part
-                        } else {
-                            cls = kUnsure;   // queue full: the binary64 re-test decides
+            const uint64_t metb = (__ballot(met) >> (slot * B)) & gm;
+            const uint64_t hitb = (__ballot(cls == kHit) >> (slot * B)) & gm;
+            if (act && ci == 0) {
+                L.hm[p] = metb ? metb : hitb;
+                L.um[p] = 0ull;
+                L.sf[p] = metb ? 1u : 0u;
+            }
+            const bool op = act && cls == kOpen && !metb;
+            const uint64_t ob = __ballot(op);
+            if (ob) {
+                int base = 0;
+                if (lane == 0) base = atomicAdd(&L.nopen, __popcll(ob));
+                base = __shfl(base, 0);
+                if (op) {
+                    const int q = base + __popcll(ob & lanes_below());
+                    if (q < kOpenCap) {
+                        L.u.open[q] = ((uint32_t)p << 6) | (uint32_t)ci;
+                    } else if constexpr (kF32) {
+                        atomicOr(&L.um[p], 1ull << ci);   // queue full: the binary64 re-test decides
+                    } else {
+                        const int s = pe_entry(L.pe[p]);   // queue full: decided at once
+                        double lo[D], hi[D];
+#pragma unroll
+                        for (int k = 0; k < D; ++k) {
+                            lo[k] = box_lo(k, s);
+                            hi[k] = box_hi(k, s);
                         }
+                        if (segbox64<D>(A[u], Bq[u], lo, hi) <= R2[u] * R2[u]) atomicOr(&L.hm[p], 1ull << ci);
                     }
                 }
             }
-            if (act) record(p, ci, cls, mg, tpar);
         }
     }
     __syncthreads();
-    if constexpr (kF32) {
-        // ---- outer test, exact part: the queued tasks, one per lane
+    {
+        // ---- outer test, exact part: the queued tests, one per lane.  A
+        // capsule that meets probes the copy nearest to where it came
+        // closest: S is an existence test, so a copy found to meet settles the
+        // pair (in the copy form; in binary64 with the oriented boxes the
+        // sphere's box is not yet known to meet).
+        constexpr bool kProbe = !kSpl && (kF32 || !kObb);
         const int nq = min(L.nopen, kOpenCap);
         for (int q = tid; q < nq; q += kBlock) {
             const uint32_t tk = L.u.open[q];
             const int p = (int)(tk >> 6), i = (int)(tk & 63u);
             const uint32_t pv = L.pe[p], te = pe_slot(pv), s = pe_entry(pv);
-            const float *cp = (const float *)capb + (int64_t)L.edge[te] * (2 * D + 1) * B;
-            float A[D], Bq[D], lo[D], hi[D];
+            const T *cp = capb + (int64_t)L.edge[te] * (2 * D + 1) * B;
+            T A[D], Bq[D], lo[D], hi[D];
 #pragma unroll
             for (int k = 0; k < D; ++k) {
                 A[k] = cp[k * B + i];
@@ -1022,14 +1039,38 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
                 lo[k] = box_lo(k, s);
                 hi[k] = box_hi(k, s);
             }
-            const float R = cp[2 * D * B + i];
+            const T R = cp[2 * D * B + i];
             const float sc = fmaxf(L.es[te], L.blo[s].w);
-            float len = 0.0f;
-#pragma unroll
-            for (int k = 0; k < D; ++k) len += fabsf(Bq[k] - A[k]);
+            int cls;
             float ts;
-            const float mg = segbox32<D>(A, Bq, lo, hi, ts) - R * R;
-            record(p, i, classify_margin(mg, band_of(band_rel, sc, R, len)), mg, ts);
+            if constexpr (kF32) {
+                float len = 0.0f;
+#pragma unroll
+                for (int k = 0; k < D; ++k) len += fabsf(Bq[k] - A[k]);
+                const float mg = segbox32<D>(A, Bq, lo, hi, ts) - R * R;
+                cls = classify_margin(mg, band_of(band_rel, sc, R, len));
+                if (cls == kUnsure) atomicOr(&L.um[p], 1ull << i);
+            } else {
+                double t64;
+                cls = segbox64<D>(A, Bq, lo, hi, &t64) <= R * R ? kHit : kMiss;
+                ts = (float)t64;
+            }
+            if (cls != kHit) continue;
+            atomicOr(&L.hm[p], 1ull << i);
+            if constexpr (kProbe) {
+                if (__hip_atomic_load(&L.sf[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) continue;
+                const int Je = L.ej[te];
+                const int jj = min(Je - 1, (int)(fminf(fmaxf(ts, 0.0f), 1.0f) * (float)(Je - 1) + 0.5f));
+                T c[D];
+                load_copy<D>(samp, (int64_t)L.cfg0[te] * B + (int64_t)i * Je + jj, c);
+                bytes += D * sizeof(T);
+                bool meet;
+                if constexpr (kF32)
+                    meet = point_box32<D>(c, lo, hi) - s_rad2[i] < -band_of(band_rel, sc, L.r.r32[i], 0.0f);
+                else
+                    meet = point_box64<D>(c, lo, hi) <= s_rad2[i];
+                if (meet) atomicOr(&L.sf[p], 1u);
+            }
         }
         __syncthreads();
     }
@@ -1039,7 +1080,7 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
         // whose body's box misses is dropped (decided in binary64)
         if (tid < np) {
             const uint64_t cnd = L.hm[tid] | (kF32 ? L.um[tid] : 0ull);
-            if (cnd) {
+            if (cnd && !L.sf[tid]) {
                 const uint32_t pv = L.pe[tid], te = pe_slot(pv), s = pe_entry(pv);
                 double lo[D], hi[D];
                 if constexpr (kF32) {
@@ -1070,41 +1111,15 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
         }
         __syncthreads();
     }
-    // ---- probe: one copy per pair whose capsule met (the copy
-    // form only; a sphere the boxes dropped is not probed)
+    // ---- rows: one per (open pair, sphere whose capsule met)
     const int p = tid;   // kPairCap == kBlock: this thread's pair
-    uint32_t f = 0;
     uint64_t hmp = 0;
+    int ra = 0;
     if (p < np) {
         hmp = L.hm[p];
-        if (hmp && !kSpl && (!kObb || ((hmp >> (L.key[p] & 63u)) & 1ull))) {
-            const uint32_t key = L.key[p];
-            const int i = (int)(key & 63u);
-            const uint32_t pv = L.pe[p], te = pe_slot(pv), s = pe_entry(pv);
-            const int Je = L.ej[te];
-            // the configuration nearest the deepest capsule's closest point
-            const int jj = min(Je - 1, (int)((float)((key >> 6) & 1023u) * (1.0f / 1023.0f) * (float)(Je - 1) + 0.5f));
-            T q[D], lo[D], hi[D];
-            load_copy<D>(samp, (int64_t)L.cfg0[te] * B + (int64_t)i * Je + jj, q);
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-                lo[k] = box_lo(k, s);
-                hi[k] = box_hi(k, s);
-            }
-            bytes += D * sizeof(T);
-            if constexpr (kF32) {
-                const float sc = fmaxf(L.es[te], L.blo[s].w);
-                const int cls = classify_margin(point_box32<D>(q, lo, hi) - s_rad2[i],
-                                                band_of(band_rel, sc, L.r.r32[i], 0.0f));
-                f = cls == kHit ? 1u : (cls == kUnsure ? 2u : 0u);
-            } else {
-                f = point_box64<D>(q, lo, hi) <= s_rad2[i] ? 1u : 0u;
-            }
-        }
-        L.sf[p] = f;
+        ra = L.sf[p] ? 0 : __popcll(hmp);
     }
-    // ---- rows: one per (open pair, sphere whose capsule met)
-    const int ra = (p < np && !(f & 1u)) ? __popcll(hmp) : 0;
+    if (tid == 0) L.nopen = 0;   // for the next round
     int nrows;
     const int rpre = block_scan(ra, &nrows, L.wsum);
     __syncthreads();
@@ -1354,6 +1369,7 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int deferred, int li0
         if (tid < B) L.r.r32[tid] = (float)rm.rad64[tid];
     }
     if (tid == 0) {
+        L.nopen = 0;
         L.rc_n = (kCont && kF32 && !deferred) ? rm.rc_cnt[blockIdx.x] : 0;
         L.pl_n = 0;
     }
@@ -1909,7 +1925,6 @@ struct ShareLds {
     float es[kPairCap];                   // edge s (largest |coordinate| of its box)
     uint32_t pe[kPairCap];                // pair << 16 | pair
     unsigned long long hm[kPairCap], um[kPairCap];
-    uint32_t key[kPairCap];
     union alignas(8) {
         uint32_t open[kOpenCap];
         struct {
@@ -1940,7 +1955,10 @@ __device__ __forceinline__ void share_body(const RmDev &rm)
         s_rad2[tid] = rm.rad2_32[tid];
         L.r.r32[tid] = (float)rm.rad64[tid];
     }
-    if (tid == 0) L.rc_n = 0;   // pairs queued in this share's re-test region
+    if (tid == 0) {
+        L.nopen = 0;
+        L.rc_n = 0;   // pairs queued in this share's re-test region
+    }
     // prefix of the regions' pair counts: kPer consecutive regions per thread
     constexpr int kPer = kStatBlocks / kBlock;
     static_assert(kStatBlocks % kBlock == 0, "regions are scanned kPer per thread");
