@@ -144,13 +144,11 @@ typedef struct {
     double cell_size;             /* grid cell edge; 0 = heuristic; < 0 = one
                                      cell covering everything                   */
     int32_t host_threads;         /* threads for the host build; 0 = automatic  */
-    int32_t retest_capacity;      /* FP32 mode: undecided pairs each item block
-                                     (at most 2048 of them) may queue for the
-                                     binary64 re-test, over all the items it
-                                     takes of this roadmap in one update,
-                                     before it leaves a whole work item to the
-                                     binary64 pass instead; 0 = 1024, at most
-                                     2^20.  Any value gives the same labels.   */
+    int32_t retest_capacity;      /* FP32 mode: undecided pairs a block of the
+                                     item kernel collects before it re-tests
+                                     them in binary64, 1..2^20; 0 = the most a
+                                     block can hold, 64, as does any larger
+                                     value.  Any value gives the same labels.   */
     int32_t item_edges;           /* edges per work item of the classify
                                      kernels (one block of 256 threads each,
                                      up to two edges per thread), 1..512;
@@ -217,10 +215,10 @@ typedef struct {
     int64_t n_cells_visited;      /* (cell, edge) entries scanned by the grid   */
     int64_t test_bytes;           /* bytes the classify kernels read and wrote:
                                      the item kernel, the balanced pair testing
-                                     and the binary64 pass together             */
+                                     and the binary64 re-tests together         */
     int64_t item_bytes;           /* the FP32 item kernel's part of test_bytes
                                      (its pair listing and inline pair tests)   */
-    int64_t fp64_bytes;           /* the binary64 pass's part of test_bytes     */
+    int64_t fp64_bytes;           /* the binary64 re-tests' part of test_bytes  */
 } rgg_update_result;
 
 typedef struct {
@@ -334,7 +332,7 @@ rgg_status rgg_batch_destroy(rgg_batch *b);
  * on the launch's stream: rgg_batch_timing_read returns the summed
  * milliseconds of each stage over the launches since the last read and
  * resets them: ms[0] diff, ms[1] grid cells, ms[2] 0, ms[3] the item kernels,
- * ms[4] the binary64 pass, ms[5] labels and gray lists.  It waits for the
+ * ms[4] 0, ms[5] labels and gray lists.  It waits for the
  * timed launches. */
 rgg_status rgg_batch_timing_enable(rgg_batch *b, int32_t on);
 rgg_status rgg_batch_timing_read(rgg_batch *b, double ms[6], int64_t *n_launches);
@@ -347,7 +345,7 @@ rgg_status rgg_update_batch(rgg_context *ctx, int32_t n, const rgg_update_req *r
  * hipMalloc, such as tight serving loops or harnesses that forbid it): the
  * batched update of rgg_update_batch, computing the same results, with the
  * request table in a fixed device array that the library holds (one per
- * device, up to 256 requests, 121 KiB, kept until the process ends)
+ * device, up to 256 requests, 111 KiB, kept until the process ends)
  * instead of a batch created per call.  Calls no allocator: no hipMalloc,
  * hipFree, pinned or pageable host allocation, graph or event creation.
  * Arguments as rgg_update_batch (device pointers in reqs, queued on
@@ -573,7 +571,8 @@ rgg_status rgg_gray_list(rgg_roadmap *rm, int64_t *out, int64_t cap, int64_t *n)
  * ms[0] diff, ms[1] grid cells, ms[2] the FP32 item kernel (pair listing
  * and the inline pair tests: every test by default), ms[3] the balanced pair
  * testing (FP32 mode with pair listing) or the binary64 item kernel (FP64
- * mode), ms[4] FP64 re-test, ms[5] labels and gray compaction.  *n_updates
+ * mode), ms[4] the events alone (the FP64 re-test is
+ * part of the kernels that test the pairs), ms[5] labels and gray compaction.  *n_updates
  * receives the number of updates timed.  Each event adds a few microseconds
  * to the timeline of a timed update. */
 rgg_status rgg_timing_enable(rgg_roadmap *rm, int32_t on);

@@ -71,7 +71,7 @@ rgg_status install_grid(rgg_roadmap *rm, const HostGrid &grid, int32_t chunk)
     RmDev &dv = rm->dv;
     const int64_t ncells = (int64_t)grid.dim[0] * grid.dim[1] * grid.dim[2];
     const size_t ncw = (size_t)((ncells + 31) / 32);
-    int32_t *cstart = nullptr, *cedges = nullptr, *df = nullptr;
+    int32_t *cstart = nullptr, *cedges = nullptr;
     uint32_t *bits = nullptr;
     int2 *items = nullptr;
     int4 *cslot = nullptr;
@@ -79,7 +79,6 @@ rgg_status install_grid(rgg_roadmap *rm, const HostGrid &grid, int32_t chunk)
         rm->release(cstart);
         rm->release(cedges);
         rm->release(bits);
-        rm->release(df);
         rm->release(items);
         rm->release(cslot);
         return s;
@@ -88,8 +87,6 @@ rgg_status install_grid(rgg_roadmap *rm, const HostGrid &grid, int32_t chunk)
     if ((st = rm->upload(&cstart, grid.start.data(), grid.start.size(), "grid starts")) != RGG_OK) return undo(st);
     if ((st = rm->upload(&cedges, grid.edges.data(), grid.edges.size(), "grid lists")) != RGG_OK) return undo(st);
     if ((st = rm->alloc(&bits, ncw, "cell marks")) != RGG_OK) return undo(st);
-    if ((st = rm->alloc(&df, (size_t)std::max<int64_t>(grid.items_cap, 1), "deferred items")) != RGG_OK)
-        return undo(st);
     if (ncells == 1) {
         // the one cell's work items never change: (0, h) for every chunk h
         std::vector<int2> fixed((size_t)grid.items_cap);
@@ -112,14 +109,12 @@ rgg_status install_grid(rgg_roadmap *rm, const HostGrid &grid, int32_t chunk)
     rm->release(dv.cell_start);
     rm->release(dv.cell_edges);
     rm->release(dv.cell_bits);
-    rm->release(dv.df);
     rm->release(dv.items);
     rm->release(dv.cell_slot);
     dv.cell_start = cstart;
     dv.cell_edges = cedges;
     dv.cell_slot = cslot;
     dv.cell_bits = bits;
-    dv.df = df;
     dv.items = items;
     dv.chunk = chunk;
     for (int d = 0; d < 3; ++d) {
@@ -486,22 +481,16 @@ int64_t device_bytes_needed(const HostGeometry &g, const HostGrid &grid, const R
     add(grid.edges.size(), 4);
     if (ncells > 1 && !grid.edges.empty()) add(grid.edges.size(), sizeof(int4));
     add((size_t)((ncells + 31) / 32), 4);
-    add((size_t)std::max<int64_t>(grid.items_cap, 1), 4);
     add((size_t)grid.items_cap, sizeof(int2));
     const int64_t ntiles = std::max<int64_t>(1, (E + kLabelTile - 1) / kLabelTile);
-    const int32_t rc_cap = p.retest_capacity > 0 ? p.retest_capacity : kRcCap;
     add((size_t)E, sizeof(int2));
     add((size_t)M, sizeof(rgg_box));
     add((size_t)(2 * M), sizeof(ChgEntry));
-    add((size_t)kStatBlocks * rc_cap, sizeof(int2));
-    add((size_t)kStatBlocks, 4);
     if (p.mixed) {
         add((size_t)kStatBlocks, 4);
         if (p.inline_rounds != kInlineAll) {
             const int32_t pl_cap = p.pair_list_capacity > 0 ? p.pair_list_capacity : kPairListCap;
             add((size_t)kStatBlocks * pl_cap, sizeof(int2));
-            add((size_t)kStatBlocks * rt_cap_of(pl_cap), sizeof(int2));
-            add((size_t)kStatBlocks, 4);
         }
     }
     add((size_t)kStatBlocks * kStats, 8);
@@ -648,9 +637,7 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
     if ((st = rm->upload(&dv.resident, resident ? resident : absent.data(), (size_t)M, "obstacle slots")) != RGG_OK)
         return guard(st);
     if ((st = rm->alloc(&dv.chg, (size_t)(2 * M), "changed entries")) != RGG_OK) return guard(st);
-    dv.rc_cap = p.retest_capacity > 0 ? p.retest_capacity : kRcCap;
-    if ((st = rm->alloc(&dv.rc, (size_t)kStatBlocks * dv.rc_cap, "re-test regions")) != RGG_OK) return guard(st);
-    if ((st = rm->alloc(&dv.rc_cnt, (size_t)kStatBlocks, "re-test counts")) != RGG_OK) return guard(st);
+    dv.rc_cap = p.retest_capacity > 0 ? std::min(p.retest_capacity, kRcCap) : kRcCap;
     if (mixed) {
         dv.pl_cap = p.pair_list_capacity > 0 ? p.pair_list_capacity : kPairListCap;
         dv.inline_rounds = p.inline_rounds;
@@ -659,14 +646,10 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
         if (he != hipSuccess) return guard(hip_fail(he, "occupancy query"));
         dv.test_slots = slots;
         // the listing kernel writes its blocks' pair counts in every form;
-        // the lists and the shares' re-test regions exist only with listing
+        // the lists exist only with listing
         if ((st = rm->alloc(&dv.pl_cnt, (size_t)kStatBlocks, "pair list counts")) != RGG_OK) return guard(st);
         if (dv.inline_rounds != kInlineAll) {
             if ((st = rm->alloc(&dv.pl, (size_t)kStatBlocks * dv.pl_cap, "pair lists")) != RGG_OK) return guard(st);
-            if ((st = rm->alloc(&dv.rt, (size_t)kStatBlocks * rt_cap_of(dv.pl_cap), "share re-test regions")) !=
-                RGG_OK)
-                return guard(st);
-            if ((st = rm->alloc(&dv.rt_cnt, (size_t)kStatBlocks, "share re-test counts")) != RGG_OK) return guard(st);
         }
     }
     if ((st = rm->alloc(&dv.blk_stats, (size_t)kStatBlocks * kStats, "statistics")) != RGG_OK) return guard(st);
@@ -729,13 +712,8 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
     if (st != RGG_OK) return guard(st);
     if ((st = hip_ok(hipMemset(dv.ctl, 0, sizeof(Ctl)), "clear control")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipMemset(dv.tile_state, 0, sizeof(unsigned long long) * dv.ntiles), "clear tile states")) != RGG_OK) return guard(st);
-    if ((st = hip_ok(hipMemset(dv.rc_cnt, 0, sizeof(int32_t) * kStatBlocks), "clear re-test counts")) != RGG_OK) return guard(st);
     if (mixed) {
         if ((st = hip_ok(hipMemset(dv.pl_cnt, 0, sizeof(int32_t) * kStatBlocks), "clear pair list counts")) != RGG_OK)
-            return guard(st);
-        if (dv.rt_cnt &&
-            (st = hip_ok(hipMemset(dv.rt_cnt, 0, sizeof(int32_t) * kStatBlocks), "clear share re-test counts")) !=
-                RGG_OK)
             return guard(st);
     }
     if ((st = hip_ok(hipMemset(dv.blk_stats, 0, sizeof(unsigned long long) * kStatBlocks * kStats), "clear statistics")) != RGG_OK) return guard(st);

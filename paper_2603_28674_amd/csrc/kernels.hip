@@ -17,10 +17,8 @@
 //               rest for
 //   k_pairs     which cuts the listed pairs into equal shares, one per
 //               block, and runs the same tests on them.  In the FP32 mode a
-//               pair whose margin falls inside the rounding band is left to
-//   k_fp64      which decides it in binary64, one wavefront per pair; an
-//               item whose block ran out of re-test room is then run again
-//               whole in binary64 by the same kernel (skipped otherwise);
+//               pair whose margin falls inside the rounding band is decided
+//               in binary64 by the block that tested it;
 //   k_labels    labels from the counters and the ordered gray list, in one
 //               pass (k_count + k_write, the two-pass form, serve the label
 //               queries and the batch).
@@ -32,9 +30,8 @@
 // Hot loops keep off single global counters: on MI355X device-scope atomics
 // on one address serialise across the eight XCDs, so work lists are
 // positional and statistics go to 256 rows shared through atomics.  The few
-// single-address counters are k_labels' tickets (one per 4096-edge tile),
-// the batched item kernel's claims (one per item past two per block) and
-// the rare appends to a roadmap's list of items left whole.
+// single-address counters are k_labels' tickets (one per 4096-edge tile) and
+// the batched item kernel's claims (one per item past two per block).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -51,14 +48,9 @@ constexpr int kDiffBlock = 1024;
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
 constexpr int kGrid = kStatBlocks; // blocks of the item kernels
-constexpr int kFp64Grid = 256;     // blocks of the binary64 pass of the FP32 mode
 constexpr int kBatchItemGrid = 1024;  // blocks of a batched item kernel: the blocks of the
                                       // FP32 kernel resident at once (4 per CU, 256 CUs)
 constexpr int kBatchStatic = 2;       // items a batched item block takes before it claims
-constexpr int kFp64BatchGrid = 32; // blocks per roadmap of the batched binary64 pass
-static_assert(kStatBlocks % kFp64Grid == 0 && kStatBlocks / kFp64BatchGrid <= 64, "re-test regions per block");
-static_assert(kBatchItemGrid <= kStatBlocks, "a batched item block's row and region exist");
-static_assert(kFp64Grid <= kStatRows && kFp64BatchGrid <= kStatRows, "a binary64 block owns a statistics row");
 static_assert(kStatBlocks % 256 == 0, "statistics rows are folded 256 at a time");
 
 enum : int { kMiss = 0, kHit = 1, kUnsure = 2, kOpen = 3 };
@@ -415,7 +407,6 @@ __device__ __forceinline__ void diff_body(const RmDev &rm, const rgg_box *__rest
         s_base = 0;
         s_any = 0;
         rm.ctl->n_items = 0;
-        rm.ctl->n_df = 0;
         rm.ctl->claim = 0;
         rm.ctl->label_ticket = 0;
     }
@@ -553,7 +544,7 @@ __device__ inline void load_copy(const T *samp, int64_t idx, T (&q)[D])
 }
 
 // ------------------------------------------------------------------------
-// binary64 re-test of one (edge, box) pair by one wavefront: the definition
+// binary64 re-test of an (edge, box) pair by one wavefront: the definition
 // (C = some capsule meets, S = some sphere's capsule and one of its copies
 // meet), used for the pairs whose binary32 decision fell inside the band
 // ------------------------------------------------------------------------
@@ -574,7 +565,7 @@ __device__ inline CopyMap copy_map(int J)
 }
 
 template <int D>
-__device__ bool copies_meet64(const RmDev &rm, const double *sb, int64_t P, const CopyMap &cm, uint64_t m,
+__device__ bool copies_meet64(const RmDev &rm, const double *sb, const CopyMap &cm, uint64_t m,
                               const double *lo, const double *hi, const double *rad, int *lst,
                               unsigned long long *bytes)
 {
@@ -639,71 +630,6 @@ __device__ bool splines_meet64(const RmDev &rm, int64_t e, uint64_t m, const dou
     return false;
 }
 
-// Binary64 decision of one (edge e, changed entry ci) pair by one wavefront:
-// C and S by their definition (capsules, the oriented boxes, then copies or
-// spline segments), added to the edge's counters.  lst: 64 ints of LDS for
-// the wavefront; rad: the binary64 radii in LDS.
-template <int D, int MODE>
-__device__ inline void retest_one(const RmDev &rm, int64_t e, int ci, int *lst, const double *rad, uint32_t &n_outer,
-                                  unsigned long long &bytes)
-{
-    const int lane = lane_id();
-    const int B = rm.B;
-    const ChgEntry &en = rm.chg[ci];
-    double lo[D], hi[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        lo[d] = en.lo[d];
-        hi[d] = en.hi[d];
-    }
-    // the edge's sample range is loaded with its capsules: it is needed as
-    // soon as one capsule meets, and would otherwise add a round trip
-    int64_t s0 = 0, P = 0;
-    if constexpr ((MODE & kModeSplines) == 0) {
-        s0 = rm.p_fixed ? e * rm.p_fixed : rm.soff[e];
-        P = rm.p_fixed ? rm.p_fixed : rm.soff[e + 1] - s0;
-    }
-    bool hit = false;
-    if (lane < B) {
-        const double *cp = rm.cap64 + e * (2 * D + 1) * B;
-        double A[D], Bp[D];
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            A[d] = cp[d * B + lane];
-            Bp[d] = cp[(D + d) * B + lane];
-        }
-        const double R = cp[2 * D * B + lane];
-        hit = segbox64<D>(A, Bp, lo, hi) <= R * R;
-    }
-    uint64_t hm = __ballot(hit);
-    bytes += (2 * D + 1) * B * 8;
-    if constexpr ((MODE & kModeObb) != 0) {
-        // spheres whose body's oriented box misses are dropped
-        bool keep = false;
-        uint64_t sp = 0;
-        if (hm && lane < rm.nbody) {
-            sp = rm.body_sph[lane];
-            if (sp & hm) {
-                keep = obb_box_meet64<D>(rm.obb64 + (e * rm.nbody + lane) * obb_words(D), lo, hi);
-                bytes += obb_words(D) * 8;
-            }
-        }
-        uint64_t allowed = keep ? sp : 0ull;
-        for (int o = 32; o > 0; o >>= 1) allowed |= __shfl_xor(allowed, o);
-        hm &= allowed;
-    }
-    if (!hm) return;
-    bool S;
-    if constexpr ((MODE & kModeSplines) != 0) {
-        S = splines_meet64<D>(rm, e, hm, lo, hi, &bytes);
-    } else {
-        const CopyMap cm = copy_map((int)(P / B));
-        S = copies_meet64<D>(rm, rm.samp64 + copy_stride<D>() * s0, P, cm, hm, lo, hi, rad, lst, &bytes);
-    }
-    ++n_outer;
-    if (lane == 0) add_counts(rm, e, en.sign, S ? en.sign : 0);
-}
-
 // ------------------------------------------------------------------------
 // k_item: one block per work item (grid cell c, a chunk of at most 256 of
 // its edges; the chunk size is the roadmap's work-item size).
@@ -732,9 +658,8 @@ __device__ inline void retest_one(const RmDev &rm, int64_t e, int ci, int *lst, 
 //      spatial ones.
 //   5. per pair C and S; the edge's counter deltas are summed in LDS and
 //      added once per edge.  In FP32 a pair whose decision fell inside the
-//      rounding band goes to the block's re-test region, decided in binary64
-//      by k_fp64 (one wavefront per pair); when the region is full the
-//      whole item is left to k_fp64's second part, which runs it in binary64.
+//      rounding band is queued and decided in binary64 by the same block
+//      (retest_queued), after the item's rounds or when the queue fills.
 // ------------------------------------------------------------------------
 
 constexpr int kSubTile = 128;             // changed entries staged per tile
@@ -742,9 +667,10 @@ constexpr int kSlots = 2;                 // edge slots per thread
 constexpr int kItemCap = kSlots * kBlock; // edges per work item at most
 constexpr int kWords = kSubTile / 32;     // overlap words per edge
 constexpr int kPairCap = kBlock;          // pairs per round (one per thread)
-static_assert(rt_cap_of(1) == kPairCap, "a share's re-test region holds a round");
 constexpr int kRowCap = 256;              // (pair, sphere) rows per copy round
 constexpr int kOpenCap = 1024;            // capsule tests queued for the exact part
+constexpr int kRetestCap = kPairCap + kRcCap;  // pairs queued for the binary64 re-test: what
+                                          // may be waiting before a round, and the round
 static_assert(kWords == 4, "a slab mask holds one uint4 of entry bits");
 static_assert(kSubTile <= 65536 && kItemCap <= 65536, "a pair is (edge slot << 16) | entry in 32 bits");
 static_assert(kLocalCells * 4 == kWords * kItemCap, "the overlap words reuse the slab masks' storage");
@@ -752,7 +678,7 @@ static_assert(2 * 3 * slabs_of(3) <= kLocalCells && 2 * 2 * slabs_of(2) <= kLoca
                   slabs_of(3) <= 128,
               "the slab masks fit their storage and one wavefront's scan (two slabs a lane)");
 static_assert(kOpenCap >= 3 * kRowCap + 1, "the rows fit the capsule queue's storage");
-static_assert(kOpenCap * 4 >= kPairCap * 8 + kBlock * 4 + 64 * 8, "the overflow re-test fits the queue's storage");
+static_assert(kOpenCap * 4 >= kWaves * 64 * 4 + 64 * 8, "the re-test's scratch fits the queue's storage");
 
 __device__ inline int pe_slot(uint32_t v) { return (int)(v >> 16); }
 __device__ inline int pe_entry(uint32_t v) { return (int)(v & 0xFFFFu); }
@@ -766,6 +692,11 @@ struct Radii32 {
     float r32[64];                        // sphere radii, binary32 (for the band)
 };
 struct NoRadii {};
+struct RetestQueue {
+    int2 pair[kRetestCap];
+    int n;
+};
+struct NoQueue {};
 
 template <typename T>
 struct ItemLds {
@@ -788,8 +719,8 @@ struct ItemLds {
     uint32_t pe[kPairCap];                // edge slot << 16 | staged entry
     unsigned long long hm[kPairCap], um[kPairCap];
     // the capsule-test queue is dead once the exact part has run; the rows
-    // and their copy offsets live after it, in the same storage, and after
-    // the decisions it is the scratch of a binary64 overflow re-test
+    // and their copy offsets live after it, in the same storage, and between
+    // rounds it is the scratch of the binary64 re-test
     union alignas(8) {
         uint32_t open[kOpenCap];          // queued (pair << 6 | sphere) capsule tests
         struct {
@@ -801,8 +732,9 @@ struct ItemLds {
     int nopen;
     uint32_t sf[kPairCap];
     int wsum[kWaves];
-    int rc_n, rc_start, defer;
-    int pl_n, pl_start;                   // pairs this block listed (pair listing)
+    // pairs (edge, changed entry) queued for the binary64 re-test
+    typename std::conditional<std::is_same<T, float>::value, RetestQueue, NoQueue>::type r64;
+    int pl_n;                             // pairs this block listed (pair listing)
     unsigned long long acc[kStats];
 };
 
@@ -887,13 +819,109 @@ __device__ inline int coprime_step(int n)
     return 1;
 }
 
+// Binary64 decisions of the pairs queued in L.r64, by the whole block: C and S
+// by their definition (capsules, the oriented boxes, then copies or spline
+// segments), added to the edges' counters.  A wavefront takes up to 64 / B
+// pairs at a time, the capsules of all of them on its lanes, then the copies
+// pair by pair.  The queue ends empty; L.u serves as scratch.
+// A block re-tests its own pairs (a spatial update queues about one per two
+// blocks) at the end of its item: a chain of two loads and the exact minimum,
+// 4 us at the end of some blocks.  A kernel of its own for all blocks' pairs
+// cost 8 to 11 us of every update: the prefix of the blocks' counts, four
+// dependent loads and a launch.
+template <int D, int MODE, typename Lds>
+__device__ __forceinline__ void retest_queued(const RmDev &rm, Lds &L, const int *s_lane, uint32_t &n_outer)
+{
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
+    const int B = rm.B, Gw = 64 / B;
+    int *lst = reinterpret_cast<int *>(&L.u) + wv * 64;
+    double *rad = reinterpret_cast<double *>(reinterpret_cast<int *>(&L.u) + kWaves * 64);
+    if (tid < B) rad[tid] = rm.rad64[tid];
+    const int n = L.r64.n;
+    __syncthreads();
+    unsigned long long bytes = 0;
+    const uint64_t gm = (B == 64 ? 0ull : 1ull << B) - 1ull;
+    const int per = min(Gw, (n + kWaves - 1) / kWaves);
+    const int slot = s_lane[lane] >> 8, ci = s_lane[lane] & 255;
+    for (int q0 = wv * per; q0 < n; q0 += kWaves * per) {
+        const int m = min(per, n - q0);
+        bool hit = false;
+        if (slot < m) {
+            const int2 pr = L.r64.pair[q0 + slot];
+            const ChgEntry &en = rm.chg[pr.y];
+            const double *cp = rm.cap64 + (int64_t)pr.x * (2 * D + 1) * B;
+            double A[D], Bp[D], lo[D], hi[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                A[d] = cp[d * B + ci];
+                Bp[d] = cp[(D + d) * B + ci];
+                lo[d] = en.lo[d];
+                hi[d] = en.hi[d];
+            }
+            const double R = cp[2 * D * B + ci];
+            hit = segbox64<D>(A, Bp, lo, hi) <= R * R;
+        }
+        const uint64_t hits = __ballot(hit);
+        bytes += (unsigned long long)m * (2 * D + 1) * B * 8;
+        for (int g = 0; g < m; ++g) {
+            uint64_t hm = (hits >> (g * B)) & gm;
+            if (!hm) continue;
+            const int2 pr = L.r64.pair[q0 + g];
+            const int64_t e = pr.x;
+            const ChgEntry &en = rm.chg[pr.y];
+            double lo[D], hi[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                lo[d] = en.lo[d];
+                hi[d] = en.hi[d];
+            }
+            if constexpr ((MODE & kModeObb) != 0) {
+                // spheres whose body's oriented box misses are dropped
+                bool keep = false;
+                uint64_t sp = 0;
+                if (lane < rm.nbody) {
+                    sp = rm.body_sph[lane];
+                    if (sp & hm) {
+                        keep = obb_box_meet64<D>(rm.obb64 + (e * rm.nbody + lane) * obb_words(D), lo, hi);
+                        bytes += lane == 0 ? obb_words(D) * 8 : 0;
+                    }
+                }
+                uint64_t allowed = keep ? sp : 0ull;
+                for (int o = 32; o > 0; o >>= 1) allowed |= __shfl_xor(allowed, o);
+                hm &= allowed;
+                if (!hm) continue;
+            }
+            bool S;
+            if constexpr ((MODE & kModeSplines) != 0) {
+                S = splines_meet64<D>(rm, e, hm, lo, hi, &bytes);
+            } else {
+                const int64_t s0 = rm.p_fixed ? e * rm.p_fixed : rm.soff[e];
+                const int64_t P = rm.p_fixed ? rm.p_fixed : rm.soff[e + 1] - s0;
+                const CopyMap cm = copy_map((int)(P / B));
+                S = copies_meet64<D>(rm, rm.samp64 + copy_stride<D>() * s0, cm, hm, lo, hi, rad, lst, &bytes);
+            }
+            if (lane == 0) {
+                ++n_outer;
+                add_counts(rm, e, en.sign, S ? en.sign : 0);
+            }
+        }
+    }
+    if (lane == 0) atomicAdd(&L.acc[kStatFp64Bytes], bytes);
+    __syncthreads();
+    if (tid == 0) {
+        L.acc[2] += (unsigned long long)n;
+        L.r64.n = 0;
+    }
+    __syncthreads();
+}
+
 // One round of at most kPairCap pairs listed in L.pe (edge slot << 16 |
 // entry): the outer test (capsules, then the oriented boxes), the probe, the
 // inner test (copies or spline segments) and the decisions.  Item blocks
-// (kShare false) sum each edge's counter deltas in L.dC / L.dS and leave
-// their item whole to the binary64 pass when the re-test region is full;
-// pair-share blocks (kShare true: slot and entry are the pair itself) add
-// the deltas to the counters at once and re-test an overflow themselves.
+// (kShare false) sum each edge's counter deltas in L.dC / L.dS, pair-share
+// blocks (kShare true: slot and entry are the pair itself) add the deltas to
+// the counters at once.  Undecided pairs are queued in L.r64, which has room
+// for a round (the caller re-tests them).
 template <int D, typename T, int MODE, bool kShare, typename Lds>
 __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_rad2, const int *s_lane, int np,
                                            uint32_t &n_pairs, uint32_t &n_outer, unsigned long long &bytes)
@@ -1287,16 +1315,13 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
     }
     // ---- decisions
     bool unsure = false;
-    int2 rec = make_int2(0, 0);
     if (p < np) {
         const uint64_t ump = kF32 ? L.um[p] : 0ull;
         if (hmp || ump) {
             const uint32_t fp = L.sf[p];
             const uint32_t pv = L.pe[p], te = pe_slot(pv), s = pe_entry(pv);
             unsure = kF32 && (!hmp || (!(fp & 1u) && ((fp & 2u) || ump)));
-            if (unsure) {
-                rec = make_int2(L.edge[te], L.gidx[s]);
-            } else {
+            if (!unsure) {
                 const int sign = L.sign[s];
                 if constexpr (kShare) {
                     add_counts(rm, L.edge[te], sign, (fp & 1u) ? sign : 0);
@@ -1309,48 +1334,29 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
         }
     }
     if constexpr (kF32) {
-        // undecided pairs go to the block's re-test region for the binary64
-        // pass.  An item block whose region is full leaves its item whole to
-        // that pass; a pair share never fills its own region (it holds at
-        // most rt_cap_of(pl_cap) pairs)
-        int tot_u;
-        const int upre = block_scan(unsure ? 1 : 0, &tot_u, L.wsum);
-        if (tot_u > 0) {
-            const int base = L.rc_n;
-            if constexpr (kShare) {
-                if (unsure) rm.rt[(int64_t)blockIdx.x * rt_cap_of(rm.pl_cap) + base + upre] = rec;
-                __syncthreads();
-                if (tid == 0) L.rc_n = base + tot_u;
-            } else {
-                const bool fits = !L.defer && base + tot_u <= rm.rc_cap;
-                if (fits && unsure) rm.rc[(int64_t)blockIdx.x * rm.rc_cap + base + upre] = rec;
-                __syncthreads();
-                if (tid == 0) {
-                    if (fits) L.rc_n = base + tot_u;
-                    else L.defer = 1;
-                }
+        // undecided pairs are queued for the binary64 re-test
+        const uint64_t ub = __ballot(unsure);
+        if (ub) {
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&L.r64.n, __popcll(ub));
+            base = __shfl(base, 0);
+            if (unsure) {
+                const uint32_t pv = L.pe[p];
+                L.r64.pair[base + __popcll(ub & lanes_below())] = make_int2(L.edge[pe_slot(pv)], L.gidx[pe_entry(pv)]);
             }
         }
     }
     __syncthreads();
 }
 
-// deferred == 0: the main pass: items li0, li0 + lstride, ... (statistics
-// row and re-test region blockIdx.x).
-// deferred == 1: the binary64 pass over the items the FP32 blocks left whole
-// (their list rm.df, ctl->n_df long): entries li0, li0 + lstride, ...
-// (statistics row li0).
+// Items li0, li0 + lstride, ... of the roadmap (statistics row blockIdx.x).
 //
 // kList: the pair listing of the FP32 mode.  Each round of pairs goes to this
 // block's region of the pair list (rm.pl, for the pair-share kernel) while
 // the region has room; a round that does not fit is tested here, as the
 // fused kernel does.
-// kCont: this block may have visited the roadmap before in this launch (the
-// batched kernel's claimed items): its re-test region continues from the
-// count it wrote then, and its statistics are added to its row, which
-// start from zero (both are cleared after they are read).
-template <int D, typename T, int MODE, bool kList = false, bool kCont = false>
-__device__ __forceinline__ void item_body(const RmDev &rm, int deferred, int li0, int lstride)
+template <int D, typename T, int MODE, bool kList = false>
+__device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
 {
     constexpr bool kF32 = std::is_same<T, float>::value;
     static_assert(!kList || kF32, "the pair listing serves the FP32 mode");
@@ -1370,11 +1376,10 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int deferred, int li0
     }
     if (tid == 0) {
         L.nopen = 0;
-        L.rc_n = (kCont && kF32 && !deferred) ? rm.rc_cnt[blockIdx.x] : 0;
+        if constexpr (kF32) L.r64.n = 0;
         L.pl_n = 0;
     }
     const int status = ctl->status;
-    const int n_df = (deferred && status == RGG_OK) ? ctl->n_df : 0;
     __syncthreads();
     // wavefront-uniform counts (kept in scalar registers) and per-lane ones
     uint32_t n_pairs = 0, visited = 0, cand = 0, n_outer = 0;
@@ -1385,328 +1390,321 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int deferred, int li0
     const float4 *aabb = reinterpret_cast<const float4 *>(rm.aabb);
     const int jfix = rm.p_fixed ? rm.p_fixed / B : 0;
     constexpr int kSl = slabs_of(D);   // slabs per axis of the slab masks
-    // next work item of this block; false when there is none
-    int li = li0;
-    auto next_item = [&](int &it) -> bool {
-        if (!deferred) {
-            if (status != RGG_OK || li >= n_items) return false;
-            it = li;
-        } else {
-            if (li >= n_df) return false;
-            it = rm.df[li];
-        }
-        li += lstride;
-        return true;
-    };
-    int it;
-    while (next_item(it)) {
-        // with one cell the items are (0, h) and the cell's list is every
-        // edge in order: the item's edges are beg .. end - 1 themselves
-        const int2 item = single ? make_int2(0, it) : rm.items[it];
-        const int64_t c = item.x;
-        const int32_t cx = (int32_t)(c % rm.gdim[0]);
-        const int32_t cy = (int32_t)((c / rm.gdim[0]) % rm.gdim[1]);
-        const int32_t cz = (int32_t)(c / ((int64_t)rm.gdim[0] * rm.gdim[1]));
-        int64_t beg, end;
-        if (single) {
-            beg = (int64_t)item.y * rm.chunk;
-            end = min(rm.E, beg + rm.chunk);
-        } else {
-            beg = (int64_t)rm.cell_start[c] + (int64_t)item.y * rm.chunk;
-            end = min((int64_t)rm.cell_start[c + 1], beg + rm.chunk);
-        }
-        const int n_e = (int)(end - beg);   // edge slots in use: tid, tid + kBlock
-        int e[kSlots], J[kSlots];
-        float es[kSlots];
-        uint32_t j0[kSlots];
-#pragma unroll
-        for (int h = 0; h < kSlots; ++h) {
-            const int sl = tid + h * kBlock;
-            e[h] = 0;
-            J[h] = 0;
-            es[h] = 0.0f;
-            j0[h] = 0;
-            if (sl < n_e) {
-                if (!single) {
-                    // the cell list's slot: one contiguous load, no gather
-                    const int4 cs = rm.cell_slot[beg + sl];
-                    e[h] = cs.x;
-                    es[h] = __int_as_float(cs.y);
-                    j0[h] = (uint32_t)cs.z;
-                    J[h] = cs.w;
-                } else {
-                    e[h] = (int)(beg + sl);
-                    es[h] = aabb[2 * (int64_t)e[h]].w;
-                    if (jfix) {
-                        J[h] = jfix;
-                        j0[h] = (uint32_t)((int64_t)e[h] * jfix);
+    // where to go on: the item, its tile of changed entries, the tile's round
+    // (not zero only after the re-test queue filled in the middle of an item)
+    int it = li0, tile0 = 0, round0 = 0;
+    bool full = status == RGG_OK;
+    uint32_t had = 0;   // bit h: edge slot h of the item has pairs
+    while (full) {
+        full = false;
+        for (; it < n_items && !full; it += full ? 0 : lstride) {
+            const bool anew = tile0 == 0 && round0 == 0;
+            // with one cell the items are (0, h) and the cell's list is every
+            // edge in order: the item's edges are beg .. end - 1 themselves
+            const int2 item = single ? make_int2(0, it) : rm.items[it];
+            const int64_t c = item.x;
+            const int32_t cx = (int32_t)(c % rm.gdim[0]);
+            const int32_t cy = (int32_t)((c / rm.gdim[0]) % rm.gdim[1]);
+            const int32_t cz = (int32_t)(c / ((int64_t)rm.gdim[0] * rm.gdim[1]));
+            int64_t beg, end;
+            if (single) {
+                beg = (int64_t)item.y * rm.chunk;
+                end = min(rm.E, beg + rm.chunk);
+            } else {
+                beg = (int64_t)rm.cell_start[c] + (int64_t)item.y * rm.chunk;
+                end = min((int64_t)rm.cell_start[c + 1], beg + rm.chunk);
+            }
+            const int n_e = (int)(end - beg);   // edge slots in use: tid, tid + kBlock
+            int e[kSlots], J[kSlots];
+            float es[kSlots];
+            uint32_t j0[kSlots];
+    #pragma unroll
+            for (int h = 0; h < kSlots; ++h) {
+                const int sl = tid + h * kBlock;
+                e[h] = 0;
+                J[h] = 0;
+                es[h] = 0.0f;
+                j0[h] = 0;
+                if (sl < n_e) {
+                    if (!single) {
+                        // the cell list's slot: one contiguous load, no gather
+                        const int4 cs = rm.cell_slot[beg + sl];
+                        e[h] = cs.x;
+                        es[h] = __int_as_float(cs.y);
+                        j0[h] = (uint32_t)cs.z;
+                        J[h] = cs.w;
                     } else {
-                        const int64_t s0 = rm.soff[e[h]];
-                        j0[h] = (uint32_t)(s0 / B);
-                        J[h] = (int)((rm.soff[e[h] + 1] - s0) / B);
-                    }
-                }
-                bytes += 32;
-            }
-        }
-        // with one cell every entry covers it: the first tile's entries are
-        // requested together with the edges (binary32 boxes, size, sign)
-        const bool pf = kF32 && single;
-        float4 pf_a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), pf_b = pf_a;
-        if (pf && tid < kSubTile && tid < n_chg) {
-            const float4 *q = reinterpret_cast<const float4 *>(&rm.chg[tid]);
-            pf_a = q[0];   // lo32[0..2], hi32[0]
-            pf_b = q[1];   // hi32[1..2], sbox, sign
-        }
-        __syncthreads();   // the previous item is done with the LDS arrays
-#pragma unroll
-        for (int h = 0; h < kSlots; ++h) {
-            const int sl = tid + h * kBlock;
-            L.edge[sl] = e[h];
-            L.es[sl] = es[h];
-            L.cfg0[sl] = j0[h];
-            L.ej[sl] = J[h];
-            L.dC[sl] = 0;
-            L.dS[sl] = 0;
-        }
-        if (wv == 0) visited += (uint32_t)n_e;
-        if (tid == 0) {
-            L.rc_start = L.rc_n;
-            L.pl_start = L.pl_n;
-            L.defer = 0;
-            // the main pass visits every item once: clear the cell's mark with
-            // its first chunk, so the next update starts from zero marks
-            if (!deferred && !single && item.y == 0) atomicAnd(&rm.cell_bits[c >> 5], ~(1u << (c & 31)));
-        }
-        uint32_t had = 0;   // bit h: edge slot h has pairs
-        bool fused = !kList;   // some round of this item was tested here
-        int n_round = 0;       // this item's pair rounds so far
-        for (int j0 = 0; j0 < n_chg; j0 += kSubTile) {
-            // the slab masks start empty (the previous tile or item is done
-            // with their storage); the staging scan's barriers order this
-            // before they are filled
-            for (int q = tid; q < 2 * D * kSl; q += kBlock) L.g.sm[q] = make_uint4(0u, 0u, 0u, 0u);
-            // stage the entries covering this cell
-            const int j = j0 + tid;
-            const bool first = pf && j0 == 0;
-            bool in = false;
-            if (tid < kSubTile && j < n_chg) {
-                if (first) {
-                    in = true;
-                } else {
-                    const ChgEntry &en = rm.chg[j];
-                    in = single || (cx >= en.c0[0] && cx <= en.c1[0] && cy >= en.c0[1] && cy <= en.c1[1] &&
-                                    cz >= en.c0[2] && cz <= en.c1[2]);
-                }
-            }
-            int nt;
-            const int pos = block_scan(in ? 1 : 0, &nt, L.wsum);
-            if (in) {
-                if (first) {
-                    L.blo[pos] = make_float4(pf_a.x, pf_a.y, pf_a.z, pf_b.z);
-                    L.bhi[pos] = make_float4(pf_a.w, pf_b.x, pf_b.y, 0.0f);
-                    L.sign[pos] = __float_as_int(pf_b.w);
-                } else {
-                    const ChgEntry &en = rm.chg[j];
-                    L.blo[pos] = make_float4(en.lo32[0], en.lo32[1], en.lo32[2], en.sbox);
-                    L.bhi[pos] = make_float4(en.hi32[0], en.hi32[1], en.hi32[2], 0.0f);
-                    if constexpr (!kF32) {
-                        for (int k = 0; k < 3; ++k) {
-                            L.x.lo[k][pos] = en.lo[k];
-                            L.x.hi[k][pos] = en.hi[k];
+                        e[h] = (int)(beg + sl);
+                        es[h] = aabb[2 * (int64_t)e[h]].w;
+                        if (jfix) {
+                            J[h] = jfix;
+                            j0[h] = (uint32_t)((int64_t)e[h] * jfix);
+                        } else {
+                            const int64_t s0 = rm.soff[e[h]];
+                            j0[h] = (uint32_t)(s0 / B);
+                            J[h] = (int)((rm.soff[e[h] + 1] - s0) / B);
                         }
                     }
-                    L.sign[pos] = en.sign;
-                }
-                L.gidx[pos] = j;
-            }
-            if (nt == 0) continue;   // uniform: nt is the block total
-            const int nw = (nt + 31) >> 5;
-            __syncthreads();
-            // block-local slab masks: each staged entry marks the slab its
-            // range starts in and the slab it ends in, on every axis ...
-            if (tid < nt) {
-                const float4 l = L.blo[tid], h = L.bhi[tid];
-                const float lo3[3] = {l.x, l.y, l.z}, hi3[3] = {h.x, h.y, h.z};
-                const uint32_t bit = 1u << (tid & 31);
-                const int wd = tid >> 5;
-                uint32_t *mw = reinterpret_cast<uint32_t *>(L.g.sm);
-#pragma unroll
-                for (int d = 0; d < D; ++d) {
-                    atomicOr(&mw[((2 * d) * kSl + slab_of(rm, d, lo3[d], kSl)) * 4 + wd], bit);
-                    atomicOr(&mw[((2 * d + 1) * kSl + slab_of(rm, d, hi3[d], kSl)) * 4 + wd], bit);
+                    bytes += anew ? 32 : 0;
                 }
             }
-            __syncthreads();
-            // ... then each axis's start marks become "starts at or before s"
-            // (an OR over slabs 0..s) and its end marks "ends at or after s"
-            // (an OR over s..n-1): one wavefront per (axis, mark), each lane
-            // two slabs, the lanes joined by a wavefront scan
-            for (int a = wv; a < 2 * D; a += kWaves) {
-                const bool up = (a & 1) == 0;   // start marks: forward
-                uint4 *arr = L.g.sm + a * kSl;
-                const int s0 = 2 * lane, s1 = 2 * lane + 1;
-                auto at = [&](int s) -> uint4 & { return arr[up ? s : kSl - 1 - s]; };
-                uint4 v0 = s0 < kSl ? at(s0) : make_uint4(0u, 0u, 0u, 0u);
-                uint4 v1 = s1 < kSl ? at(s1) : make_uint4(0u, 0u, 0u, 0u);
-                v1 = make_uint4(v1.x | v0.x, v1.y | v0.y, v1.z | v0.z, v1.w | v0.w);
-                uint4 ex = v1;   // inclusive OR over lanes 0..lane, then shifted
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const uint32_t x = __shfl_up(ex.x, o), y = __shfl_up(ex.y, o), z = __shfl_up(ex.z, o),
-                                   w = __shfl_up(ex.w, o);
-                    if (lane >= o) ex = make_uint4(ex.x | x, ex.y | y, ex.z | z, ex.w | w);
-                }
-                uint4 pre = make_uint4(__shfl_up(ex.x, 1), __shfl_up(ex.y, 1), __shfl_up(ex.z, 1),
-                                       __shfl_up(ex.w, 1));
-                if (lane == 0) pre = make_uint4(0u, 0u, 0u, 0u);
-                if (s0 < kSl) at(s0) = make_uint4(pre.x | v0.x, pre.y | v0.y, pre.z | v0.z, pre.w | v0.w);
-                if (s1 < kSl) at(s1) = make_uint4(pre.x | v1.x, pre.y | v1.y, pre.z | v1.z, pre.w | v1.w);
+            // with one cell every entry covers it: the first tile's entries are
+            // requested together with the edges (binary32 boxes, size, sign)
+            const bool pf = kF32 && single;
+            float4 pf_a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), pf_b = pf_a;
+            if (pf && tid < kSubTile && tid < n_chg) {
+                const float4 *q = reinterpret_cast<const float4 *>(&rm.chg[tid]);
+                pf_a = q[0];   // lo32[0..2], hi32[0]
+                pf_b = q[1];   // hi32[1..2], sbox, sign
             }
-            __syncthreads();
-            // the staged entries each of this thread's edges meets, 32 per
-            // word: the candidates whose slab range meets the edge's on
-            // every axis (all reads of the slab masks first: their storage
-            // then takes the words), then the exact test against the edge's
-            // box
-            float4 bl[kSlots], bh[kSlots];
-            uint32_t cw[kSlots][kWords];
-            // both slots' boxes are requested before either is used
-#pragma unroll
+            __syncthreads();   // the previous item is done with the LDS arrays
+    #pragma unroll
             for (int h = 0; h < kSlots; ++h) {
                 const int sl = tid + h * kBlock;
-                bl[h] = make_float4(0, 0, 0, 0);
-                bh[h] = bl[h];
-                if (sl < n_e) {
-                    bl[h] = aabb[2 * (int64_t)L.edge[sl]];
-                    bh[h] = aabb[2 * (int64_t)L.edge[sl] + 1];
-                }
+                L.edge[sl] = e[h];
+                L.es[sl] = es[h];
+                L.cfg0[sl] = j0[h];
+                L.ej[sl] = J[h];
+                L.dC[sl] = 0;
+                L.dS[sl] = 0;
             }
-#pragma unroll
-            for (int h = 0; h < kSlots; ++h) {
-                const int sl = tid + h * kBlock;
-#pragma unroll
-                for (int w = 0; w < kWords; ++w) cw[h][w] = 0u;
-                if (sl < n_e) {
-                    const float lo3[3] = {bl[h].x, bl[h].y, bl[h].z}, hi3[3] = {bh[h].x, bh[h].y, bh[h].z};
-                    uint4 m = make_uint4(~0u, ~0u, ~0u, ~0u);
-#pragma unroll
+            if (wv == 0 && anew) visited += (uint32_t)n_e;
+            if (tid == 0) {
+                // every item is visited once: clear the cell's mark with its
+                // first chunk, so the next update starts from zero marks
+                if (!single && item.y == 0) atomicAnd(&rm.cell_bits[c >> 5], ~(1u << (c & 31)));
+            }
+            if (anew) had = 0;
+            bool fused = !kList;   // some round of this item was tested here
+            int n_round = 0;       // this item's pair rounds so far
+            for (int j0 = tile0; j0 < n_chg && !full; j0 += kSubTile) {
+                // the slab masks start empty (the previous tile or item is done
+                // with their storage); the staging scan's barriers order this
+                // before they are filled
+                for (int q = tid; q < 2 * D * kSl; q += kBlock) L.g.sm[q] = make_uint4(0u, 0u, 0u, 0u);
+                // stage the entries covering this cell
+                const int j = j0 + tid;
+                const bool first = pf && j0 == 0;
+                bool in = false;
+                if (tid < kSubTile && j < n_chg) {
+                    if (first) {
+                        in = true;
+                    } else {
+                        const ChgEntry &en = rm.chg[j];
+                        in = single || (cx >= en.c0[0] && cx <= en.c1[0] && cy >= en.c0[1] && cy <= en.c1[1] &&
+                                        cz >= en.c0[2] && cz <= en.c1[2]);
+                    }
+                }
+                int nt;
+                const int pos = block_scan(in ? 1 : 0, &nt, L.wsum);
+                if (in) {
+                    if (first) {
+                        L.blo[pos] = make_float4(pf_a.x, pf_a.y, pf_a.z, pf_b.z);
+                        L.bhi[pos] = make_float4(pf_a.w, pf_b.x, pf_b.y, 0.0f);
+                        L.sign[pos] = __float_as_int(pf_b.w);
+                    } else {
+                        const ChgEntry &en = rm.chg[j];
+                        L.blo[pos] = make_float4(en.lo32[0], en.lo32[1], en.lo32[2], en.sbox);
+                        L.bhi[pos] = make_float4(en.hi32[0], en.hi32[1], en.hi32[2], 0.0f);
+                        if constexpr (!kF32) {
+                            for (int k = 0; k < 3; ++k) {
+                                L.x.lo[k][pos] = en.lo[k];
+                                L.x.hi[k][pos] = en.hi[k];
+                            }
+                        }
+                        L.sign[pos] = en.sign;
+                    }
+                    L.gidx[pos] = j;
+                }
+                if (nt == 0) continue;   // uniform: nt is the block total
+                const int nw = (nt + 31) >> 5;
+                __syncthreads();
+                // block-local slab masks: each staged entry marks the slab its
+                // range starts in and the slab it ends in, on every axis ...
+                if (tid < nt) {
+                    const float4 l = L.blo[tid], h = L.bhi[tid];
+                    const float lo3[3] = {l.x, l.y, l.z}, hi3[3] = {h.x, h.y, h.z};
+                    const uint32_t bit = 1u << (tid & 31);
+                    const int wd = tid >> 5;
+                    uint32_t *mw = reinterpret_cast<uint32_t *>(L.g.sm);
+    #pragma unroll
                     for (int d = 0; d < D; ++d) {
-                        // entries starting at or before the edge's last slab
-                        // and ending at or after its first
-                        const uint4 st = L.g.sm[(2 * d) * kSl + slab_of(rm, d, hi3[d], kSl)];
-                        const uint4 en = L.g.sm[(2 * d + 1) * kSl + slab_of(rm, d, lo3[d], kSl)];
-                        m = make_uint4(m.x & st.x & en.x, m.y & st.y & en.y, m.z & st.z & en.z, m.w & st.w & en.w);
+                        atomicOr(&mw[((2 * d) * kSl + slab_of(rm, d, lo3[d], kSl)) * 4 + wd], bit);
+                        atomicOr(&mw[((2 * d + 1) * kSl + slab_of(rm, d, hi3[d], kSl)) * 4 + wd], bit);
                     }
-                    cw[h][0] = m.x;
-                    cw[h][1] = m.y;
-                    cw[h][2] = m.z;
-                    cw[h][3] = m.w;
                 }
-            }
-            __syncthreads();
-            int cnt = 0;
-#pragma unroll
-            for (int h = 0; h < kSlots; ++h) {
-                const int sl = tid + h * kBlock;
-                if (sl >= n_e) continue;
-                int ch = 0;
-#pragma unroll
-                for (int w = 0; w < kWords; ++w) {
-                    if (w < nw) {
-                        const int left = nt - 32 * w;   // staged entries from this word on
-                        uint32_t m = cw[h][w] & (left >= 32 ? ~0u : ((1u << left) - 1u)), bits = 0;
-                        while (m) {
-                            const int b = __ffs(m) - 1;
-                            m &= m - 1;
-                            const float4 l = L.blo[w * 32 + b], hb = L.bhi[w * 32 + b];
-                            bool hit = (l.x <= bh[h].x) & (hb.x >= bl[h].x) & (l.y <= bh[h].y) & (hb.y >= bl[h].y) &
-                                       (l.z <= bh[h].z) & (hb.z >= bl[h].z);
-                            if (hit && !single) {
-                                const float lo3[3] = {l.x, l.y, l.z};
-                                hit = pair_owned<D, float>(rm, bl[h], lo3, c);
-                            }
-                            bits |= (uint32_t)hit << b;
+                __syncthreads();
+                // ... then each axis's start marks become "starts at or before s"
+                // (an OR over slabs 0..s) and its end marks "ends at or after s"
+                // (an OR over s..n-1): one wavefront per (axis, mark), each lane
+                // two slabs, the lanes joined by a wavefront scan
+                for (int a = wv; a < 2 * D; a += kWaves) {
+                    const bool up = (a & 1) == 0;   // start marks: forward
+                    uint4 *arr = L.g.sm + a * kSl;
+                    const int s0 = 2 * lane, s1 = 2 * lane + 1;
+                    auto at = [&](int s) -> uint4 & { return arr[up ? s : kSl - 1 - s]; };
+                    uint4 v0 = s0 < kSl ? at(s0) : make_uint4(0u, 0u, 0u, 0u);
+                    uint4 v1 = s1 < kSl ? at(s1) : make_uint4(0u, 0u, 0u, 0u);
+                    v1 = make_uint4(v1.x | v0.x, v1.y | v0.y, v1.z | v0.z, v1.w | v0.w);
+                    uint4 ex = v1;   // inclusive OR over lanes 0..lane, then shifted
+    #pragma unroll
+                    for (int o = 1; o < 64; o <<= 1) {
+                        const uint32_t x = __shfl_up(ex.x, o), y = __shfl_up(ex.y, o), z = __shfl_up(ex.z, o),
+                                       w = __shfl_up(ex.w, o);
+                        if (lane >= o) ex = make_uint4(ex.x | x, ex.y | y, ex.z | z, ex.w | w);
+                    }
+                    uint4 pre = make_uint4(__shfl_up(ex.x, 1), __shfl_up(ex.y, 1), __shfl_up(ex.z, 1),
+                                           __shfl_up(ex.w, 1));
+                    if (lane == 0) pre = make_uint4(0u, 0u, 0u, 0u);
+                    if (s0 < kSl) at(s0) = make_uint4(pre.x | v0.x, pre.y | v0.y, pre.z | v0.z, pre.w | v0.w);
+                    if (s1 < kSl) at(s1) = make_uint4(pre.x | v1.x, pre.y | v1.y, pre.z | v1.z, pre.w | v1.w);
+                }
+                __syncthreads();
+                // the staged entries each of this thread's edges meets, 32 per
+                // word: the candidates whose slab range meets the edge's on
+                // every axis (all reads of the slab masks first: their storage
+                // then takes the words), then the exact test against the edge's
+                // box
+                float4 bl[kSlots], bh[kSlots];
+                uint32_t cw[kSlots][kWords];
+                // both slots' boxes are requested before either is used
+    #pragma unroll
+                for (int h = 0; h < kSlots; ++h) {
+                    const int sl = tid + h * kBlock;
+                    bl[h] = make_float4(0, 0, 0, 0);
+                    bh[h] = bl[h];
+                    if (sl < n_e) {
+                        bl[h] = aabb[2 * (int64_t)L.edge[sl]];
+                        bh[h] = aabb[2 * (int64_t)L.edge[sl] + 1];
+                    }
+                }
+    #pragma unroll
+                for (int h = 0; h < kSlots; ++h) {
+                    const int sl = tid + h * kBlock;
+    #pragma unroll
+                    for (int w = 0; w < kWords; ++w) cw[h][w] = 0u;
+                    if (sl < n_e) {
+                        const float lo3[3] = {bl[h].x, bl[h].y, bl[h].z}, hi3[3] = {bh[h].x, bh[h].y, bh[h].z};
+                        uint4 m = make_uint4(~0u, ~0u, ~0u, ~0u);
+    #pragma unroll
+                        for (int d = 0; d < D; ++d) {
+                            // entries starting at or before the edge's last slab
+                            // and ending at or after its first
+                            const uint4 st = L.g.sm[(2 * d) * kSl + slab_of(rm, d, hi3[d], kSl)];
+                            const uint4 en = L.g.sm[(2 * d + 1) * kSl + slab_of(rm, d, lo3[d], kSl)];
+                            m = make_uint4(m.x & st.x & en.x, m.y & st.y & en.y, m.z & st.z & en.z, m.w & st.w & en.w);
                         }
-                        L.g.om[w][sl] = bits;
-                        ch += __popc(bits);
+                        cw[h][0] = m.x;
+                        cw[h][1] = m.y;
+                        cw[h][2] = m.z;
+                        cw[h][3] = m.w;
                     }
                 }
-                cnt += ch;
-                if (ch) had |= 1u << h;
-            }
-            int tp;
-            const int pre = block_scan(cnt, &tp, L.wsum);
-            for (int r0 = 0; r0 < tp; r0 += kPairCap) {
-                const int np = min(kPairCap, tp - r0);
-                if (cnt > 0 && pre < r0 + np && pre + cnt > r0) {
-                    int k = pre;
-                    for (int h = 0; h < kSlots && k < r0 + np; ++h) {
-                        const int sl = tid + h * kBlock;
-                        if (sl >= n_e) break;
-                        for (int w = 0; w < nw && k < r0 + np; ++w) {
-                            uint32_t m = L.g.om[w][sl];
-                            while (m && k < r0 + np) {
-                                const int s = (w << 5) + __ffs(m) - 1;
+                __syncthreads();
+                int cnt = 0;
+    #pragma unroll
+                for (int h = 0; h < kSlots; ++h) {
+                    const int sl = tid + h * kBlock;
+                    if (sl >= n_e) continue;
+                    int ch = 0;
+    #pragma unroll
+                    for (int w = 0; w < kWords; ++w) {
+                        if (w < nw) {
+                            const int left = nt - 32 * w;   // staged entries from this word on
+                            uint32_t m = cw[h][w] & (left >= 32 ? ~0u : ((1u << left) - 1u)), bits = 0;
+                            while (m) {
+                                const int b = __ffs(m) - 1;
                                 m &= m - 1;
-                                if (k >= r0) L.pe[k - r0] = ((uint32_t)sl << 16) | (uint32_t)s;
-                                ++k;
+                                const float4 l = L.blo[w * 32 + b], hb = L.bhi[w * 32 + b];
+                                bool hit = (l.x <= bh[h].x) & (hb.x >= bl[h].x) & (l.y <= bh[h].y) & (hb.y >= bl[h].y) &
+                                           (l.z <= bh[h].z) & (hb.z >= bl[h].z);
+                                if (hit && !single) {
+                                    const float lo3[3] = {l.x, l.y, l.z};
+                                    hit = pair_owned<D, float>(rm, bl[h], lo3, c);
+                                }
+                                bits |= (uint32_t)hit << b;
+                            }
+                            L.g.om[w][sl] = bits;
+                            ch += __popc(bits);
+                        }
+                    }
+                    cnt += ch;
+                    if (ch) had |= 1u << h;
+                }
+                int tp;
+                const int pre = block_scan(cnt, &tp, L.wsum);
+                for (int r0 = j0 == tile0 ? round0 : 0; r0 < tp && !full; r0 += kPairCap) {
+                    const int np = min(kPairCap, tp - r0);
+                    if (cnt > 0 && pre < r0 + np && pre + cnt > r0) {
+                        int k = pre;
+                        for (int h = 0; h < kSlots && k < r0 + np; ++h) {
+                            const int sl = tid + h * kBlock;
+                            if (sl >= n_e) break;
+                            for (int w = 0; w < nw && k < r0 + np; ++w) {
+                                uint32_t m = L.g.om[w][sl];
+                                while (m && k < r0 + np) {
+                                    const int s = (w << 5) + __ffs(m) - 1;
+                                    m &= m - 1;
+                                    if (k >= r0) L.pe[k - r0] = ((uint32_t)sl << 16) | (uint32_t)s;
+                                    ++k;
+                                }
                             }
                         }
                     }
-                }
-                if constexpr (kList) {
-                    // after the item's first inline_rounds rounds, a round
-                    // goes to the pair list when the region has room
-                    if (n_round++ >= rm.inline_rounds) {
-                        __syncthreads();   // the round's pairs are in L.pe
-                        const int base = L.pl_n;
-                        if (base + np <= rm.pl_cap) {
-                            if (tid < np) {
-                                const uint32_t v = L.pe[tid];
-                                rm.pl[(int64_t)blockIdx.x * rm.pl_cap + base + tid] =
-                                    make_int2(L.edge[pe_slot(v)], L.gidx[pe_entry(v)]);
+                    bool test = true;
+                    if constexpr (kList) {
+                        // after the item's first inline_rounds rounds, a round
+                        // goes to the pair list when the region has room
+                        if (n_round++ >= rm.inline_rounds) {
+                            __syncthreads();   // the round's pairs are in L.pe
+                            const int base = L.pl_n;
+                            if (base + np <= rm.pl_cap) {
+                                if (tid < np) {
+                                    const uint32_t v = L.pe[tid];
+                                    rm.pl[(int64_t)blockIdx.x * rm.pl_cap + base + tid] =
+                                        make_int2(L.edge[pe_slot(v)], L.gidx[pe_entry(v)]);
+                                }
+                                bytes += tid < np ? 8 : 0;
+                                __syncthreads();
+                                if (tid == 0) L.pl_n = base + np;
+                                __syncthreads();
+                                test = false;
                             }
-                            bytes += tid < np ? 8 : 0;
-                            __syncthreads();
-                            if (tid == 0) L.pl_n = base + np;
-                            __syncthreads();
-                            continue;
+                        }
+                        fused = fused || test;
+                    }
+                    if (test) test_round<D, T, MODE, false>(rm, L, s_rad2, s_lane, np, n_pairs, n_outer, bytes);
+                    if constexpr (kF32) {
+                        // no room for another round: re-test, then go on from here
+                        if (L.r64.n >= rm.rc_cap) {
+                            full = true;
+                            tile0 = j0;
+                            round0 = r0 + kPairCap;
                         }
                     }
-                    fused = true;
                 }
-                test_round<D, T, MODE, false>(rm, L, s_rad2, s_lane, np, n_pairs, n_outer, bytes);
             }
-        }
-        cand += (uint32_t)(__popcll(__ballot(had & 1u)) + __popcll(__ballot(had & 2u)));
-        if (fused) bytes += (unsigned long long)__popc(had) * ((2 * D + 1) * B * sizeof(T) + 16);
-        __syncthreads();
-        if (!L.defer) {
-#pragma unroll
+            if (!full) tile0 = round0 = 0;
+            if (!full) cand += (uint32_t)(__popcll(__ballot(had & 1u)) + __popcll(__ballot(had & 2u)));
+            if (fused && !full) bytes += (unsigned long long)__popc(had) * ((2 * D + 1) * B * sizeof(T) + 16);
+            __syncthreads();
+    #pragma unroll
             for (int h = 0; h < kSlots; ++h) {
                 const int sl = tid + h * kBlock;
                 if (sl < n_e) add_counts(rm, L.edge[sl], L.dC[sl], L.dS[sl]);
             }
-        } else if (tid == 0) {
-            // the whole item goes to the binary64 pass: its queued re-tests
-            // and listed pairs are withdrawn (the withdrawn pairs are
-            // counted here, as the rounds this block tested are)
-            L.acc[0] += (unsigned long long)(L.pl_n - L.pl_start);
-            L.rc_n = L.rc_start;
-            L.pl_n = L.pl_start;
-            // each item is left whole at most once per update, so the
-            // list (items_cap long) has room
-            rm.df[atomicAdd(&rm.ctl->n_df, 1)] = it;
+        }
+        if constexpr (kF32) {
+            __syncthreads();
+            if (L.r64.n) retest_queued<D, MODE>(rm, L, s_lane, n_outer);
         }
     }
     __syncthreads();
-    // the binary64 pass counts its pairs as re-tested
     // per-lane counts are summed over the wavefront first: LDS atomics on
     // one address from every lane are slow
     const unsigned long long w_outer = wave_sum_u64(n_outer), w_bytes = wave_sum_u64(bytes);
-    if (tid == 0 && n_pairs) atomicAdd(&L.acc[deferred ? 2 : 0], (unsigned long long)n_pairs);
-    const int byte_row = deferred ? kStatFp64Bytes : (kList ? kStatItemBytes : kStatPairBytes);
+    if (tid == 0 && n_pairs) atomicAdd(&L.acc[0], (unsigned long long)n_pairs);
+    const int byte_row = kList ? kStatItemBytes : kStatPairBytes;
     if (lane == 0) {
         if (w_outer) atomicAdd(&L.acc[1], w_outer);
         if (w_bytes) atomicAdd(&L.acc[byte_row], w_bytes);
@@ -1715,20 +1713,10 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int deferred, int li0
     }
     __syncthreads();
     // statistic k at bs[k * kStatBlocks]: item blocks add to row blockIdx &
-    // (kStatRows - 1), shared with other blocks (atomics); the binary64 pass's
-    // block li0 owns row li0
-    unsigned long long *bs = rm.blk_stats + (deferred ? li0 : (int)(blockIdx.x & (kStatRows - 1)));
-    if (!deferred) {
-        if (tid < kStats && L.acc[tid]) atomicAdd(&bs[tid * kStatBlocks], L.acc[tid]);
-        if (kF32 && tid == 0) {
-            rm.rc_cnt[blockIdx.x] = L.rc_n;
-            if (kList) rm.pl_cnt[blockIdx.x] = L.pl_n;
-        }
-    } else if (tid == 0 && (L.acc[1] | L.acc[2] | L.acc[kStatFp64Bytes])) {
-        bs[1 * kStatBlocks] += L.acc[1];
-        bs[2 * kStatBlocks] += L.acc[2];
-        bs[kStatFp64Bytes * kStatBlocks] += L.acc[kStatFp64Bytes];
-    }
+    // (kStatRows - 1), shared with other blocks (atomics)
+    unsigned long long *bs = rm.blk_stats + (int)(blockIdx.x & (kStatRows - 1));
+    if (tid < kStats && L.acc[tid]) atomicAdd(&bs[tid * kStatBlocks], L.acc[tid]);
+    if (kList && tid == 0) rm.pl_cnt[blockIdx.x] = L.pl_n;
 }
 
 // The binary32 kernel is held to 128 VGPRs (four waves per SIMD, four
@@ -1736,172 +1724,13 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int deferred, int li0
 template <int D, int MODE>
 __global__ void __launch_bounds__(kBlock, 4) k_item32(RmDev rm)
 {
-    item_body<D, float, MODE, true>(rm, 0, (int)blockIdx.x, (int)gridDim.x);
+    item_body<D, float, MODE, true>(rm, (int)blockIdx.x, (int)gridDim.x);
 }
 
 template <int D, int MODE>
 __global__ void __launch_bounds__(kBlock) k_item64(RmDev rm)
 {
-    item_body<D, double, MODE>(rm, 0, (int)blockIdx.x, (int)gridDim.x);
-}
-
-// Binary64 re-test of the pairs queued by the FP32 blocks whose regions this
-// block takes, one wavefront per pair: the item blocks' re-test regions b,
-// b + G, ... (at most 64 of them), then the pair shares' regions of the same
-// blocks; statistics row b.
-template <int D, int MODE>
-__device__ __forceinline__ void retest_pairs(const RmDev &rm, int b, int G)
-{
-    const int kReg = kStatBlocks / G;
-    __shared__ int s_lst[kWaves][64];
-    __shared__ double s_rad[64];
-    __shared__ int s_off[65];
-    __shared__ unsigned long long s_acc[3];
-    const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
-    const bool ok = rm.ctl->status == RGG_OK;
-    if (tid < rm.B) s_rad[tid] = rm.rad64[tid];
-    if (tid < 3) s_acc[tid] = 0;
-    unsigned long long n_re = 0, bytes = 0;
-    uint32_t n_outer = 0;
-    // regions [kReg] at reg[(b + k G) * cap], counts cnt[b + k G]
-    auto run = [&](int32_t *cnt, const int2 *reg_base, int32_t cap) {
-        __syncthreads();   // s_off is free
-        // pair counts of this block's regions, as an exclusive prefix
-        if (tid < 64) {
-            int n = 0;
-            if (tid < kReg) {
-                int *rc = cnt + b + tid * G;
-                const int v = *rc;   // loaded whatever the status, so both loads are in flight at once
-                n = ok ? v : 0;
-                *rc = 0;   // cleared for the next update
-            }
-            int tot;
-            const int pre = wave_prefix(n, &tot);
-            if (tid < kReg) s_off[tid] = pre;
-            if (tid == 0) s_off[kReg] = tot;
-        }
-        __syncthreads();
-        const int total = s_off[kReg];
-        int reg = 0;
-        for (int q = wv; q < total; q += kWaves) {
-            while (s_off[reg + 1] <= q) ++reg;
-            const int k = q - s_off[reg];
-            const int2 pr = reg_base[(int64_t)(b + reg * G) * cap + k];
-            retest_one<D, MODE>(rm, pr.x, pr.y, s_lst[wv], s_rad, n_outer, bytes);
-            ++n_re;
-        }
-    };
-    run(rm.rc_cnt, rm.rc, rm.rc_cap);
-    if (rm.rt) run(rm.rt_cnt, rm.rt, rt_cap_of(rm.pl_cap));
-    if (lane == 0 && n_re) {
-        atomicAdd(&s_acc[0], n_re);
-        atomicAdd(&s_acc[1], (unsigned long long)n_outer);
-        atomicAdd(&s_acc[2], bytes);
-    }
-    __syncthreads();
-    if (tid == 0 && s_acc[0]) {
-        unsigned long long *bs = rm.blk_stats + b;
-        bs[1 * kStatBlocks] += s_acc[1];
-        bs[2 * kStatBlocks] += s_acc[0];
-        bs[kStatFp64Bytes * kStatBlocks] += s_acc[2];
-    }
-}
-
-// Binary64 re-test of the queued pairs of one roadmap, spread over the whole
-// grid: every block sums the pair counts of all re-test regions (the item
-// blocks' regions r, then the pair shares' as regions kStatBlocks + r) into
-// one prefix in LDS, and wavefront w of W takes pairs w, w + W, ... of the
-// regions' concatenation.  The pairs of a heavy region are thus spread over
-// many wavefronts instead of one block's four.  The counts are not cleared
-// here (another block may still be reading them): every block of the item
-// kernel and of the pair-share kernel writes its own region's count at its
-// end, and the label kernel's statistics block clears them for the batched
-// pass, whose blocks write only the regions of roadmaps they visit.
-template <int D, int MODE>
-__device__ __forceinline__ void retest_spread(const RmDev &rm)
-{
-    constexpr int kReg = 2 * kStatBlocks;   // item regions, then share regions
-    constexpr int kPer = kReg / kBlock;     // consecutive regions per thread
-    __shared__ int s_pre[kReg];
-    __shared__ int s_lst[kWaves][64];
-    __shared__ double s_rad[64];
-    __shared__ int s_w[kWaves];
-    __shared__ unsigned long long s_acc[3];
-    const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
-    const int32_t *rt_cnt = rm.rt ? rm.rt_cnt : nullptr;
-    if (tid < rm.B) s_rad[tid] = rm.rad64[tid];
-    if (tid < 3) s_acc[tid] = 0;
-    // coalesced loads of the counts, issued with the status load rather
-    // than after it, then each thread sums its own kPer
-    int n[kPer];
-#pragma unroll
-    for (int h = 0; h < kPer; ++h) {
-        const int r = h * kBlock + tid;
-        n[h] = r < kStatBlocks ? rm.rc_cnt[r] : (rt_cnt ? rt_cnt[r - kStatBlocks] : 0);
-    }
-    const bool ok = rm.ctl->status == RGG_OK;
-#pragma unroll
-    for (int h = 0; h < kPer; ++h) s_pre[h * kBlock + tid] = ok ? n[h] : 0;
-    __syncthreads();
-    int v[kPer], sum = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        v[j] = s_pre[tid * kPer + j];
-        sum += v[j];
-    }
-    int total;
-    int pre = block_scan(sum, &total, s_w);   // its barriers order the reads above before the writes below
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        s_pre[tid * kPer + j] = pre;
-        pre += v[j];
-    }
-    __syncthreads();
-    unsigned long long n_re = 0, bytes = 0;
-    uint32_t n_outer = 0;
-    const int W = (int)gridDim.x * kWaves;
-    const int32_t rt_cap = rt_cap_of(rm.pl_cap);
-    for (int q = (int)blockIdx.x * kWaves + wv; q < total; q += W) {
-        // the region holding pair q: the last r with s_pre[r] <= q
-        int lo = 0, hi = kReg - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_pre[mid] <= q) lo = mid;
-            else hi = mid - 1;
-        }
-        const int k = q - s_pre[lo];
-        const int2 pr = lo < kStatBlocks ? rm.rc[(int64_t)lo * rm.rc_cap + k]
-                                         : rm.rt[(int64_t)(lo - kStatBlocks) * rt_cap + k];
-        retest_one<D, MODE>(rm, pr.x, pr.y, s_lst[wv], s_rad, n_outer, bytes);
-        ++n_re;
-    }
-    if (lane == 0 && n_re) {
-        atomicAdd(&s_acc[0], n_re);
-        atomicAdd(&s_acc[1], (unsigned long long)n_outer);
-        atomicAdd(&s_acc[2], bytes);
-    }
-    __syncthreads();
-    if (tid == 0 && s_acc[0]) {
-        unsigned long long *bs = rm.blk_stats + blockIdx.x;
-        bs[1 * kStatBlocks] += s_acc[1];
-        bs[2 * kStatBlocks] += s_acc[0];
-        bs[kStatFp64Bytes * kStatBlocks] += s_acc[2];
-    }
-}
-
-// The binary64 pass of the FP32 mode of one roadmap: the queued pairs
-// (spread over the grid), then the items left whole because their blocks'
-// re-test regions were full (rare: skipped unless one was deferred in this
-// update; entries b, b + G, ... of the roadmap's list).  One kernel for both, so the common case
-// costs one launch; it runs one block per CU, so the binary64 item path's
-// registers cost no occupancy.
-template <int D, int MODE>
-__global__ void __launch_bounds__(kBlock) k_fp64(RmDev rm)
-{
-    const int n_df = rm.ctl->n_df;
-    retest_spread<D, MODE>(rm);
-    if (!n_df) return;
-    item_body<D, double, MODE>(rm, 1, (int)blockIdx.x, (int)gridDim.x);
+    item_body<D, double, MODE>(rm, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // ------------------------------------------------------------------------
@@ -1936,7 +1765,7 @@ struct ShareLds {
     int nopen;
     uint32_t sf[kPairCap];
     int wsum[kWaves];
-    int rc_n;
+    RetestQueue r64;
     int pref[kStatBlocks + 1];            // listed pairs before each region
     unsigned long long acc[kStats];
 };
@@ -1957,7 +1786,7 @@ __device__ __forceinline__ void share_body(const RmDev &rm)
     }
     if (tid == 0) {
         L.nopen = 0;
-        L.rc_n = 0;   // pairs queued in this share's re-test region
+        L.r64.n = 0;
     }
     // prefix of the regions' pair counts: kPer consecutive regions per thread
     constexpr int kPer = kStatBlocks / kBlock;
@@ -2026,6 +1855,7 @@ __device__ __forceinline__ void share_body(const RmDev &rm)
         if (tid < np && (tid == 0 || L.edge[tid] != L.edge[tid - 1]))
             bytes += (unsigned long long)((2 * D + 1) * B * sizeof(float) + (jfix ? 0 : 16));
         test_round<D, float, MODE, true>(rm, L, s_rad2, s_lane, np, n_pairs, n_outer, bytes);
+        if (L.r64.n) retest_queued<D, MODE>(rm, L, s_lane, n_outer);
     }
     __syncthreads();
     const unsigned long long w_outer = wave_sum_u64(n_outer), w_bytes = wave_sum_u64(bytes);
@@ -2041,8 +1871,8 @@ __device__ __forceinline__ void share_body(const RmDev &rm)
         if (L.acc[0]) atomicAdd(&bs[0], L.acc[0]);
         if (L.acc[1]) atomicAdd(&bs[1 * kStatBlocks], L.acc[1]);
         if (L.acc[2]) atomicAdd(&bs[2 * kStatBlocks], L.acc[2]);
+        if (L.acc[kStatFp64Bytes]) atomicAdd(&bs[kStatFp64Bytes * kStatBlocks], L.acc[kStatFp64Bytes]);
         if (L.acc[kStatPairBytes]) atomicAdd(&bs[kStatPairBytes * kStatBlocks], L.acc[kStatPairBytes]);
-        rm.rt_cnt[blockIdx.x] = L.rc_n;
     }
 }
 
@@ -2264,15 +2094,6 @@ __device__ __forceinline__ void labels_body(const RmDev &rm, uint8_t *labels, in
     if (tile >= rm.ntiles) {
         // every block has its ticket: the counter starts from zero next time
         if (tid == 0) __hip_atomic_store(&rm.ctl->label_ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // the binary64 pass read the re-test counts without clearing them;
-        // a batched pass needs them zero, as its item blocks write only the
-        // regions of the roadmaps they visit
-        if (rm.mixed) {
-            for (int r = tid; r < kStatBlocks; r += kBlock) {
-                rm.rc_cnt[r] = 0;
-                if (rm.rt) rm.rt_cnt[r] = 0;
-            }
-        }
         fold_stats(rm, res);
         return;
     }
@@ -2395,9 +2216,8 @@ __global__ void __launch_bounds__(kDiffBlock) k_diff_batch(BatchReq *tab, const 
 // kBatchStatic of them, then claims the rest one at a time from a counter
 // (items kBatchStatic * G on), so blocks whose items were light take more
 // and the launch ends near the mean block time rather than the heaviest
-// block's.  A block may then visit a roadmap more than once: its re-test
-// region and statistics row continue across the visits (kCont).  The next
-// claim is issued before the current item runs, so its latency is hidden.
+// block's.  The next claim is issued before the current item runs, so its
+// latency is hidden.
 template <int D, typename T>
 __device__ __forceinline__ void item_batch_body(const BatchReq *tab, const int32_t *grp, int n)
 {
@@ -2435,7 +2255,7 @@ __device__ __forceinline__ void item_batch_body(const BatchReq *tab, const int32
             load_rm(&s_rm, tab[grp[lo]].rm);
             cur = lo;
         }
-        item_body<D, T, 0, false, true>(s_rm, 0, g - s_pref[lo], 1 << 30);
+        item_body<D, T, 0>(s_rm, g - s_pref[lo], 1 << 30);
         if (claims && tid == 0) s_next = nxt;
         __syncthreads();
         g = claims ? s_next : g + G;
@@ -2452,20 +2272,6 @@ template <int D>
 __global__ void __launch_bounds__(kBlock) k_item64_batch(const BatchReq *tab, const int32_t *grp, int n)
 {
     item_batch_body<D, double>(tab, grp, n);
-}
-
-// kFp64BatchGrid blocks per request of the group: its queued pairs, then
-// (if any) its items left whole
-template <int D>
-__global__ void __launch_bounds__(kBlock) k_fp64_batch(const BatchReq *tab, const int32_t *grp)
-{
-    __shared__ RmDev s_rm;
-    const int r = (int)blockIdx.x / kFp64BatchGrid, b = (int)blockIdx.x % kFp64BatchGrid;
-    load_rm(&s_rm, tab[grp[r]].rm);
-    const int n_df = s_rm.ctl->n_df;
-    retest_pairs<D, 0>(s_rm, b, kFp64BatchGrid);
-    if (!n_df) return;
-    item_body<D, double, 0>(s_rm, 1, b, kFp64BatchGrid);
 }
 
 // request owning a tile: the last r with first[r] <= tile (n <= kMaxBatch)
@@ -2566,16 +2372,14 @@ __global__ void __launch_bounds__(kBlock) k_write_batch(const BatchReq *tab, int
 
 namespace {
 
-// The kernel of role k for the roadmap's dimension and form: 0 the pair
-// listing, 1 the pair testing, 2 the binary64 pass (FP32 mode), 3 the
-// binary64 item kernel (FP64 mode).
+// The kernel of role k for the roadmap's dimension and form: 0 the item kernel
+// and 1 the pair testing of the FP32 mode, 2 the item kernel of the FP64 mode.
 template <int D, int MODE>
 void *fn_of(int k)
 {
     switch (k) {
     case 0: return (void *)k_item32<D, MODE>;
     case 1: return (void *)k_pairs<D, MODE>;
-    case 2: return (void *)k_fp64<D, MODE>;
     default: return (void *)k_item64<D, MODE>;
     }
 }
@@ -2602,14 +2406,12 @@ struct Node {
 };
 
 // The kernels of one update, in order.  Stage events: ev[0] before, ev[1]
-// after the diff, ev[2] after the cell activation, ev[3] after the pair
-// listing, ev[4] after the pair testing, ev[5] after the binary64 pass,
-// ev[6] after the labels.  The FP64 mode's one item kernel stands for the
-// testing (ev[3] before it).  With a single grid cell there is nothing to
-// activate: k_diff emits the items.
-// blocks of the item kernel for a one-cell roadmap: one per item, at most
-// kGrid (the rows of statistics and re-test regions past the grid stay zero:
-// their readers clear them after every update)
+// after the diff, ev[2] after the cell activation, ev[3] after the FP32 item
+// kernel, ev[4] after the pair testing, ev[5] after the binary64 re-test (part
+// of the two before it: no time), ev[6] after the labels.  The FP64 mode's one
+// item kernel stands for the testing (ev[3] before it).
+// Blocks of the item kernel for a one-cell roadmap: one per item, at most
+// kGrid.
 unsigned fixed_items_grid(const RmDev &rm)
 {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(kGrid, rm.items_cap));
@@ -2628,12 +2430,11 @@ int plan(const RmDev &rm, Node out[7])
         // start and stop (with pair listing every block writes its list's
         // count, so the whole grid runs)
         const unsigned grid = single && !share ? fixed_items_grid(rm) : kGrid;
-        out[n++] = {fn(rm, 0), dim3(grid), 1, 3, share ? 3 : 4};
-        if (share) out[n++] = {fn(rm, 1), dim3(kGrid), 1, 4, 4};
-        out[n++] = {fn(rm, 2), dim3(kFp64Grid), 1, 5, 5};
+        out[n++] = {fn(rm, 0), dim3(grid), 1, 3, share ? 3 : 5};
+        if (share) out[n++] = {fn(rm, 1), dim3(kGrid), 1, 4, 5};
     } else {
         out[n++] = {diff_fn, dim3(1), 0, 1, 3};
-        out[n++] = {fn(rm, 3), dim3(single ? fixed_items_grid(rm) : kGrid), 1, 4, 5};
+        out[n++] = {fn(rm, 2), dim3(single ? fixed_items_grid(rm) : kGrid), 1, 4, 5};
     }
     out[n++] = {(void *)k_labels, dim3(rm.ntiles + 1), 4, 6, 6};
     return n;
@@ -2793,8 +2594,8 @@ static_assert(sizeof(BatchReq) % 4 == 0, "request rows are copied as 32-bit word
 // The kernels of a batched update in order, each handed to `emit(fn, grid,
 // block, args)` (a graph-node adder or a stream launcher).  With `h_tab`
 // (pinned host rows) the diff kernel copies them to `tab`.
-// `after(stage)` follows each kernel: 0 diff, 1 cells, 3 item, 4 binary64
-// pass, 5 labels (count and write).
+// `after(stage)` follows each kernel: 0 diff, 1 cells, 3 item, 5 labels (count
+// and write).
 template <typename Emit, typename After>
 hipError_t batch_kernels(Emit emit, After after, const BatchReq *tab, const BatchReq *h_tab, const int32_t *grp,
                          int n, const BatchGroup *groups, int n_groups, bool any_grid, int n_tiles, int n_wtiles)
@@ -2820,12 +2621,6 @@ hipError_t batch_kernels(Emit emit, After after, const BatchReq *tab, const Batc
                              : (gr.mixed ? (void *)k_item32_batch<2> : (void *)k_item64_batch<2>);
         if ((err = emit(fn, dim3(kBatchItemGrid), dim3(kBlock), a_item)) != hipSuccess) return err;
         if ((err = after(3)) != hipSuccess) return err;
-        if (gr.mixed) {
-            void *a_fp[] = {(void *)&t, (void *)&gp};
-            void *fp = gr.D == 3 ? (void *)k_fp64_batch<3> : (void *)k_fp64_batch<2>;
-            if ((err = emit(fp, dim3(kFp64BatchGrid * cnt), dim3(kBlock), a_fp)) != hipSuccess) return err;
-            if ((err = after(4)) != hipSuccess) return err;
-        }
     }
     if ((err = emit((void *)k_count_batch, dim3(n_tiles), dim3(kBlock), a_tn)) != hipSuccess) return err;
     if ((err = emit((void *)k_write_batch, dim3(n_wtiles), dim3(kBlock), a_tn)) != hipSuccess) return err;

@@ -16,7 +16,6 @@ struct Ctl {
     int32_t status;        // RGG_OK / RGG_E_INVALID_ARG / RGG_E_STATE_MISMATCH
     int32_t n_chg;         // changed (box, sign) entries
     int32_t n_items;       // (cell, chunk) work items of the grid scan
-    int32_t n_df;          // items left whole to the binary64 pass (their list's length)
     int32_t label_ticket;  // next tile of the one-pass label kernel (dispatch order)
     int32_t claim;         // items claimed past the static ones by a batched item
                            // launch (the counter of its group's first request)
@@ -90,21 +89,14 @@ struct RmDev {
     rgg_box *resident;         // [M] obstacle slots
     ChgEntry *chg;             // [2M]
     int2 *items;               // [items_cap] (cell, chunk)
-    int2 *rc;                  // [kStatBlocks][rc_cap] (edge, entry) pairs each block of
-                               // the FP32 item kernel leaves to the binary64 re-test
-    int32_t *rc_cnt;           // [kStatBlocks]
-    int32_t rc_cap;
-    int32_t *df;               // [items_cap] items left whole to the binary64 pass (an
-                               // item block's re-test region was full), ctl->n_df of them
+    int32_t rc_cap;            // FP32 mode: undecided pairs a block collects before it
+                               // re-tests them (1..kRcCap)
     // the FP32 mode's pair listing and pair testing
     int32_t pl_cap;            // pairs each listing block may leave for the pair testing
     int32_t inline_rounds;     // pair rounds of an item its listing block tests before it
                                // lists the rest (kInlineAll: every round, no pair testing)
     int2 *pl;                  // [kStatBlocks][pl_cap] (edge, entry) pairs
     int32_t *pl_cnt;           // [kStatBlocks] pairs each listing block left
-    int2 *rt;                  // [kStatBlocks][rt_cap(pl_cap)] pairs each share left to the
-                               // binary64 re-test (a share holds at most that many pairs)
-    int32_t *rt_cnt;           // [kStatBlocks]
     int32_t *tile_cnt;         // [ntiles] gray edges per label tile
     unsigned long long *tile_state;   // [ntiles] look-back words of the one-pass label
                                       // kernel: flag (bits 62-63) | gray count
@@ -119,12 +111,12 @@ __host__ __device__ constexpr int obb_words(int D) { return 2 * D + D * D; }
 
 // per-block statistics rows: pairs, pairs whose outer approximation met,
 // re-tested pairs, bytes of the testing kernels, grid entries scanned,
-// candidate edges, bytes of the pair listing, bytes of the binary64 pass
+// candidate edges, bytes of the pair listing, bytes of the binary64 re-tests
 constexpr int kStats = 8;
 constexpr int kStatPairBytes = 3, kStatItemBytes = 6, kStatFp64Bytes = 7;
-constexpr int kStatBlocks = 2048;  // blocks of the item kernels
+constexpr int kStatBlocks = 2048;  // blocks of the item kernels at most
 constexpr int kStatRows = 256;     // rows of blk_stats in use: item and pair-share blocks add
-                                   // to row blockIdx & 255 (atomics), binary64 blocks to their own
+                                   // to row blockIdx & 255 (atomics)
 constexpr int kMaxSlots = 4096;    // 2*slots changed entries at most
 
 constexpr int kLocalCells = 512;   // uint4 words of the item kernel's slab masks (at most)
@@ -132,13 +124,9 @@ constexpr int kLocalCells = 512;   // uint4 words of the item kernel's slab mask
 __host__ __device__ constexpr int slabs_of(int D) { return D == 3 ? 80 : 128; }
 constexpr int kCopyStride3 = 4;    // values per sample copy in 3-D (xyz + pad)
 constexpr int kCopyStride2 = 2;    // in 2-D
-constexpr int kRcCap = 1024;       // default re-test pairs one item-kernel block may queue
+constexpr int kRcCap = 64;         // undecided pairs a block collects before it re-tests them
 constexpr int kPairListCap = 512;  // pairs one listing block may hand to the pair testing
 constexpr int kInlineAll = 0x7fffffff;   // inline_rounds: every round tested by the listing block
-// Capacity of a share's re-test region: a share holds at most one round
-// (kPairCap pairs) or, when the shares span every statistics block, at most
-// one listing block's capacity.
-__host__ __device__ constexpr int32_t rt_cap_of(int32_t pl_cap) { return pl_cap > 256 ? pl_cap : 256; }
 constexpr int kLabelTile = 4096;   // edges per block of the label kernels
 
 struct UpdateArgs {
@@ -167,7 +155,7 @@ constexpr int kMaxBatch = 256;     // requests per batched launch
 // allocates nothing.
 constexpr size_t kBatchTableBytes = (sizeof(BatchReq) * kMaxBatch + 255) / 256 * 256;
 constexpr size_t kBatchScratchBytes = kBatchTableBytes + sizeof(int32_t) * kMaxBatch;
-static_assert(kBatchScratchBytes <= 121 * 1024, "the documented size of the fixed request table");
+static_assert(kBatchScratchBytes <= 111 * 1024, "the documented size of the fixed request table");
 // Device address of that scratch on the current device (hipGetSymbolAddress).
 hipError_t batch_scratch_address(void **ptr);
 

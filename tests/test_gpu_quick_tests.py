@@ -116,3 +116,34 @@ def test_sphere_counts(ctx, B, kind, precision):
         robot = synth.robot_se3(rng, B)
     w = dataclasses.replace(w, robot=dataclasses.replace(robot, sphere_radius=robot.sphere_radius * 0.2))
     check(ctx, w, precision)
+
+
+@pytest.mark.parametrize("kind", ["planar", "spatial"])
+@pytest.mark.parametrize("cell_size", [-1.0, 0.0])
+@pytest.mark.parametrize("item_edges", [0, 512])
+def test_retest_queue_fills(ctx, kind, cell_size, item_edges):
+    """Every pair re-tested in binary64, with several tiles of changed entries
+    per item, whatever number of pairs a block collects first: labels, pair
+    counts and candidate counts do not depend on it."""
+    from paper_2603_28674_amd import rgg
+    import oracle
+    if kind == "planar":
+        w = synth.planar_rigid(seed=8, n_nodes=900, n_boxes=180, n_updates=2, n_move=170, world=40.0)
+    else:
+        w = synth.spatial_rigid(seed=9, n_nodes=900, n_boxes=180, n_updates=2, move_frac=0.9, world=4.0)
+    seen = []
+    for cap in (1, 5, 64, 0):
+        g = rgg.Roadmap.from_workload(ctx, w, precision=rgg.RGG_PREC_FP32_RECHECK, band_rel=float("inf"),
+                                      cell_size=cell_size, item_edges=item_edges, retest_capacity=cap)
+        o = oracle.from_workload(w)
+        prev, counts = w.absent(), []
+        for cur in w.boxes:
+            ol, og = o.update(prev, cur)
+            gl, gg, n, r = g.update(prev, cur)
+            assert np.array_equal(gl, ol) and np.array_equal(gg, og)
+            assert r.n_rechecked == r.n_pairs > 0
+            counts.append((r.n_pairs, r.n_outer_hits, r.n_candidate_edges, r.n_cells_visited))
+            prev = cur
+        seen.append(counts)
+        g.close()
+    assert all(x == seen[0] for x in seen)
