@@ -73,7 +73,7 @@ rgg_status install_grid(rgg_roadmap *rm, const HostGrid &grid, int32_t chunk)
     const size_t ncw = (size_t)((ncells + 31) / 32);
     int32_t *cstart = nullptr, *cedges = nullptr;
     uint32_t *bits = nullptr;
-    int2 *items = nullptr;
+    int4 *items = nullptr;
     int4 *cslot = nullptr;
     auto undo = [&](rgg_status s) {
         rm->release(cstart);
@@ -87,14 +87,8 @@ rgg_status install_grid(rgg_roadmap *rm, const HostGrid &grid, int32_t chunk)
     if ((st = rm->upload(&cstart, grid.start.data(), grid.start.size(), "grid starts")) != RGG_OK) return undo(st);
     if ((st = rm->upload(&cedges, grid.edges.data(), grid.edges.size(), "grid lists")) != RGG_OK) return undo(st);
     if ((st = rm->alloc(&bits, ncw, "cell marks")) != RGG_OK) return undo(st);
-    if (ncells == 1) {
-        // the one cell's work items never change: (0, h) for every chunk h
-        std::vector<int2> fixed((size_t)grid.items_cap);
-        for (int64_t h = 0; h < grid.items_cap; ++h) fixed[(size_t)h] = make_int2(0, (int32_t)h);
-        if ((st = rm->upload(&items, fixed.data(), fixed.size(), "grid items")) != RGG_OK) return undo(st);
-    } else if ((st = rm->alloc(&items, (size_t)grid.items_cap, "grid items")) != RGG_OK) {
-        return undo(st);
-    }
+    // (one cell's items are chunks of the edges in order: no list)
+    if (ncells > 1 && (st = rm->alloc(&items, (size_t)grid.items_cap, "grid items")) != RGG_OK) return undo(st);
     hipError_t e = hipMemset(bits, 0, 4 * std::max<size_t>(ncw, 1));
     if (e != hipSuccess) return undo(hip_fail(e, "clear marks"));
     if (ncells > 1 && !grid.edges.empty()) {
@@ -481,7 +475,7 @@ int64_t device_bytes_needed(const HostGeometry &g, const HostGrid &grid, const R
     add(grid.edges.size(), 4);
     if (ncells > 1 && !grid.edges.empty()) add(grid.edges.size(), sizeof(int4));
     add((size_t)((ncells + 31) / 32), 4);
-    add((size_t)grid.items_cap, sizeof(int2));
+    if (ncells > 1) add((size_t)grid.items_cap, sizeof(int4));
     const int64_t ntiles = std::max<int64_t>(1, (E + kLabelTile - 1) / kLabelTile);
     add((size_t)E, sizeof(int2));
     add((size_t)M, sizeof(rgg_box));

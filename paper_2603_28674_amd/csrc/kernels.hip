@@ -45,6 +45,7 @@ namespace rgg {
 namespace {
 
 constexpr int kDiffBlock = 1024;
+constexpr int kFewChunks = 4;      // items that one thread emits for a cell
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
 constexpr int kGrid = kStatBlocks; // blocks of the item kernels
@@ -302,7 +303,8 @@ __device__ inline long long block_prefix64(long long v, long long *total, long l
 
 // Grid roadmaps: the cells the n_chg changed entries cover are marked and
 // each newly marked cell emits one work item per chunk of its edges (an
-// empty cell one item, whose first chunk clears the mark).  One block of
+// empty cell one item, whose first chunk clears the mark).  An item names its
+// slots of the cell lists, so an item block needs no look at the cell.  One block of
 // kDiffBlock threads, right after the entries are written: the (entry,
 // cell) pairs are dealt over the threads (a prefix over the entries' cell
 // counts), so every mark of a pass is in flight at once, and the items go
@@ -314,9 +316,16 @@ __device__ __forceinline__ void activate_cells(const RmDev &rm, int n_chg)
     __shared__ int s_rng[kDiffBlock][5];   // first cell (x, y, z), cells along x and y
     __shared__ long long s_w64[kNW];
     __shared__ int s_w32[kNW];
-    __shared__ int s_items;
+    __shared__ int s_items, s_nbig;
+    __shared__ int4 s_big[kDiffBlock];     // cells of many chunks: cell, first slot, slots, position
     const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
-    if (tid == 0) s_items = 0;
+    if (tid == 0) {
+        s_items = 0;
+        s_nbig = 0;
+    }
+    auto put = [&](int pos, int cell, int s0, int n, int h) {
+        if (pos < rm.items_cap) rm.items[pos] = make_int4(s0 + h * rm.chunk, min(rm.chunk, n - h * rm.chunk), cell, h);
+    };
     for (int q0 = 0; q0 < n_chg; q0 += kDiffBlock) {
         const int q = q0 + tid;
         long long cnt = 0;
@@ -337,7 +346,7 @@ __device__ __forceinline__ void activate_cells(const RmDev &rm, int n_chg)
         const int ne = min(kDiffBlock, n_chg - q0);
         for (long long t0 = 0; t0 < tot; t0 += kDiffBlock) {
             const long long t = t0 + tid;
-            int nch = 0;
+            int nch = 0, s0 = 0, n = 0;
             long long c = 0;
             if (t < tot) {
                 // the entry holding pair t: the last j with s_cpre[j] <= t
@@ -354,9 +363,9 @@ __device__ __forceinline__ void activate_cells(const RmDev &rm, int n_chg)
                 const int32_t z = s_rng[lo][2] + (int32_t)(k / ((long long)nx * ny));
                 c = ((long long)z * rm.gdim[1] + y) * rm.gdim[0] + x;
                 const uint32_t bit = 1u << (c & 31);
-                const int32_t s0 = rm.cell_start[c], s1 = rm.cell_start[c + 1];
+                s0 = rm.cell_start[c];
+                n = rm.cell_start[c + 1] - s0;
                 if (!(atomicOr(&rm.cell_bits[c >> 5], bit) & bit)) {
-                    const int32_t n = s1 - s0;
                     nch = n > 0 ? (n + rm.chunk - 1) / rm.chunk : 1;
                 }
             }
@@ -375,10 +384,24 @@ __device__ __forceinline__ void activate_cells(const RmDev &rm, int n_chg)
                 ntot += s_w32[w];
             }
             const int pos = off + x - nch;
-            for (int h = 0; h < nch; ++h)
-                if ((int64_t)pos + h < rm.items_cap) rm.items[pos + h] = make_int2((int32_t)c, h);
+            // a cell's items one after another on its thread, but a cell of
+            // many chunks (coarse grids over many edges) on a wavefront: an arm
+            // with 56k edges in 9 cells took 23 us here with one thread each
+            if (nch <= kFewChunks) {
+                for (int h = 0; h < nch; ++h) put(pos + h, (int)c, s0, n, h);
+            } else {
+                s_big[atomicAdd(&s_nbig, 1)] = make_int4((int)c, s0, n, pos);
+            }
             __syncthreads();
-            if (tid == 0) s_items += ntot;
+            for (int b = wv; b < s_nbig; b += kNW) {
+                const int4 w = s_big[b];
+                for (int h = lane; h * rm.chunk < w.z; h += 64) put(w.w + h, w.x, w.y, w.z, h);
+            }
+            __syncthreads();
+            if (tid == 0) {
+                s_items += ntot;
+                s_nbig = 0;
+            }
             __syncthreads();
         }
     }
@@ -634,14 +657,16 @@ __device__ bool splines_meet64(const RmDev &rm, int64_t e, uint64_t m, const dou
 // k_item: one block per work item (grid cell c, a chunk of at most 256 of
 // its edges; the chunk size is the roadmap's work-item size).
 //
-//   1. every thread owns one edge of the item.  The changed entries covering
-//      the cell are staged in LDS (tiles of kSubTile) and registered in a
-//      block-local pruning grid (an entry over more than kWideCells of its
-//      cells is a candidate of every edge); a thread ORs the masks of the
-//      pruning cells its edge's box covers and marks the candidates whose
-//      box meets its edge's box, 32 per LDS word.  With several grid cells a
-//      pair is taken only by the cell holding the lower corner of the two
-//      boxes' intersection, so each (edge, entry) pair is tested once.
+//   1. every thread owns up to two edges of the item.  The changed entries
+//      covering the cell are staged in LDS (tiles of kSubTile) and, when there
+//      are many, registered in block-local slab masks; a thread ANDs the masks
+//      of its edge's slabs and marks the candidates whose box meets its edge's
+//      box, 32 per LDS word.  With several grid cells a pair is taken only by
+//      the cell holding the lower corner of the two boxes' intersection, so
+//      each (edge, entry) pair is tested once.
+//      An item's start was five dependent rounds of loads (7 us of a block's
+//      16 on small roadmaps); its loads are now requested together as far as
+//      they do not depend on one another.
 //   2. outer test, lanes = (pair, sphere): the capsule's ends are two of the
 //      sphere's copies, and one that meets settles the pair (S is an existence
 //      test, and S implies C); separation and end-sphere tests settle most of
@@ -665,6 +690,9 @@ __device__ bool splines_meet64(const RmDev &rm, int64_t e, uint64_t m, const dou
 constexpr int kSubTile = 128;             // changed entries staged per tile
 constexpr int kSlots = 2;                 // edge slots per thread
 constexpr int kItemCap = kSlots * kBlock; // edges per work item at most
+constexpr int kSlabMin = 33;              // staged entries from which the slab masks are made: an
+                                          // edge tests one word's worth itself (spatial, 29k edges,
+                                          // 12 changed boxes: 41.6 us with the masks, 39.8 without)
 constexpr int kWords = kSubTile / 32;     // overlap words per edge
 constexpr int kPairCap = kBlock;          // pairs per round (one per thread)
 constexpr int kRowCap = 256;              // (pair, sphere) rows per copy round
@@ -1381,6 +1409,72 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
     __syncthreads();
 }
 
+// The block-local slab masks of the nt entries staged in L (masks zeroed
+// before): each staged entry marks the slab its range starts in and the slab it
+// ends in, on every axis; then each axis's start marks become "starts at or
+// before s" (an OR over slabs 0..s) and its end marks "ends at or after s" (an
+// OR over s..n-1): one wavefront per (axis, mark), each lane two slabs, the
+// lanes joined by a wavefront scan.
+template <int D, typename Lds>
+__device__ __forceinline__ void slab_masks(const RmDev &rm, Lds &L, int nt)
+{
+    constexpr int kSl = slabs_of(D);
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
+    if (tid < nt) {
+        const float4 l = L.blo[tid], h = L.bhi[tid];
+        const float lo3[3] = {l.x, l.y, l.z}, hi3[3] = {h.x, h.y, h.z};
+        const uint32_t bit = 1u << (tid & 31);
+        const int wd = tid >> 5;
+        uint32_t *mw = reinterpret_cast<uint32_t *>(L.g.sm);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            atomicOr(&mw[((2 * d) * kSl + slab_of(rm, d, lo3[d], kSl)) * 4 + wd], bit);
+            atomicOr(&mw[((2 * d + 1) * kSl + slab_of(rm, d, hi3[d], kSl)) * 4 + wd], bit);
+        }
+    }
+    __syncthreads();
+    for (int a = wv; a < 2 * D; a += kWaves) {
+        const bool up = (a & 1) == 0;   // start marks: forward
+        uint4 *arr = L.g.sm + a * kSl;
+        const int s0 = 2 * lane, s1 = 2 * lane + 1;
+        auto at = [&](int s) -> uint4 & { return arr[up ? s : kSl - 1 - s]; };
+        uint4 v0 = s0 < kSl ? at(s0) : make_uint4(0u, 0u, 0u, 0u);
+        uint4 v1 = s1 < kSl ? at(s1) : make_uint4(0u, 0u, 0u, 0u);
+        v1 = make_uint4(v1.x | v0.x, v1.y | v0.y, v1.z | v0.z, v1.w | v0.w);
+        uint4 ex = v1;   // inclusive OR over lanes 0..lane, then shifted
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t x = __shfl_up(ex.x, o), y = __shfl_up(ex.y, o), z = __shfl_up(ex.z, o),
+                           w = __shfl_up(ex.w, o);
+            if (lane >= o) ex = make_uint4(ex.x | x, ex.y | y, ex.z | z, ex.w | w);
+        }
+        uint4 pre = make_uint4(__shfl_up(ex.x, 1), __shfl_up(ex.y, 1), __shfl_up(ex.z, 1),
+                               __shfl_up(ex.w, 1));
+        if (lane == 0) pre = make_uint4(0u, 0u, 0u, 0u);
+        if (s0 < kSl) at(s0) = make_uint4(pre.x | v0.x, pre.y | v0.y, pre.z | v0.z, pre.w | v0.w);
+        if (s1 < kSl) at(s1) = make_uint4(pre.x | v1.x, pre.y | v1.y, pre.z | v1.z, pre.w | v1.w);
+    }
+}
+
+// What staging takes of a changed entry, requested together.
+struct Prefetched {
+    float4 a, b;            // lo32[0..2], hi32[0]; hi32[1..2], sbox, sign
+    int32_t c0[3], c1[3];
+};
+
+__device__ inline Prefetched fetch_entry(const ChgEntry &en)
+{
+    Prefetched p;
+    const float4 *q = reinterpret_cast<const float4 *>(&en);
+    p.a = q[0];
+    p.b = q[1];
+    for (int k = 0; k < 3; ++k) {
+        p.c0[k] = en.c0[k];
+        p.c1[k] = en.c1[k];
+    }
+    return p;
+}
+
 // Items li0, li0 + lstride, ... of the roadmap (statistics row blockIdx.x).
 //
 // kList: the pair listing of the FP32 mode.  Each round of pairs goes to this
@@ -1411,90 +1505,81 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
         if constexpr (kF32) L.r64.n = 0;
         L.pl_n = 0;
     }
+    const bool single = rm.ncells == 1;
+    const int4 item0 = !single && li0 < (int)rm.items_cap ? rm.items[li0] : make_int4(0, 0, 0, 0);
     const int status = ctl->status;
-    __syncthreads();
     // wavefront-uniform counts (kept in scalar registers) and per-lane ones
     uint32_t n_pairs = 0, visited = 0, cand = 0, n_outer = 0;
     unsigned long long bytes = 0;
     const int n_chg = ctl->n_chg;
     const int n_items = min(ctl->n_items, (int32_t)rm.items_cap);
-    const bool single = rm.ncells == 1;
     const float4 *aabb = reinterpret_cast<const float4 *>(rm.aabb);
     const int jfix = rm.p_fixed ? rm.p_fixed / B : 0;
     constexpr int kSl = slabs_of(D);   // slabs per axis of the slab masks
     // where to go on: the item, its tile of changed entries, the tile's round
     // (not zero only after the re-test queue filled in the middle of an item)
     int it = li0, tile0 = 0, round0 = 0;
-    bool full = status == RGG_OK;
+    bool full = true;
     uint32_t had = 0;   // bit h: edge slot h of the item has pairs
     while (full) {
         full = false;
-        for (; it < n_items && !full; it += full ? 0 : lstride) {
+        for (; it < (int)rm.items_cap && !full; it += full ? 0 : lstride) {
             const bool anew = tile0 == 0 && round0 == 0;
-            // with one cell the items are (0, h) and the cell's list is every
-            // edge in order: the item's edges are beg .. end - 1 themselves
-            const int2 item = single ? make_int2(0, it) : rm.items[it];
-            const int64_t c = item.x;
-            const int32_t cx = (int32_t)(c % rm.gdim[0]);
-            const int32_t cy = (int32_t)((c / rm.gdim[0]) % rm.gdim[1]);
-            const int32_t cz = (int32_t)(c / ((int64_t)rm.gdim[0] * rm.gdim[1]));
-            int64_t beg, end;
-            if (single) {
-                beg = (int64_t)item.y * rm.chunk;
-                end = min(rm.E, beg + rm.chunk);
-            } else {
-                beg = (int64_t)rm.cell_start[c] + (int64_t)item.y * rm.chunk;
-                end = min((int64_t)rm.cell_start[c + 1], beg + rm.chunk);
-            }
-            const int n_e = (int)(end - beg);   // edge slots in use: tid, tid + kBlock
+            // with one cell the items are chunks of the edges in order; else
+            // slots of the cell lists.  What an item needs first is requested
+            // in one go: the edges' slots and boxes and, beside them, the first
+            // tile's entries (used when there are any), so that an item's
+            // start waits for one round of loads with one cell and for three
+            // (the item, the slots, the boxes) with several.
+            int4 item = item0;
+            if (single) item = make_int4(it * rm.chunk, (int)min((int64_t)rm.chunk, rm.E - (int64_t)it * rm.chunk), 0, 0);
+            else if (it != li0) item = rm.items[it];
+            if (!single && (status != RGG_OK || it >= n_items)) break;
+            const int beg = item.x, n_e = item.y;   // edge slots in use: tid, tid + kBlock
             int e[kSlots], J[kSlots];
-            float es[kSlots];
+            float4 bl[kSlots], bh[kSlots];          // the edges' boxes: (lo, s), (hi, pad)
             uint32_t j0[kSlots];
-    #pragma unroll
+#pragma unroll
             for (int h = 0; h < kSlots; ++h) {
                 const int sl = tid + h * kBlock;
                 e[h] = 0;
                 J[h] = 0;
-                es[h] = 0.0f;
                 j0[h] = 0;
+                bl[h] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                bh[h] = bl[h];
                 if (sl < n_e) {
+                    e[h] = beg + sl;
                     if (!single) {
                         // the cell list's slot: one contiguous load, no gather
                         const int4 cs = rm.cell_slot[beg + sl];
                         e[h] = cs.x;
-                        es[h] = __int_as_float(cs.y);
                         j0[h] = (uint32_t)cs.z;
                         J[h] = cs.w;
+                    } else if (jfix) {
+                        J[h] = jfix;
+                        j0[h] = (uint32_t)((int64_t)e[h] * jfix);
                     } else {
-                        e[h] = (int)(beg + sl);
-                        es[h] = aabb[2 * (int64_t)e[h]].w;
-                        if (jfix) {
-                            J[h] = jfix;
-                            j0[h] = (uint32_t)((int64_t)e[h] * jfix);
-                        } else {
-                            const int64_t s0 = rm.soff[e[h]];
-                            j0[h] = (uint32_t)(s0 / B);
-                            J[h] = (int)((rm.soff[e[h] + 1] - s0) / B);
-                        }
+                        const int64_t s0 = rm.soff[e[h]];
+                        j0[h] = (uint32_t)(s0 / B);
+                        J[h] = (int)((rm.soff[e[h] + 1] - s0) / B);
                     }
-                    bytes += anew ? 32 : 0;
+                    bl[h] = aabb[2 * (int64_t)e[h]];
+                    bh[h] = aabb[2 * (int64_t)e[h] + 1];
                 }
             }
-            // with one cell every entry covers it: the first tile's entries are
-            // requested together with the edges (binary32 boxes, size, sign)
-            const bool pf = kF32 && single;
-            float4 pf_a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), pf_b = pf_a;
-            if (pf && tid < kSubTile && tid < n_chg) {
-                const float4 *q = reinterpret_cast<const float4 *>(&rm.chg[tid]);
-                pf_a = q[0];   // lo32[0..2], hi32[0]
-                pf_b = q[1];   // hi32[1..2], sbox, sign
-            }
+            Prefetched pf{};
+            if (tid < kSubTile && tid < 2 * rm.M) pf = fetch_entry(rm.chg[tid]);
+            // this block's place in the work, now that its loads are out
+            if (status != RGG_OK || it >= n_items) break;
+            if (anew) bytes += (tid < n_e ? 32 : 0) + (tid + kBlock < n_e ? 32 : 0);
+            const int c = item.z;
+            const int cx = c % rm.gdim[0], cy = c / rm.gdim[0] % rm.gdim[1], cz = c / (rm.gdim[0] * rm.gdim[1]);
             __syncthreads();   // the previous item is done with the LDS arrays
-    #pragma unroll
+#pragma unroll
             for (int h = 0; h < kSlots; ++h) {
                 const int sl = tid + h * kBlock;
                 L.edge[sl] = e[h];
-                L.es[sl] = es[h];
+                L.es[sl] = bl[h].w;
                 L.cfg0[sl] = j0[h];
                 L.ej[sl] = J[h];
                 L.dC[sl] = 0;
@@ -1504,92 +1589,45 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
             if (tid == 0) {
                 // every item is visited once: clear the cell's mark with its
                 // first chunk, so the next update starts from zero marks
-                if (!single && item.y == 0) atomicAnd(&rm.cell_bits[c >> 5], ~(1u << (c & 31)));
+                if (!single && item.w == 0) atomicAnd(&rm.cell_bits[c >> 5], ~(1u << (c & 31)));
             }
             if (anew) had = 0;
             bool fused = !kList;   // some round of this item was tested here
             int n_round = 0;       // this item's pair rounds so far
             for (int j0 = tile0; j0 < n_chg && !full; j0 += kSubTile) {
-                // the slab masks start empty (the previous tile or item is done
-                // with their storage); the staging scan's barriers order this
-                // before they are filled
-                for (int q = tid; q < 2 * D * kSl; q += kBlock) L.g.sm[q] = make_uint4(0u, 0u, 0u, 0u);
-                // stage the entries covering this cell
+                // stage the entries covering this cell (with one cell: all)
                 const int j = j0 + tid;
-                const bool first = pf && j0 == 0;
-                bool in = false;
-                if (tid < kSubTile && j < n_chg) {
-                    if (first) {
-                        in = true;
-                    } else {
-                        const ChgEntry &en = rm.chg[j];
-                        in = single || (cx >= en.c0[0] && cx <= en.c1[0] && cy >= en.c0[1] && cy <= en.c1[1] &&
-                                        cz >= en.c0[2] && cz <= en.c1[2]);
-                    }
-                }
-                int nt;
-                const int pos = block_scan(in ? 1 : 0, &nt, L.wsum);
+                bool in = tid < kSubTile && j < n_chg;
                 if (in) {
-                    if (first) {
-                        L.blo[pos] = make_float4(pf_a.x, pf_a.y, pf_a.z, pf_b.z);
-                        L.bhi[pos] = make_float4(pf_a.w, pf_b.x, pf_b.y, 0.0f);
-                        L.sign[pos] = __float_as_int(pf_b.w);
-                    } else {
+                    if (j0 > 0) pf = fetch_entry(rm.chg[j]);
+                    in = single || (cx >= pf.c0[0] && cx <= pf.c1[0] && cy >= pf.c0[1] && cy <= pf.c1[1] &&
+                                    cz >= pf.c0[2] && cz <= pf.c1[2]);
+                }
+                int nt = min(kSubTile, n_chg - j0), pos = tid;
+                if (!single) pos = block_scan(in ? 1 : 0, &nt, L.wsum);
+                if (in) {
+                    L.blo[pos] = make_float4(pf.a.x, pf.a.y, pf.a.z, pf.b.z);
+                    L.bhi[pos] = make_float4(pf.a.w, pf.b.x, pf.b.y, 0.0f);
+                    L.sign[pos] = __float_as_int(pf.b.w);
+                    if constexpr (!kF32) {
                         const ChgEntry &en = rm.chg[j];
-                        L.blo[pos] = make_float4(en.lo32[0], en.lo32[1], en.lo32[2], en.sbox);
-                        L.bhi[pos] = make_float4(en.hi32[0], en.hi32[1], en.hi32[2], 0.0f);
-                        if constexpr (!kF32) {
-                            for (int k = 0; k < 3; ++k) {
-                                L.x.lo[k][pos] = en.lo[k];
-                                L.x.hi[k][pos] = en.hi[k];
-                            }
+                        for (int k = 0; k < 3; ++k) {
+                            L.x.lo[k][pos] = en.lo[k];
+                            L.x.hi[k][pos] = en.hi[k];
                         }
-                        L.sign[pos] = en.sign;
                     }
                     L.gidx[pos] = j;
                 }
+                pf = Prefetched{};   // not kept through the rounds
                 if (nt == 0) continue;   // uniform: nt is the block total
                 const int nw = (nt + 31) >> 5;
-                __syncthreads();
-                // block-local slab masks: each staged entry marks the slab its
-                // range starts in and the slab it ends in, on every axis ...
-                if (tid < nt) {
-                    const float4 l = L.blo[tid], h = L.bhi[tid];
-                    const float lo3[3] = {l.x, l.y, l.z}, hi3[3] = {h.x, h.y, h.z};
-                    const uint32_t bit = 1u << (tid & 31);
-                    const int wd = tid >> 5;
-                    uint32_t *mw = reinterpret_cast<uint32_t *>(L.g.sm);
-    #pragma unroll
-                    for (int d = 0; d < D; ++d) {
-                        atomicOr(&mw[((2 * d) * kSl + slab_of(rm, d, lo3[d], kSl)) * 4 + wd], bit);
-                        atomicOr(&mw[((2 * d + 1) * kSl + slab_of(rm, d, hi3[d], kSl)) * 4 + wd], bit);
-                    }
-                }
-                __syncthreads();
-                // ... then each axis's start marks become "starts at or before s"
-                // (an OR over slabs 0..s) and its end marks "ends at or after s"
-                // (an OR over s..n-1): one wavefront per (axis, mark), each lane
-                // two slabs, the lanes joined by a wavefront scan
-                for (int a = wv; a < 2 * D; a += kWaves) {
-                    const bool up = (a & 1) == 0;   // start marks: forward
-                    uint4 *arr = L.g.sm + a * kSl;
-                    const int s0 = 2 * lane, s1 = 2 * lane + 1;
-                    auto at = [&](int s) -> uint4 & { return arr[up ? s : kSl - 1 - s]; };
-                    uint4 v0 = s0 < kSl ? at(s0) : make_uint4(0u, 0u, 0u, 0u);
-                    uint4 v1 = s1 < kSl ? at(s1) : make_uint4(0u, 0u, 0u, 0u);
-                    v1 = make_uint4(v1.x | v0.x, v1.y | v0.y, v1.z | v0.z, v1.w | v0.w);
-                    uint4 ex = v1;   // inclusive OR over lanes 0..lane, then shifted
-    #pragma unroll
-                    for (int o = 1; o < 64; o <<= 1) {
-                        const uint32_t x = __shfl_up(ex.x, o), y = __shfl_up(ex.y, o), z = __shfl_up(ex.z, o),
-                                       w = __shfl_up(ex.w, o);
-                        if (lane >= o) ex = make_uint4(ex.x | x, ex.y | y, ex.z | z, ex.w | w);
-                    }
-                    uint4 pre = make_uint4(__shfl_up(ex.x, 1), __shfl_up(ex.y, 1), __shfl_up(ex.z, 1),
-                                           __shfl_up(ex.w, 1));
-                    if (lane == 0) pre = make_uint4(0u, 0u, 0u, 0u);
-                    if (s0 < kSl) at(s0) = make_uint4(pre.x | v0.x, pre.y | v0.y, pre.z | v0.z, pre.w | v0.w);
-                    if (s1 < kSl) at(s1) = make_uint4(pre.x | v1.x, pre.y | v1.y, pre.z | v1.z, pre.w | v1.w);
+                // block-local slab masks, from kSlabMin entries on (below that
+                // testing every entry costs less than the masks)
+                const bool slabs = nt >= kSlabMin;
+                if (slabs) {
+                    for (int q = tid; q < 2 * D * kSl; q += kBlock) L.g.sm[q] = make_uint4(0u, 0u, 0u, 0u);
+                    __syncthreads();
+                    slab_masks<D>(rm, L, nt);
                 }
                 __syncthreads();
                 // the staged entries each of this thread's edges meets, 32 per
@@ -1597,34 +1635,35 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
                 // every axis (all reads of the slab masks first: their storage
                 // then takes the words), then the exact test against the edge's
                 // box
-                float4 bl[kSlots], bh[kSlots];
                 uint32_t cw[kSlots][kWords];
-                // both slots' boxes are requested before either is used
-    #pragma unroll
-                for (int h = 0; h < kSlots; ++h) {
-                    const int sl = tid + h * kBlock;
-                    bl[h] = make_float4(0, 0, 0, 0);
-                    bh[h] = bl[h];
-                    if (sl < n_e) {
-                        bl[h] = aabb[2 * (int64_t)L.edge[sl]];
-                        bh[h] = aabb[2 * (int64_t)L.edge[sl] + 1];
+                if (j0 != tile0) {   // a later tile: the boxes again
+#pragma unroll
+                    for (int h = 0; h < kSlots; ++h) {
+                        const int sl = tid + h * kBlock;
+                        if (sl < n_e) {
+                            bl[h] = aabb[2 * (int64_t)L.edge[sl]];
+                            bh[h] = aabb[2 * (int64_t)L.edge[sl] + 1];
+                        }
                     }
                 }
-    #pragma unroll
+#pragma unroll
                 for (int h = 0; h < kSlots; ++h) {
                     const int sl = tid + h * kBlock;
-    #pragma unroll
+#pragma unroll
                     for (int w = 0; w < kWords; ++w) cw[h][w] = 0u;
                     if (sl < n_e) {
                         const float lo3[3] = {bl[h].x, bl[h].y, bl[h].z}, hi3[3] = {bh[h].x, bh[h].y, bh[h].z};
                         uint4 m = make_uint4(~0u, ~0u, ~0u, ~0u);
-    #pragma unroll
-                        for (int d = 0; d < D; ++d) {
-                            // entries starting at or before the edge's last slab
-                            // and ending at or after its first
-                            const uint4 st = L.g.sm[(2 * d) * kSl + slab_of(rm, d, hi3[d], kSl)];
-                            const uint4 en = L.g.sm[(2 * d + 1) * kSl + slab_of(rm, d, lo3[d], kSl)];
-                            m = make_uint4(m.x & st.x & en.x, m.y & st.y & en.y, m.z & st.z & en.z, m.w & st.w & en.w);
+                        if (slabs) {
+#pragma unroll
+                            for (int d = 0; d < D; ++d) {
+                                // entries starting at or before the edge's last
+                                // slab and ending at or after its first
+                                const uint4 st = L.g.sm[(2 * d) * kSl + slab_of(rm, d, hi3[d], kSl)];
+                                const uint4 en = L.g.sm[(2 * d + 1) * kSl + slab_of(rm, d, lo3[d], kSl)];
+                                m = make_uint4(m.x & st.x & en.x, m.y & st.y & en.y, m.z & st.z & en.z,
+                                               m.w & st.w & en.w);
+                            }
                         }
                         cw[h][0] = m.x;
                         cw[h][1] = m.y;
@@ -1634,12 +1673,12 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
                 }
                 __syncthreads();
                 int cnt = 0;
-    #pragma unroll
+#pragma unroll
                 for (int h = 0; h < kSlots; ++h) {
                     const int sl = tid + h * kBlock;
                     if (sl >= n_e) continue;
                     int ch = 0;
-    #pragma unroll
+#pragma unroll
                     for (int w = 0; w < kWords; ++w) {
                         if (w < nw) {
                             const int left = nt - 32 * w;   // staged entries from this word on
@@ -1663,6 +1702,8 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
                     cnt += ch;
                     if (ch) had |= 1u << h;
                 }
+#pragma unroll
+                for (int h = 0; h < kSlots; ++h) bl[h] = bh[h] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // not kept
                 int tp;
                 const int pre = block_scan(cnt, &tp, L.wsum);
                 for (int r0 = j0 == tile0 ? round0 : 0; r0 < tp && !full; r0 += kPairCap) {
@@ -1720,7 +1761,7 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
             if (!full) cand += (uint32_t)(__popcll(__ballot(had & 1u)) + __popcll(__ballot(had & 2u)));
             if (fused && !full) bytes += (unsigned long long)__popc(had) * ((2 * D + 1) * B * sizeof(T) + 16);
             __syncthreads();
-    #pragma unroll
+#pragma unroll
             for (int h = 0; h < kSlots; ++h) {
                 const int sl = tid + h * kBlock;
                 if (sl < n_e) add_counts(rm, L.edge[sl], L.dC[sl], L.dS[sl]);

@@ -88,7 +88,8 @@ struct RmDev {
     uint32_t *cell_bits;       // [ceil(ncells/32)] touched cells, zero between updates
     rgg_box *resident;         // [M] obstacle slots
     ChgEntry *chg;             // [2M]
-    int2 *items;               // [items_cap] (cell, chunk)
+    int4 *items;               // [items_cap] (first slot of the cell lists, slots, cell, chunk);
+                               // not used with one cell, whose items are chunks of the edges
     int32_t rc_cap;            // FP32 mode: undecided pairs a block collects before it
                                // re-tests them (1..kRcCap)
     // the FP32 mode's pair listing and pair testing

@@ -1,0 +1,53 @@
+"""Work items against the oracle (GPU): cells of few and of many chunks (their
+items are emitted by a thread or by a wavefront), items with fewer and more
+changed entries than the slab masks start from and than one tile holds, cells
+without edges, and moves that leave the grid."""
+import numpy as np
+import pytest
+
+from paper_2603_28674_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2603_28674_amd import rgg
+    c = rgg.rgg_context_create(0)
+    yield c
+    rgg.rgg_context_destroy(c)
+
+
+@pytest.mark.parametrize("kind", ["planar", "spatial"])
+@pytest.mark.parametrize("cells", [1, 2, 5, 20])
+@pytest.mark.parametrize("item_edges", [1, 37, 64, 511])
+@pytest.mark.parametrize("n_boxes", [4, 16, 17, 64, 65, 150])
+def test_items(ctx, kind, cells, item_edges, n_boxes):
+    """n_boxes moved at once: 2 n_boxes changed entries around 32, 33, 128 and
+    300; a cell then holds from one item to some thousand."""
+    from paper_2603_28674_amd import rgg
+    import oracle
+    if kind == "planar":
+        w = synth.planar_rigid(seed=n_boxes, n_nodes=500, n_boxes=n_boxes, n_updates=2, n_move=n_boxes, world=30.0,
+                               resolution=0.5)
+        world = 30.0
+    else:
+        w = synth.spatial_rigid(seed=n_boxes, n_nodes=400, n_boxes=n_boxes, n_updates=2, move_frac=1.0, world=3.0,
+                                samples=5)
+        world = 3.0
+    out = w.boxes[-1].copy()          # half of the boxes leave the grid, then come back
+    out[::2, :2] += 50.0 * world
+    out[::2, 3:5] += 50.0 * world
+    w.boxes = w.boxes + [out, w.boxes[-1]]
+    rng = np.random.default_rng(cells)
+    for prec in (rgg.RGG_PREC_FP64, rgg.RGG_PREC_FP32_RECHECK):
+        g = rgg.Roadmap.from_workload(ctx, w, precision=prec, cell_size=-1.0 if cells == 1 else world / cells,
+                                      item_edges=item_edges)
+        o = oracle.from_workload(w)
+        prev = w.absent()
+        for cur in w.boxes:
+            ol, og = o.update(prev, cur)
+            gl, gg, n, _ = g.update(prev, cur)
+            assert np.array_equal(gl, ol) and np.array_equal(gg, og)
+            prev = cur
+        g.close()
