@@ -443,6 +443,9 @@ int32_t inline_rounds_of(int32_t opt)
 
 rgg_status hip_ok(hipError_t e, const char *what) { return e == hipSuccess ? RGG_OK : hip_fail(e, what); }
 
+// Values of the binary32 capsules (RmDev::cap32).
+size_t cap32_words(const HostGeometry &g) { return (size_t)(g.E * g.B) * (g.D == 3 ? 8 : 4); }
+
 // Device bytes make_roadmap allocates for g, grid and p (each array at least
 // one element, as rgg_roadmap::alloc gives it).
 int64_t device_bytes_needed(const HostGeometry &g, const HostGrid &grid, const RoadmapParams &p)
@@ -459,7 +462,8 @@ int64_t device_bytes_needed(const HostGeometry &g, const HostGrid &grid, const R
     add((size_t)B, 4);
     if (p.mixed) {
         add(g.samp.size(), 4);
-        add(g.cap.size(), 4);
+        add(cap32_words(g), 4);
+        if (g.D == 2) add((size_t)(E * B), 4);
     }
     if (!g.obb.empty()) {
         add(g.obb.size(), 8);
@@ -575,14 +579,41 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
         std::vector<float> tmp;
         float *s32, *c32;
         try {
-            tmp.resize(std::max(nsamp, ncap));
+            tmp.resize(std::max(nsamp, cap32_words(g)));
         } catch (const std::bad_alloc &) {
             return guard(fail(RGG_E_OUT_OF_MEMORY, "host memory for binary32 copies"));
         }
         for (size_t i = 0; i < nsamp; ++i) tmp[i] = (float)g.samp[i];
         if ((st = rm->upload(&s32, tmp.data(), nsamp, "binary32 samples")) != RGG_OK) return guard(st);
-        for (size_t i = 0; i < ncap; ++i) tmp[i] = (float)g.cap[i];
-        if ((st = rm->upload(&c32, tmp.data(), ncap, "binary32 capsules")) != RGG_OK) return guard(st);
+        std::vector<float> rad;
+        try {
+            if (D == 2) rad.resize((size_t)(E * B));
+        } catch (const std::bad_alloc &) {
+            return guard(fail(RGG_E_OUT_OF_MEMORY, "host memory for binary32 copies"));
+        }
+        for (int64_t e = 0; e < E; ++e) {
+            const double *cp = g.cap.data() + e * (2 * D + 1) * B;
+            for (int i = 0; i < B; ++i) {
+                const int64_t k = e * B + i;
+                float *q = tmp.data() + k * (D == 3 ? 8 : 4);
+                for (int d = 0; d < D; ++d) {
+                    q[d] = (float)cp[d * B + i];
+                    q[D == 3 ? 4 + d : 2 + d] = (float)cp[(D + d) * B + i];
+                }
+                if (D == 3) {
+                    q[3] = (float)cp[6 * B + i];
+                    q[7] = fabsf(q[4] - q[0]) + fabsf(q[5] - q[1]) + fabsf(q[6] - q[2]);
+                } else {
+                    rad[(size_t)k] = (float)cp[4 * B + i];
+                }
+            }
+        }
+        if ((st = rm->upload(&c32, tmp.data(), cap32_words(g), "binary32 capsules")) != RGG_OK) return guard(st);
+        if (D == 2) {
+            float *cr;
+            if ((st = rm->upload(&cr, rad.data(), rad.size(), "binary32 capsule radii")) != RGG_OK) return guard(st);
+            dv.capr32 = cr;
+        }
         dv.samp32 = s32;
         dv.cap32 = c32;
     }

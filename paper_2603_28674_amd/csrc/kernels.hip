@@ -813,8 +813,6 @@ __device__ inline double band64_of(double s, double R, double L)
     return 1e-12 * ((s + R) * (R + L) + L * L);
 }
 
-__device__ inline float fabs_of(float x) { return fabsf(x); }
-__device__ inline double fabs_of(double x) { return fabs(x); }
 __device__ inline float max_of(float a, float b) { return fmaxf(a, b); }
 __device__ inline double max_of(double a, double b) { return fmax(a, b); }
 __device__ inline float min_of(float a, float b) { return fminf(a, b); }
@@ -828,6 +826,54 @@ template <int D>
 __device__ inline double point_box_of(const double *c, const double *lo, const double *hi)
 {
     return point_box64<D>(c, lo, hi);
+}
+
+// Capsule i of edge e: its ends, radius and the L1 length of its axis.  The
+// binary32 capsules are read as aligned 16-byte words, (A, R) and (B, L1) in
+// 3-D, (A, B) and the radius beside it in 2-D: two loads from one address
+// where the [2D + 1][B] rows of the binary64 ones took seven, each with an
+// address of its own, in a phase that is bound by instruction issue.
+template <int D>
+__device__ __forceinline__ void load_capsule(const RmDev &rm, int e, int i, float (&A)[D], float (&Bq)[D], float &R,
+                                             float &len)
+{
+    const int64_t k = (int64_t)e * rm.B + i;
+    const float4 *q = reinterpret_cast<const float4 *>(rm.cap32);
+    if constexpr (D == 3) {
+        const float4 a = q[2 * k], b = q[2 * k + 1];
+        A[0] = a.x;
+        A[1] = a.y;
+        A[2] = a.z;
+        R = a.w;
+        Bq[0] = b.x;
+        Bq[1] = b.y;
+        Bq[2] = b.z;
+        len = b.w;
+    } else {
+        const float4 a = q[k];
+        A[0] = a.x;
+        A[1] = a.y;
+        Bq[0] = a.z;
+        Bq[1] = a.w;
+        R = rm.capr32[k];
+        len = fabsf(a.z - a.x) + fabsf(a.w - a.y);
+    }
+}
+
+template <int D>
+__device__ __forceinline__ void load_capsule(const RmDev &rm, int e, int i, double (&A)[D], double (&Bq)[D], double &R,
+                                             double &len)
+{
+    const int B = rm.B;
+    const double *cp = rm.cap64 + (int64_t)e * (2 * D + 1) * B;
+    len = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        A[d] = cp[d * B + i];
+        Bq[d] = cp[(D + d) * B + i];
+        len += fabs(Bq[d] - A[d]);
+    }
+    R = cp[2 * D * B + i];
 }
 
 // The last of n rows whose first unit is at most c.
@@ -956,7 +1002,6 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
     const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
     const int B = rm.B;
     const int Gw = 64 / B;
-    const T *capb = kF32 ? (const T *)rm.cap32 : (const T *)rm.cap64;
     const T *samp = kF32 ? (const T *)rm.samp32 : (const T *)rm.samp64;
     const float band_rel = rm.band_rel;
     const int jfix = rm.p_fixed ? rm.p_fixed / B : 0;
@@ -984,22 +1029,15 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
     const int slot = s_lane[lane] >> 8, ci = s_lane[lane] & 255;
     const uint64_t gm = (B == 64 ? 0ull : 1ull << B) - 1ull;   // a pair's lanes, from lane slot * B on
     for (int p0 = 0; p0 < np; p0 += kWaves * Gw * kCapU) {
-        T A[kCapU][D], Bq[kCapU][D], R2[kCapU];
+        T A[kCapU][D], Bq[kCapU][D], R2[kCapU], L1[kCapU];
         int pu[kCapU];
 #pragma unroll
         for (int u = 0; u < kCapU; ++u) {
             pu[u] = p0 + (u * kWaves + wv) * Gw + slot;
             R2[u] = T(0);
-            if (slot < Gw && pu[u] < np) {
-                const int te = pe_slot(L.pe[pu[u]]);
-                const T *cp = capb + (int64_t)L.edge[te] * (2 * D + 1) * B;
-#pragma unroll
-                for (int k = 0; k < D; ++k) {
-                    A[u][k] = cp[k * B + ci];
-                    Bq[u][k] = cp[(D + k) * B + ci];
-                }
-                R2[u] = cp[2 * D * B + ci];
-            }
+            L1[u] = T(0);
+            if (slot < Gw && pu[u] < np)
+                load_capsule<D>(rm, L.edge[pe_slot(L.pe[pu[u]])], ci, A[u], Bq[u], R2[u], L1[u]);
         }
 #pragma unroll
         for (int u = 0; u < kCapU; ++u) {
@@ -1017,10 +1055,10 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
                 }
                 const float sc = fmaxf(L.es[pe_slot(L.pe[p])], L.blo[s].w);
                 const T R = R2[u], RR = R * R;
-                T len = T(0), sep = T(0);
+                const T len = L1[u];
+                T sep = T(0);
 #pragma unroll
                 for (int k = 0; k < D; ++k) {
-                    len += fabs_of(Bq[u][k] - A[u][k]);
                     sep = max_of(sep, max_of(lo[k] - max_of(A[u][k], Bq[u][k]), min_of(A[u][k], Bq[u][k]) - hi[k]));
                 }
                 T band, rband;
@@ -1081,23 +1119,17 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
             const uint32_t tk = L.u.open[q];
             const int p = (int)(tk >> 6), i = (int)(tk & 63u);
             const uint32_t pv = L.pe[p], te = pe_slot(pv), s = pe_entry(pv);
-            const T *cp = capb + (int64_t)L.edge[te] * (2 * D + 1) * B;
-            T A[D], Bq[D], lo[D], hi[D];
+            T A[D], Bq[D], lo[D], hi[D], R, len;
+            load_capsule<D>(rm, L.edge[te], i, A, Bq, R, len);
 #pragma unroll
             for (int k = 0; k < D; ++k) {
-                A[k] = cp[k * B + i];
-                Bq[k] = cp[(D + k) * B + i];
                 lo[k] = box_lo(k, s);
                 hi[k] = box_hi(k, s);
             }
-            const T R = cp[2 * D * B + i];
             const float sc = fmaxf(L.es[te], L.blo[s].w);
             int cls;
             float ts;
             if constexpr (kF32) {
-                float len = 0.0f;
-#pragma unroll
-                for (int k = 0; k < D; ++k) len += fabsf(Bq[k] - A[k]);
                 const float mg = segbox32<D>(A, Bq, lo, hi, ts) - R * R;
                 cls = classify_margin(mg, band_of(band_rel, sc, R, len));
                 if (cls == kUnsure) atomicOr(&L.um[p], 1ull << i);
@@ -1242,14 +1274,15 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
                 const uint32_t rv = L.u.rw.row[tid];
                 const int i = (int)(rv & 63u);
                 const uint32_t pv = L.pe[rv >> 6], te = pe_slot(pv), s = pe_entry(pv);
-                const T *cp = capb + (int64_t)L.edge[te] * (2 * D + 1) * B;
-                const float sc = fmaxf(L.es[te], L.blo[s].w), R = (float)cp[2 * D * B + i];
+                T A[D], Bq[D], R1, len;
+                load_capsule<D>(rm, L.edge[te], i, A, Bq, R1, len);
+                const float sc = fmaxf(L.es[te], L.blo[s].w), R = (float)R1;
                 const float W = R + 1e-5f * (sc + R);   // far beyond rounding of any coordinate
                 float t0 = 0.0f, t1 = 1.0f;
 #pragma unroll
                 for (int k = 0; k < D; ++k) {
-                    const float A = (float)cp[k * B + i], d = (float)(cp[(D + k) * B + i] - cp[k * B + i]);
-                    const float a = (float)box_lo(k, s) - W - A, b = (float)box_hi(k, s) + W - A;
+                    const float A0 = (float)A[k], d = (float)(Bq[k] - A[k]);
+                    const float a = (float)box_lo(k, s) - W - A0, b = (float)box_hi(k, s) + W - A0;
                     if (fabsf(d) > 1e-6f * (sc + R)) {   // else the axis stays inside what it is inside of
                         const float inv = __builtin_amdgcn_rcpf(d);
                         t0 = fmaxf(t0, fminf(a * inv, b * inv));

@@ -47,7 +47,8 @@ struct RmDev {
     const int64_t *soff;
     const float *samp32;
     const double *samp64;
-    const float *cap32;
+    const float *cap32;        // per edge and sphere, 16-byte words: (A, R), (B, L1) in 3-D, (A, B) in 2-D
+    const float *capr32;       // [E][B] capsule radii (2-D)
     const double *cap64;
     const float *aabb;
     const float *rad2_32;      // [B] r_i^2 rounded to binary32
@@ -156,7 +157,7 @@ constexpr int kMaxBatch = 256;     // requests per batched launch
 // allocates nothing.
 constexpr size_t kBatchTableBytes = (sizeof(BatchReq) * kMaxBatch + 255) / 256 * 256;
 constexpr size_t kBatchScratchBytes = kBatchTableBytes + sizeof(int32_t) * kMaxBatch;
-static_assert(kBatchScratchBytes <= 111 * 1024, "the documented size of the fixed request table");
+static_assert(kBatchScratchBytes <= 113 * 1024, "the documented size of the fixed request table");
 // Device address of that scratch on the current device (hipGetSymbolAddress).
 hipError_t batch_scratch_address(void **ptr);
 
