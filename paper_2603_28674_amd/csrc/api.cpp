@@ -62,6 +62,21 @@ int host_threads(int requested)
 
 constexpr int32_t kChunk = 256;   // edges per grid work item by default (one per thread)
 
+// The fixed items of a grid of several cells (RmDev::fixed); none when there
+// are more than kFixedItems.
+std::vector<int4> fixed_items(const HostGrid &grid, int32_t chunk)
+{
+    std::vector<int4> out;
+    const int64_t ncells = (int64_t)grid.dim[0] * grid.dim[1] * grid.dim[2];
+    if (ncells <= 1 || grid.items_cap - ncells > kFixedItems) return out;   // each cell counts one item or more
+    for (int64_t c = 0; c < ncells; ++c)
+        for (int32_t b = grid.start[(size_t)c], h = 0; b < grid.start[(size_t)c + 1]; b += chunk, ++h) {
+            if ((int)out.size() == kFixedItems) return {};
+            out.push_back(make_int4(b, std::min(chunk, grid.start[(size_t)c + 1] - b), (int32_t)c, h));
+        }
+    return out;
+}
+
 // Puts `grid` (built for work items of `chunk` edges) in place of the
 // roadmap's current grid, if any.  The new arrays are allocated first, so a
 // failure leaves the old grid in use.  The caller makes sure no queued work
@@ -74,13 +89,15 @@ rgg_status install_grid(rgg_roadmap *rm, const HostGrid &grid, int32_t chunk)
     int32_t *cstart = nullptr, *cedges = nullptr;
     uint32_t *bits = nullptr;
     int4 *items = nullptr;
-    int4 *cslot = nullptr;
+    int4 *cslot = nullptr, *fixed = nullptr;
+    const std::vector<int4> fix = fixed_items(grid, chunk);
     auto undo = [&](rgg_status s) {
         rm->release(cstart);
         rm->release(cedges);
         rm->release(bits);
         rm->release(items);
         rm->release(cslot);
+        rm->release(fixed);
         return s;
     };
     rgg_status st;
@@ -89,6 +106,7 @@ rgg_status install_grid(rgg_roadmap *rm, const HostGrid &grid, int32_t chunk)
     if ((st = rm->alloc(&bits, ncw, "cell marks")) != RGG_OK) return undo(st);
     // (one cell's items are chunks of the edges in order: no list)
     if (ncells > 1 && (st = rm->alloc(&items, (size_t)grid.items_cap, "grid items")) != RGG_OK) return undo(st);
+    if (!fix.empty() && (st = rm->upload(&fixed, fix.data(), fix.size(), "fixed items")) != RGG_OK) return undo(st);
     hipError_t e = hipMemset(bits, 0, 4 * std::max<size_t>(ncw, 1));
     if (e != hipSuccess) return undo(hip_fail(e, "clear marks"));
     if (ncells > 1 && !grid.edges.empty()) {
@@ -105,6 +123,9 @@ rgg_status install_grid(rgg_roadmap *rm, const HostGrid &grid, int32_t chunk)
     rm->release(dv.cell_bits);
     rm->release(dv.items);
     rm->release(dv.cell_slot);
+    rm->release(dv.fixed);
+    dv.fixed = fixed;
+    dv.n_fixed = ncells == 1 ? (int32_t)grid.items_cap : (int32_t)fix.size();
     dv.cell_start = cstart;
     dv.cell_edges = cedges;
     dv.cell_slot = cslot;
@@ -480,6 +501,7 @@ int64_t device_bytes_needed(const HostGeometry &g, const HostGrid &grid, const R
     if (ncells > 1 && !grid.edges.empty()) add(grid.edges.size(), sizeof(int4));
     add((size_t)((ncells + 31) / 32), 4);
     if (ncells > 1) add((size_t)grid.items_cap, sizeof(int4));
+    if (const size_t n = fixed_items(grid, p.chunk).size()) add(n, sizeof(int4));
     const int64_t ntiles = std::max<int64_t>(1, (E + kLabelTile - 1) / kLabelTile);
     add((size_t)E, sizeof(int2));
     add((size_t)M, sizeof(rgg_box));

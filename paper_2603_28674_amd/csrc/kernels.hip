@@ -414,9 +414,11 @@ __device__ __forceinline__ void activate_cells(const RmDev &rm, int n_chg)
 // one entry (the entry is a chain of binary64 roundings and cell indices,
 // which one wavefront runs at its latency); a chunk of the update covers
 // kDiffBlock / 2 slots, its old boxes' entries first.
+// n_fixed: the number of fixed items that the item kernel will visit, 0 when a
+// grid's cells have to be activated.
 template <int D>
 __device__ __forceinline__ void diff_body(const RmDev &rm, const rgg_box *__restrict__ old_b,
-                                          const rgg_box *__restrict__ new_b)
+                                          const rgg_box *__restrict__ new_b, int32_t n_fixed)
 {
     constexpr int kHalf = kDiffBlock / 2;
     __shared__ int s_tot[kDiffBlock / 64];
@@ -471,9 +473,9 @@ __device__ __forceinline__ void diff_body(const RmDev &rm, const rgg_box *__rest
     if (tid == 0) {
         rm.ctl->status = status;
         rm.ctl->n_chg = status ? 0 : s_base;
-        // one grid cell: its items (0, h) are fixed at build; they are all
-        // work as soon as one changed box lies inside the grid
-        if (rm.ncells == 1) rm.ctl->n_items = (status == RGG_OK && s_any) ? (int32_t)rm.items_cap : 0;
+        // fixed items are all looked at as soon as one changed box lies
+        // inside the grid
+        if (n_fixed) rm.ctl->n_items = (status == RGG_OK && s_any) ? n_fixed : 0;
     }
     if (status == RGG_OK) {
         if (dirty0) rm.resident[j] = n0;
@@ -482,7 +484,7 @@ __device__ __forceinline__ void diff_body(const RmDev &rm, const rgg_box *__rest
             if (!same_box(n, rm.resident[k])) rm.resident[k] = n;
         }
         // the entries written above are read back by this block's threads
-        if (rm.ncells > 1) {
+        if (!n_fixed) {
             __syncthreads();
             activate_cells(rm, s_base);
         }
@@ -493,7 +495,7 @@ template <int D>
 __global__ void __launch_bounds__(kDiffBlock) k_diff(RmDev rm, const rgg_box *__restrict__ old_b,
                                                      const rgg_box *__restrict__ new_b)
 {
-    diff_body<D>(rm, old_b, new_b);
+    diff_body<D>(rm, old_b, new_b, rm.n_fixed);
 }
 
 // ------------------------------------------------------------------------
@@ -596,28 +598,33 @@ __device__ bool copies_meet64(const RmDev &rm, const double *sb, const CopyMap &
     if (lane < rm.B && ((m >> lane) & 1ull)) lst[__popcll(m & lanes_below())] = lane;
     wave_sync();
     const int nsph = __popcll(m);
-    for (int sp0 = 0; sp0 < nsph; sp0 += cm.spc) {
-        for (int j0 = 0; j0 < cm.J; j0 += cm.jw) {
-            const int js = j0 + cm.jj;
-            const bool valid = cm.sub < cm.spc && sp0 + cm.sub < nsph && js < cm.J;
-            bool hit = false;
-            if (valid) {
-                const int i = lst[sp0 + cm.sub];
-                double p[D];
+    // (spheres, configurations) in wavefront-sized pieces, two in flight
+    const int nj = (cm.J + cm.jw - 1) / cm.jw, n = ((nsph + cm.spc - 1) / cm.spc) * nj;
+    bool met = false;
+    for (int k0 = 0; k0 < n && !met; k0 += 2) {
+        double p[2][D], r[2];
+        bool valid[2];
 #pragma unroll
-                for (int k = 0; k < D; ++k) p[k] = sb[((int64_t)i * cm.J + js) * copy_stride<D>() + k];
-                const double r = rad[i];
-                hit = point_box64<D>(p, lo, hi) <= r * r;
+        for (int u = 0; u < 2; ++u) {
+            const int sp = ((k0 + u) / nj) * cm.spc + cm.sub, js = ((k0 + u) % nj) * cm.jw + cm.jj;
+            valid[u] = k0 + u < n && cm.sub < cm.spc && sp < nsph && js < cm.J;
+            r[u] = 0.0;
+            if (valid[u]) {
+                const int i = lst[sp];
+#pragma unroll
+                for (int k = 0; k < D; ++k) p[u][k] = sb[((int64_t)i * cm.J + js) * copy_stride<D>() + k];
+                r[u] = rad[i];
             }
-            *bytes += (unsigned long long)(__popcll(__ballot(valid)) * D * 8);
-            if (__ballot(hit)) {
-                wave_sync();
-                return true;
-            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool hit = valid[u] && point_box64<D>(p[u], lo, hi) <= r[u] * r[u];
+            *bytes += (unsigned long long)(__popcll(__ballot(valid[u])) * D * 8);
+            met = met || __ballot(hit);
         }
     }
     wave_sync();
-    return false;
+    return met;
 }
 
 // some kept spline segment of a sphere in m meets the box (binary64, one
@@ -706,7 +713,7 @@ static_assert(2 * 3 * slabs_of(3) <= kLocalCells && 2 * 2 * slabs_of(2) <= kLoca
                   slabs_of(3) <= 128,
               "the slab masks fit their storage and one wavefront's scan (two slabs a lane)");
 static_assert(kOpenCap >= 3 * kRowCap + 1, "the rows fit the capsule queue's storage");
-static_assert(kOpenCap * 4 >= kWaves * 64 * 4 + 64 * 8, "the re-test's scratch fits the queue's storage");
+static_assert(kOpenCap >= kWaves * 64, "the re-test's scratch fits the queue's storage");
 
 __device__ inline int pe_slot(uint32_t v) { return (int)(v >> 16); }
 __device__ inline int pe_entry(uint32_t v) { return (int)(v & 0xFFFFu); }
@@ -904,10 +911,7 @@ __device__ __forceinline__ void retest_queued(const RmDev &rm, Lds &L, const int
     const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
     const int B = rm.B, Gw = 64 / B;
     int *lst = reinterpret_cast<int *>(&L.u) + wv * 64;
-    double *rad = reinterpret_cast<double *>(reinterpret_cast<int *>(&L.u) + kWaves * 64);
-    if (tid < B) rad[tid] = rm.rad64[tid];
     const int n = L.r64.n;
-    __syncthreads();
     unsigned long long bytes = 0;
     const uint64_t gm = (B == 64 ? 0ull : 1ull << B) - 1ull;
     const int per = min(Gw, (n + kWaves - 1) / kWaves);
@@ -967,7 +971,7 @@ __device__ __forceinline__ void retest_queued(const RmDev &rm, Lds &L, const int
                 const int64_t s0 = rm.p_fixed ? e * rm.p_fixed : rm.soff[e];
                 const int64_t P = rm.p_fixed ? rm.p_fixed : rm.soff[e + 1] - s0;
                 const CopyMap cm = copy_map((int)(P / B));
-                S = copies_meet64<D>(rm, rm.samp64 + copy_stride<D>() * s0, cm, hm, lo, hi, rad, lst, &bytes);
+                S = copies_meet64<D>(rm, rm.samp64 + copy_stride<D>() * s0, cm, hm, lo, hi, rm.rad64, lst, &bytes);
             }
             if (lane == 0) {
                 ++n_outer;
@@ -993,7 +997,7 @@ __device__ __forceinline__ void retest_queued(const RmDev &rm, Lds &L, const int
 // for a round (the caller re-tests them).
 template <int D, typename T, int MODE, bool kShare, typename Lds>
 __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_rad2, const int *s_lane, int np,
-                                           uint32_t &n_pairs, uint32_t &n_outer, unsigned long long &bytes)
+                                           uint32_t &n_pairs, uint32_t &n_outer, uint32_t &bytes)
 {
     constexpr bool kF32 = std::is_same<T, float>::value;
     constexpr bool kObb = (MODE & kModeObb) != 0;
@@ -1510,12 +1514,17 @@ __device__ inline Prefetched fetch_entry(const ChgEntry &en)
 
 // Items li0, li0 + lstride, ... of the roadmap (statistics row blockIdx.x).
 //
+// The items are rm.fixed (fixed) or those that this update's cell activation
+// emitted.  An item of the fixed list may lie in a cell that no changed box
+// covers; it ends after its staging and counts for nothing.
+//
 // kList: the pair listing of the FP32 mode.  Each round of pairs goes to this
 // block's region of the pair list (rm.pl, for the pair-share kernel) while
 // the region has room; a round that does not fit is tested here, as the
 // fused kernel does.
-template <int D, typename T, int MODE, bool kList = false>
-__device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
+// kOne: item li0 alone, of an update that the caller knows to be valid.
+template <int D, typename T, int MODE, bool kList = false, bool kOne = false>
+__device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride, bool fixed)
 {
     constexpr bool kF32 = std::is_same<T, float>::value;
     static_assert(!kList || kF32, "the pair listing serves the FP32 mode");
@@ -1539,13 +1548,14 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
         L.pl_n = 0;
     }
     const bool single = rm.ncells == 1;
-    const int4 item0 = !single && li0 < (int)rm.items_cap ? rm.items[li0] : make_int4(0, 0, 0, 0);
-    const int status = ctl->status;
+    const int4 *const items = fixed ? rm.fixed : rm.items;
+    const int cap = kOne ? li0 + 1 : (single || fixed ? rm.n_fixed : (int)rm.items_cap);
+    const int4 item0 = !single && li0 < cap ? items[li0] : make_int4(0, 0, 0, 0);
+    const int status = kOne ? RGG_OK : ctl->status;
     // wavefront-uniform counts (kept in scalar registers) and per-lane ones
-    uint32_t n_pairs = 0, visited = 0, cand = 0, n_outer = 0;
-    unsigned long long bytes = 0;
+    uint32_t n_pairs = 0, visited = 0, cand = 0, n_outer = 0, bytes = 0;
     const int n_chg = ctl->n_chg;
-    const int n_items = min(ctl->n_items, (int32_t)rm.items_cap);
+    const int n_items = kOne ? cap : min(ctl->n_items, cap);
     const float4 *aabb = reinterpret_cast<const float4 *>(rm.aabb);
     const int jfix = rm.p_fixed ? rm.p_fixed / B : 0;
     constexpr int kSl = slabs_of(D);   // slabs per axis of the slab masks
@@ -1556,7 +1566,7 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
     uint32_t had = 0;   // bit h: edge slot h of the item has pairs
     while (full) {
         full = false;
-        for (; it < (int)rm.items_cap && !full; it += full ? 0 : lstride) {
+        for (; it < cap && !full; it += full ? 0 : lstride) {
             const bool anew = tile0 == 0 && round0 == 0;
             // with one cell the items are chunks of the edges in order; else
             // slots of the cell lists.  What an item needs first is requested
@@ -1566,8 +1576,9 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
             // (the item, the slots, the boxes) with several.
             int4 item = item0;
             if (single) item = make_int4(it * rm.chunk, (int)min((int64_t)rm.chunk, rm.E - (int64_t)it * rm.chunk), 0, 0);
-            else if (it != li0) item = rm.items[it];
-            if (!single && (status != RGG_OK || it >= n_items)) break;
+            else if (it != li0) item = items[it];
+            // (an emitted item is not looked at before it is known to be one)
+            if (!single && !fixed && (status != RGG_OK || it >= n_items)) break;
             const int beg = item.x, n_e = item.y;   // edge slots in use: tid, tid + kBlock
             int e[kSlots], J[kSlots];
             float4 bl[kSlots], bh[kSlots];          // the edges' boxes: (lo, s), (hi, pad)
@@ -1604,7 +1615,6 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
             if (tid < kSubTile && tid < 2 * rm.M) pf = fetch_entry(rm.chg[tid]);
             // this block's place in the work, now that its loads are out
             if (status != RGG_OK || it >= n_items) break;
-            if (anew) bytes += (tid < n_e ? 32 : 0) + (tid + kBlock < n_e ? 32 : 0);
             const int c = item.z;
             const int cx = c % rm.gdim[0], cy = c / rm.gdim[0] % rm.gdim[1], cz = c / (rm.gdim[0] * rm.gdim[1]);
             __syncthreads();   // the previous item is done with the LDS arrays
@@ -1618,15 +1628,19 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
                 L.dC[sl] = 0;
                 L.dS[sl] = 0;
             }
-            if (wv == 0 && anew) visited += (uint32_t)n_e;
             if (tid == 0) {
-                // every item is visited once: clear the cell's mark with its
-                // first chunk, so the next update starts from zero marks
-                if (!single && item.w == 0) atomicAnd(&rm.cell_bits[c >> 5], ~(1u << (c & 31)));
+                // every emitted item is visited once: clear the cell's mark
+                // with its first chunk, so the next update starts from zero marks
+                if (!single && !fixed && item.w == 0) atomicAnd(&rm.cell_bits[c >> 5], ~(1u << (c & 31)));
             }
             if (anew) had = 0;
             bool fused = !kList;   // some round of this item was tested here
             int n_round = 0;       // this item's pair rounds so far
+            bool covered = kOne;   // some changed entry covers the item's cell
+            if (kOne && anew) {
+                if (wv == 0) visited += (uint32_t)n_e;
+                bytes += (tid < n_e ? 32 : 0) + (tid + kBlock < n_e ? 32 : 0);
+            }
             for (int j0 = tile0; j0 < n_chg && !full; j0 += kSubTile) {
                 // stage the entries covering this cell (with one cell: all)
                 const int j = j0 + tid;
@@ -1653,6 +1667,13 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
                 }
                 pf = Prefetched{};   // not kept through the rounds
                 if (nt == 0) continue;   // uniform: nt is the block total
+                if constexpr (!kOne) {
+                    if (anew && !covered) {
+                        if (wv == 0) visited += (uint32_t)n_e;
+                        bytes += (tid < n_e ? 32 : 0) + (tid + kBlock < n_e ? 32 : 0);
+                    }
+                    covered = true;
+                }
                 const int nw = (nt + 31) >> 5;
                 // block-local slab masks, from kSlabMin entries on (below that
                 // testing every entry costs less than the masks)
@@ -1791,8 +1812,9 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
                 }
             }
             if (!full) tile0 = round0 = 0;
+            if (!covered) continue;
             if (!full) cand += (uint32_t)(__popcll(__ballot(had & 1u)) + __popcll(__ballot(had & 2u)));
-            if (fused && !full) bytes += (unsigned long long)__popc(had) * ((2 * D + 1) * B * sizeof(T) + 16);
+            if (fused && !full) bytes += (uint32_t)__popc(had) * ((2 * D + 1) * B * sizeof(T) + 16);
             __syncthreads();
 #pragma unroll
             for (int h = 0; h < kSlots; ++h) {
@@ -1830,13 +1852,13 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride)
 template <int D, int MODE>
 __global__ void __launch_bounds__(kBlock, 4) k_item32(RmDev rm)
 {
-    item_body<D, float, MODE, true>(rm, (int)blockIdx.x, (int)gridDim.x);
+    item_body<D, float, MODE, true>(rm, (int)blockIdx.x, (int)gridDim.x, rm.n_fixed > 0);
 }
 
 template <int D, int MODE>
 __global__ void __launch_bounds__(kBlock) k_item64(RmDev rm)
 {
-    item_body<D, double, MODE>(rm, (int)blockIdx.x, (int)gridDim.x);
+    item_body<D, double, MODE>(rm, (int)blockIdx.x, (int)gridDim.x, rm.n_fixed > 0);
 }
 
 // ------------------------------------------------------------------------
@@ -1921,8 +1943,7 @@ __device__ __forceinline__ void share_body(const RmDev &rm)
     const int64_t hi = b < G ? (int64_t)total * (b + 1) / G : 0;
     const float4 *aabb = reinterpret_cast<const float4 *>(rm.aabb);
     const int jfix = rm.p_fixed ? rm.p_fixed / B : 0;
-    uint32_t n_pairs = 0, n_outer = 0;
-    unsigned long long bytes = 0;
+    uint32_t n_pairs = 0, n_outer = 0, bytes = 0;
     for (int64_t r0 = lo; r0 < hi; r0 += kPairCap) {
         const int np = (int)min((int64_t)kPairCap, hi - r0);
         if (tid < np) {
@@ -1959,7 +1980,7 @@ __device__ __forceinline__ void share_body(const RmDev &rm)
         }
         __syncthreads();
         if (tid < np && (tid == 0 || L.edge[tid] != L.edge[tid - 1]))
-            bytes += (unsigned long long)((2 * D + 1) * B * sizeof(float) + (jfix ? 0 : 16));
+            bytes += (uint32_t)((2 * D + 1) * B * sizeof(float) + (jfix ? 0 : 16));
         test_round<D, float, MODE, true>(rm, L, s_rad2, s_lane, np, n_pairs, n_outer, bytes);
         if (L.r64.n) retest_queued<D, MODE>(rm, L, s_lane, n_outer);
     }
@@ -2313,8 +2334,10 @@ __global__ void __launch_bounds__(kDiffBlock) k_diff_batch(BatchReq *tab, const 
     } else {
         load_row(&q, tab[blockIdx.x]);
     }
-    if (q.rm.D == 3) diff_body<3>(q.rm, q.a.old_b, q.a.new_b);
-    else diff_body<2>(q.rm, q.a.old_b, q.a.new_b);
+    // a grid's cells are activated here: a batch has many items to choose from
+    const int32_t fixed = q.rm.ncells == 1 ? q.rm.n_fixed : 0;
+    if (q.rm.D == 3) diff_body<3>(q.rm, q.a.old_b, q.a.new_b, fixed);
+    else diff_body<2>(q.rm, q.a.old_b, q.a.new_b, fixed);
 }
 
 // The items of all requests of one group form one range: request r owns
@@ -2361,7 +2384,7 @@ __device__ __forceinline__ void item_batch_body(const BatchReq *tab, const int32
             load_rm(&s_rm, tab[grp[lo]].rm);
             cur = lo;
         }
-        item_body<D, T, 0>(s_rm, g - s_pref[lo], 1 << 30);
+        item_body<D, T, 0, false, true>(s_rm, g - s_pref[lo], 1, false);
         if (claims && tid == 0) s_next = nxt;
         __syncthreads();
         g = claims ? s_next : g + G;
@@ -2516,31 +2539,26 @@ struct Node {
 // kernel, ev[4] after the pair testing, ev[5] after the binary64 re-test (part
 // of the two before it: no time), ev[6] after the labels.  The FP64 mode's one
 // item kernel stands for the testing (ev[3] before it).
-// Blocks of the item kernel for a one-cell roadmap: one per item, at most
-// kGrid.
-unsigned fixed_items_grid(const RmDev &rm)
-{
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(kGrid, rm.items_cap));
-}
+// Blocks of the item kernel for fixed items: one per item, at most kGrid.
+unsigned fixed_items_grid(const RmDev &rm) { return (unsigned)std::max(1, std::min(kGrid, rm.n_fixed)); }
 
 int plan(const RmDev &rm, Node out[7])
 {
     int n = 0;
-    const bool single = rm.ncells == 1;
+    const bool fixed = rm.n_fixed > 0;
     void *const diff_fn = rm.D == 3 ? (void *)k_diff<3> : (void *)k_diff<2>;
     if (rm.mixed) {
         out[n++] = {diff_fn, dim3(1), 0, 1, 2};
         // with every round tested inline there is nothing to share out
         const bool share = rm.inline_rounds != kInlineAll;
-        // one grid cell: its items are fixed, and blocks past them would only
-        // start and stop (with pair listing every block writes its list's
-        // count, so the whole grid runs)
-        const unsigned grid = single && !share ? fixed_items_grid(rm) : kGrid;
+        // blocks past the fixed items would only start and stop (with pair
+        // listing every block writes its list's count, so the whole grid runs)
+        const unsigned grid = fixed && !share ? fixed_items_grid(rm) : kGrid;
         out[n++] = {fn(rm, 0), dim3(grid), 1, 3, share ? 3 : 5};
         if (share) out[n++] = {fn(rm, 1), dim3(kGrid), 1, 4, 5};
     } else {
         out[n++] = {diff_fn, dim3(1), 0, 1, 3};
-        out[n++] = {fn(rm, 2), dim3(single ? fixed_items_grid(rm) : kGrid), 1, 4, 5};
+        out[n++] = {fn(rm, 2), dim3(fixed ? fixed_items_grid(rm) : kGrid), 1, 4, 5};
     }
     out[n++] = {(void *)k_labels, dim3(rm.ntiles + 1), 4, 6, 6};
     return n;

@@ -78,6 +78,13 @@ struct RmDev {
     // gather through the edge id
     const int4 *cell_slot;
     int64_t items_cap;
+    // Fixed items, all visited by every update: with one cell the chunks of
+    // the edges (no list), with several the chunks of every cell's list in the
+    // order of the cells, as long as the device holds their blocks at once.
+    // n_fixed = 0: an update activates the cells it covers and emits their
+    // items (which a batch does with any grid).
+    const int4 *fixed;
+    int32_t n_fixed, pad3;
     // block-local slab masks (binary32): slab of x on axis d is
     // clamp(floor((x - sl_org[d]) * sl_inv[d]), 0, slabs_of(D) - 1)
     float sl_org[3];
@@ -89,8 +96,8 @@ struct RmDev {
     uint32_t *cell_bits;       // [ceil(ncells/32)] touched cells, zero between updates
     rgg_box *resident;         // [M] obstacle slots
     ChgEntry *chg;             // [2M]
-    int4 *items;               // [items_cap] (first slot of the cell lists, slots, cell, chunk);
-                               // not used with one cell, whose items are chunks of the edges
+    int4 *items;               // [items_cap] (first slot of the cell lists, slots, cell, chunk) of
+                               // the activated cells (grids)
     int32_t rc_cap;            // FP32 mode: undecided pairs a block collects before it
                                // re-tests them (1..kRcCap)
     // the FP32 mode's pair listing and pair testing
@@ -119,6 +126,9 @@ constexpr int kStatPairBytes = 3, kStatItemBytes = 6, kStatFp64Bytes = 7;
 constexpr int kStatBlocks = 2048;  // blocks of the item kernels at most
 constexpr int kStatRows = 256;     // rows of blk_stats in use: item and pair-share blocks add
                                    // to row blockIdx & 255 (atomics)
+constexpr int kFixedItems = 1024;  // fixed items of a grid at most: the blocks resident at once. An
+                                   // uncovered item ends in 3 us beside the covered ones; the
+                                   // activation it spares takes 4 to 6 us of the diff kernel
 constexpr int kMaxSlots = 4096;    // 2*slots changed entries at most
 
 constexpr int kLocalCells = 512;   // uint4 words of the item kernel's slab masks (at most)
@@ -157,7 +167,7 @@ constexpr int kMaxBatch = 256;     // requests per batched launch
 // allocates nothing.
 constexpr size_t kBatchTableBytes = (sizeof(BatchReq) * kMaxBatch + 255) / 256 * 256;
 constexpr size_t kBatchScratchBytes = kBatchTableBytes + sizeof(int32_t) * kMaxBatch;
-static_assert(kBatchScratchBytes <= 113 * 1024, "the documented size of the fixed request table");
+static_assert(kBatchScratchBytes <= 117 * 1024, "the documented size of the fixed request table");
 // Device address of that scratch on the current device (hipGetSymbolAddress).
 hipError_t batch_scratch_address(void **ptr);
 
