@@ -504,6 +504,7 @@ __global__ void __launch_bounds__(kDiffBlock) k_diff(RmDev rm, const rgg_box *__
 
 // exclusive prefix of v over the block; *total receives the block sum.
 // Contains barriers: every thread must call it.
+template <int kNW = kWaves>
 __device__ inline int block_scan(int v, int *total, int *wsum)
 {
     const int lane = lane_id(), wv = threadIdx.x >> 6;
@@ -513,7 +514,7 @@ __device__ inline int block_scan(int v, int *total, int *wsum)
     if (lane == 0) wsum[wv] = wt;
     __syncthreads();
     int off = 0, tot = 0;
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < kNW; ++w) {
         off += w < wv ? wsum[w] : 0;
         tot += wsum[w];
     }
@@ -2030,23 +2031,25 @@ __device__ inline int block_sum(int v, int *s_w)
     return t;
 }
 
-// Each thread of a label block owns kLabelRun consecutive edges of the tile.
+// Each thread of a label block owns R consecutive edges of the tile: 16 in a
+// block of 256 threads, 4 in one of 1,024.
 constexpr int kLabelRun = kLabelTile / kBlock;
-static_assert(kLabelRun == 16, "a run is stored as one 16-byte label word");
+constexpr int kWideRun = 4;
 
-__device__ inline void load_run(const RmDev &rm, int64_t e0, int2 (&c)[kLabelRun])
+template <int R>
+__device__ inline void load_run(const RmDev &rm, int64_t e0, int2 (&c)[R])
 {
-    if (e0 + kLabelRun <= rm.E) {
-        const int4 *src = reinterpret_cast<const int4 *>(rm.cnt + e0);   // 16-byte aligned: e0 % 16 == 0
+    if (e0 + R <= rm.E) {
+        const int4 *src = reinterpret_cast<const int4 *>(rm.cnt + e0);   // 16-byte aligned: e0 % R == 0
 #pragma unroll
-        for (int h = 0; h < kLabelRun / 2; ++h) {
+        for (int h = 0; h < R / 2; ++h) {
             const int4 v = src[h];
             c[2 * h] = make_int2(v.x, v.y);
             c[2 * h + 1] = make_int2(v.z, v.w);
         }
     } else {
 #pragma unroll
-        for (int h = 0; h < kLabelRun; ++h) c[h] = e0 + h < rm.E ? rm.cnt[e0 + h] : make_int2(0, 0);
+        for (int h = 0; h < R; ++h) c[h] = e0 + h < rm.E ? rm.cnt[e0 + h] : make_int2(0, 0);
     }
 }
 
@@ -2072,16 +2075,18 @@ __device__ __forceinline__ void fold_stats(const RmDev &rm, rgg_update_result *r
     __shared__ unsigned long long s_part[kWaves][kStats];
     const int tid = threadIdx.x;
     static_assert(kStatRows == kBlock, "one statistics row a thread");
+    const bool on = tid < kStatRows;
     unsigned long long v[kStats];
 #pragma unroll
-    for (int k = 0; k < kStats; ++k) v[k] = rm.blk_stats[k * kStatBlocks + tid];
+    for (int k = 0; k < kStats; ++k) v[k] = on ? rm.blk_stats[k * kStatBlocks + tid] : 0ull;
 #pragma unroll
-    for (int k = 0; k < kStats; ++k) rm.blk_stats[k * kStatBlocks + tid] = 0ull;
+    for (int k = 0; k < kStats; ++k)
+        if (on) rm.blk_stats[k * kStatBlocks + tid] = 0ull;
     const int lane = lane_id(), wv = tid >> 6;
 #pragma unroll
     for (int k = 0; k < kStats; ++k) {
         const unsigned long long w = wave_sum_u64(v[k]);
-        if (lane == 0) s_part[wv][k] = w;
+        if (on && lane == 0) s_part[wv][k] = w;
     }
     __syncthreads();
     if (tid == 0 && res) {
@@ -2102,15 +2107,16 @@ __device__ __forceinline__ void fold_stats(const RmDev &rm, rgg_update_result *r
     }
 }
 
-// Labels of this thread's run of edges e0 .. e0 + kLabelRun - 1; returns
+// Labels of this thread's run of edges e0 .. e0 + R - 1; returns
 // how many are GRAY.
-__device__ __forceinline__ int run_labels(const RmDev &rm, int64_t e0, uint8_t (&lab)[kLabelRun])
+template <int R>
+__device__ __forceinline__ int run_labels(const RmDev &rm, int64_t e0, uint8_t (&lab)[R])
 {
-    int2 c[kLabelRun];
+    int2 c[R];
     load_run(rm, e0, c);
     int ng = 0;
 #pragma unroll
-    for (int h = 0; h < kLabelRun; ++h) {
+    for (int h = 0; h < R; ++h) {
         lab[h] = label_of(c[h]);
         ng += (e0 + h < rm.E && lab[h] == RGG_GRAY) ? 1 : 0;
     }
@@ -2118,19 +2124,22 @@ __device__ __forceinline__ int run_labels(const RmDev &rm, int64_t e0, uint8_t (
 }
 
 // Stores a run's labels (when labels is not null).
-__device__ __forceinline__ void store_run(const RmDev &rm, uint8_t *labels, int64_t e0, const uint8_t (&lab)[kLabelRun])
+template <int R>
+__device__ __forceinline__ void store_run(const RmDev &rm, uint8_t *labels, int64_t e0, const uint8_t (&lab)[R])
 {
     if (!labels) return;
-    if (e0 + kLabelRun <= rm.E && ((uintptr_t)(labels + e0) & 15u) == 0) {
-        uint32_t wds[kLabelRun / 4];
+    static_assert(R == 16 || R == 4, "a run is stored as one label word");
+    if (e0 + R <= rm.E && ((uintptr_t)(labels + e0) & (R - 1u)) == 0) {
+        uint32_t wds[R / 4];
 #pragma unroll
-        for (int q = 0; q < kLabelRun / 4; ++q)
+        for (int q = 0; q < R / 4; ++q)
             wds[q] = (uint32_t)lab[4 * q] | ((uint32_t)lab[4 * q + 1] << 8) | ((uint32_t)lab[4 * q + 2] << 16) |
                      ((uint32_t)lab[4 * q + 3] << 24);
-        *reinterpret_cast<uint4 *>(labels + e0) = make_uint4(wds[0], wds[1], wds[2], wds[3]);
+        if constexpr (R == 16) *reinterpret_cast<uint4 *>(labels + e0) = make_uint4(wds[0], wds[1], wds[2], wds[3]);
+        else *reinterpret_cast<uint32_t *>(labels + e0) = wds[0];
     } else {
 #pragma unroll
-        for (int h = 0; h < kLabelRun; ++h)
+        for (int h = 0; h < R; ++h)
             if (e0 + h < rm.E) labels[e0 + h] = lab[h];
     }
 }
@@ -2141,19 +2150,20 @@ __device__ __forceinline__ void store_run(const RmDev &rm, uint8_t *labels, int6
 // ..., then consecutive threads write consecutive positions, so the 8-byte
 // stores coalesce instead of each thread's landing a few positions apart.
 // Every thread of the block calls it (one barrier).
+template <int R>
 __device__ __forceinline__ void store_gray(const RmDev &rm, int64_t *gray, int64_t cap, int64_t e0,
-                                           const uint8_t (&lab)[kLabelRun], int64_t before, int pre, int tot)
+                                           const uint8_t (&lab)[R], int64_t before, int pre, int tot)
 {
     __shared__ uint16_t s_gid[kLabelTile];   // tile-local edge index of each GRAY id
     static_assert(kLabelTile <= 65536, "a tile-local index fits 16 bits");
     if (!gray) return;
-    const int64_t t0 = e0 - (int64_t)threadIdx.x * kLabelRun;   // the tile's first edge
+    const int64_t t0 = e0 - (int64_t)threadIdx.x * R;   // the tile's first edge
     int p = pre;
 #pragma unroll
-    for (int h = 0; h < kLabelRun; ++h)
-        if (e0 + h < rm.E && lab[h] == RGG_GRAY) s_gid[p++] = (uint16_t)(threadIdx.x * kLabelRun + h);
+    for (int h = 0; h < R; ++h)
+        if (e0 + h < rm.E && lab[h] == RGG_GRAY) s_gid[p++] = (uint16_t)(threadIdx.x * R + h);
     __syncthreads();
-    for (int i = threadIdx.x; i < tot; i += kBlock) {
+    for (int i = threadIdx.x; i < tot; i += kLabelTile / R) {
         const int64_t pos = before + i;
         if (pos < cap) gray[pos] = t0 + s_gid[i];
     }
@@ -2208,10 +2218,12 @@ __device__ __forceinline__ void write_body(const RmDev &rm, uint8_t *labels, int
 constexpr unsigned long long kTileAgg = 1ull << 62, kTilePre = 2ull << 62, kTileVal = (1ull << 62) - 1;
 constexpr int kLookBackSpins = 1 << 20;
 
+template <int R>
 __device__ __forceinline__ void labels_body(const RmDev &rm, uint8_t *labels, int64_t *gray, int64_t cap,
                                            rgg_update_result *res)
 {
-    __shared__ int s_w[kWaves];
+    constexpr int kThreads = kLabelTile / R;
+    __shared__ int s_w[kThreads / 64];
     __shared__ int s_tile, s_fail;
     __shared__ long long s_before;
     const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
@@ -2231,11 +2243,11 @@ __device__ __forceinline__ void labels_body(const RmDev &rm, uint8_t *labels, in
         if (status != RGG_OK) res->n_gray = 0;
     }
     if (status != RGG_OK) return;   // every block returns here: no one waits
-    const int64_t e0 = (int64_t)tile * kLabelTile + (int64_t)tid * kLabelRun;
-    uint8_t lab[kLabelRun];
+    const int64_t e0 = (int64_t)tile * kLabelTile + (int64_t)tid * R;
+    uint8_t lab[R];
     const int ng = run_labels(rm, e0, lab);
     int tot;
-    const int pre = block_scan(ng, &tot, s_w);
+    const int pre = block_scan<kThreads / 64>(ng, &tot, s_w);
     unsigned long long *st = rm.tile_state;
     if (tid == 0)
         __hip_atomic_store(&st[tile], (tile == 0 ? kTilePre : kTileAgg) | (unsigned long long)tot, __ATOMIC_RELEASE,
@@ -2282,10 +2294,11 @@ __device__ __forceinline__ void labels_body(const RmDev &rm, uint8_t *labels, in
     store_gray(rm, gray, cap, e0, lab, before, pre, tot);
 }
 
-__global__ void __launch_bounds__(kBlock) k_labels(RmDev rm, uint8_t *labels, int64_t *gray, int64_t cap,
-                                                   rgg_update_result *res, int)
+template <int R>
+__global__ void __launch_bounds__(kLabelTile / R) k_labels(RmDev rm, uint8_t *labels, int64_t *gray, int64_t cap,
+                                                           rgg_update_result *res, int)
 {
-    labels_body(rm, labels, gray, cap, res);
+    labels_body<R>(rm, labels, gray, cap, res);
 }
 
 __global__ void __launch_bounds__(kBlock) k_count(RmDev rm)
@@ -2527,10 +2540,16 @@ void *fn_dim(int mode, int k)
 void *fn(const RmDev &rm, int k) { return rm.D == 3 ? fn_dim<3>(rm.mode, k) : fn_dim<2>(rm.mode, k); }
 
 
+// Label tiles from which k_labels runs in blocks of 1,024 threads: the loads of
+// a tile's counters then come 2 KB in a row per wavefront instead of 128 bytes
+// apart per lane.  290k edges (71 tiles): 64.4 -> 63.3 us an update; below, the
+// larger block's barriers cost what that gains (3 tiles: 27.3 against 27.7).
+constexpr int kWideTiles = 16;
+
 struct Node {
     void *fn;
     dim3 grid;
-    int kind;      // argument list: 0 diff, 1 (rm) only, 4 write
+    int kind;      // argument list: 0 diff, 1 (rm) only, 4 labels (5: in wide blocks)
     int ev0, ev1;  // stage events ev[ev0..ev1] are recorded after the node
 };
 
@@ -2560,7 +2579,8 @@ int plan(const RmDev &rm, Node out[7])
         out[n++] = {diff_fn, dim3(1), 0, 1, 3};
         out[n++] = {fn(rm, 2), dim3(fixed ? fixed_items_grid(rm) : kGrid), 1, 4, 5};
     }
-    out[n++] = {(void *)k_labels, dim3(rm.ntiles + 1), 4, 6, 6};
+    const bool wide = rm.ntiles >= kWideTiles;
+    out[n++] = {wide ? (void *)k_labels<kWideRun> : (void *)k_labels<kLabelRun>, dim3(rm.ntiles + 1), wide ? 5 : 4, 6, 6};
     return n;
 }
 
@@ -2583,9 +2603,12 @@ struct Args {
     Args(const Args &) = delete;
     void **of(int kind)
     {
-        return kind == 0 ? diff : (kind == 4 ? write : one);
+        return kind == 0 ? diff : (kind >= 4 ? write : one);
     }
-    dim3 block(int kind) const { return dim3(kind == 0 ? kDiffBlock : kBlock); }
+    dim3 block(int kind) const
+    {
+        return dim3(kind == 0 ? kDiffBlock : (kind == 5 ? kLabelTile / kWideRun : kBlock));
+    }
 };
 
 }  // namespace
