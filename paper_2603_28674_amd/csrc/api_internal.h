@@ -55,6 +55,8 @@ struct rgg_roadmap {
     rgg_box *h_stage = nullptr;       // pinned [2M]
     rgg_box *d_stage = nullptr;       // [2M]
     rgg_update_result *h_res = nullptr;   // pinned
+    uint8_t *h_labels = nullptr;      // pinned [E], written by the label kernel of a host-buffer update
+    int64_t *h_gray = nullptr;        // pinned [E]
     rgg_update_result *d_res = nullptr;
     uint8_t *d_labels = nullptr;      // [E]
     int64_t *d_gray = nullptr;        // [E]
@@ -78,6 +80,8 @@ struct rgg_roadmap {
         for (auto &a : allocs) hipFree(a.first);
         if (h_stage) hipHostFree(h_stage);
         if (h_res) hipHostFree(h_res);
+        if (h_labels) hipHostFree(h_labels);
+        if (h_gray) hipHostFree(h_gray);
         if (done) hipEventDestroy(done);
         if (stream) hipStreamDestroy(stream);
     }
