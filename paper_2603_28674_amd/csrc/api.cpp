@@ -341,6 +341,12 @@ rgg_status tune_search(std::vector<TuneSubject *> &subj, hipStream_t s, int reps
 
 struct rgg_graph {
     int device = 0;
+    // Updates of one roadmap are a chain; a stream runs their kernels in order
+    // by itself, and launching them costs less than launching a graph of them
+    // (a chain of three kernels: 35 us a graph launch, 28 us as launches; on
+    // the host 23 and 12 us).  Only a graph of several roadmaps, whose
+    // branches overlap, is captured.
+    std::vector<UpdateArgs> chain;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<rgg_roadmap *> roadmaps;
@@ -1099,6 +1105,22 @@ rgg_status rgg_graph_create(rgg_context *ctx, int32_t n, const rgg_update_req *r
     HIP_OR_FAIL(hipSetDevice(ctx->device), "hipSetDevice");
     auto *g = new rgg_graph();
     g->device = ctx->device;
+    bool one = true;
+    for (int32_t k = 1; k < n; ++k) one = one && reqs[k].rm == reqs[0].rm;
+    if (one) {
+        if (reqs[0].rm->dv.chunk < 1 || reqs[0].rm->dv.chunk > item_edges_max()) {
+            delete g;
+            return hip_fail(hipErrorInvalidValue, "work items");
+        }
+        for (int32_t k = 0; k < n; ++k) {
+            const rgg_update_req &q = reqs[k];
+            g->chain.push_back({q.d_old, q.d_new, q.d_labels, q.d_gray, q.d_gray ? q.gray_cap : 0, q.d_result});
+        }
+        g->roadmaps.push_back(reqs[0].rm);
+        reqs[0].rm->holders++;
+        *out = g;
+        return RGG_OK;
+    }
     hipError_t e = hipGraphCreate(&g->graph, 0);
     if (e != hipSuccess) {
         delete g;
@@ -1137,6 +1159,14 @@ rgg_status rgg_graph_launch(rgg_graph *g, void *stream)
     for (rgg_roadmap *rm : g->roadmaps) {
         rgg_status st = order_after_previous(rm, s);
         if (st != RGG_OK) return st;
+    }
+    if (!g->chain.empty()) {
+        rgg_roadmap *rm = g->roadmaps[0];
+        for (size_t k = 0; k < g->chain.size(); ++k)
+            HIP_OR_FAIL(launch_update(rm->dv, g->chain[k], s, nullptr, k + 1 == g->chain.size() ? rm->done : nullptr),
+                        "update launch");
+        mark_update(rm, s);
+        return RGG_OK;
     }
     HIP_OR_FAIL(hipGraphLaunch(g->exec, s), "hipGraphLaunch");
     for (rgg_roadmap *rm : g->roadmaps) {
