@@ -2331,7 +2331,20 @@ __device__ inline void load_row(R *dst, const R &src)
     for (int k = threadIdx.x; k < (int)(sizeof(R) / 4); k += blockDim.x) b[k] = a[k];
     __syncthreads();
 }
-__device__ inline void load_rm(RmDev *dst, const RmDev &src) { load_row(dst, src); }
+
+// A row of the table as the item kernel reads it: in constant memory for the
+// compiler (no kernel after the diff writes the table), so that the view's
+// fields are scalar loads into scalar registers, as a single update's kernel
+// arguments are.  From a copy in LDS every field took vector registers, which
+// this kernel has none to spare of: 116 B of spills per lane in 2-D and 196 in
+// 3-D against 44 and 124 now, 16 planar roadmaps 71.4 -> 66.6 us, 12 spatial
+// ones 161 -> 153.  (With three blocks per CU and no spills small batches
+// would gain 1 to 4 us more, but 20 roadmaps of up to 12k nodes lose 4 to 11.)
+__device__ __forceinline__ const RmDev &const_row(const RmDev &rm)
+{
+    typedef const __attribute__((address_space(4))) RmDev *Ptr;
+    return *(const RmDev *)(Ptr)(uintptr_t)&rm;
+}
 
 // One block per roadmap.  With h_tab (this launch's pinned host rows) the
 // block reads its row from host memory and writes it to the device table,
@@ -2363,7 +2376,6 @@ __global__ void __launch_bounds__(kDiffBlock) k_diff_batch(BatchReq *tab, const 
 template <int D, typename T>
 __device__ __forceinline__ void item_batch_body(const BatchReq *tab, const int32_t *grp, int n)
 {
-    __shared__ RmDev s_rm;
     __shared__ int s_pref[kMaxBatch + 1];
     __shared__ int s_w[kWaves];
     __shared__ int s_next;
@@ -2380,7 +2392,6 @@ __device__ __forceinline__ void item_batch_body(const BatchReq *tab, const int32
     __syncthreads();
     const int G = (int)gridDim.x;
     int32_t *const claim = &tab[grp[0]].rm.ctl->claim;   // reset by the diff of this update
-    int cur = -1;                                        // the request whose view s_rm holds
     int g = (int)blockIdx.x;
     for (int k = 0; g < tot; ++k) {
         // the request owning item g: the last r with s_pref[r] <= g (uniform)
@@ -2393,11 +2404,8 @@ __device__ __forceinline__ void item_batch_body(const BatchReq *tab, const int32
         const bool claims = k + 1 >= kBatchStatic;
         int nxt = 0;
         if (claims && tid == 0) nxt = kBatchStatic * G + atomicAdd(claim, 1);
-        if (lo != cur) {
-            load_rm(&s_rm, tab[grp[lo]].rm);
-            cur = lo;
-        }
-        item_body<D, T, 0, false, true>(s_rm, g - s_pref[lo], 1, false);
+        const int li = __builtin_amdgcn_readfirstlane(g - s_pref[lo]);
+        item_body<D, T, 0, false, true>(const_row(tab[__builtin_amdgcn_readfirstlane(grp[lo])].rm), li, 1, false);
         if (claims && tid == 0) s_next = nxt;
         __syncthreads();
         g = claims ? s_next : g + G;
