@@ -1833,7 +1833,7 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride,
     // one address from every lane are slow
     const unsigned long long w_outer = wave_sum_u64(n_outer), w_bytes = wave_sum_u64(bytes);
     if (tid == 0 && n_pairs) atomicAdd(&L.acc[0], (unsigned long long)n_pairs);
-    const int byte_row = kList ? kStatItemBytes : kStatPairBytes;
+    const int byte_row = kF32 && !kOne ? kStatItemBytes : kStatPairBytes;
     if (lane == 0) {
         if (w_outer) atomicAdd(&L.acc[1], w_outer);
         if (w_bytes) atomicAdd(&L.acc[byte_row], w_bytes);
@@ -1848,12 +1848,15 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride,
     if (kList && tid == 0) rm.pl_cnt[blockIdx.x] = L.pl_n;
 }
 
-// The binary32 kernel is held to 128 VGPRs (four waves per SIMD, four
-// blocks per CU); the binary64 one keeps the compiler's choice.
-template <int D, int MODE>
-__global__ void __launch_bounds__(kBlock, 4) k_item32(RmDev rm)
+// The binary32 kernel is held to the registers with which kPerCu blocks fit on
+// a CU (four: 128 VGPRs); the binary64 one keeps the compiler's choice.  An
+// update that lists no pairs runs without the listing (kList false): 104.2
+// against 106.5 us for the arm's second forms, 27.1 against 27.9 for 11.6k
+// planar edges.
+template <int D, int MODE, bool kList, int kPerCu>
+__global__ void __launch_bounds__(kBlock, kPerCu) k_item32(RmDev rm)
 {
-    item_body<D, float, MODE, true>(rm, (int)blockIdx.x, (int)gridDim.x, rm.n_fixed > 0);
+    item_body<D, float, MODE, kList>(rm, (int)blockIdx.x, (int)gridDim.x, rm.n_fixed > 0);
 }
 
 template <int D, int MODE>
@@ -2523,14 +2526,17 @@ __global__ void __launch_bounds__(kBlock) k_write_batch(const BatchReq *tab, int
 namespace {
 
 // The kernel of role k for the roadmap's dimension and form: 0 the item kernel
-// and 1 the pair testing of the FP32 mode, 2 the item kernel of the FP64 mode.
+// and 1 the pair testing of the FP32 mode with pair listing, 2 the item kernel
+// of the FP64 mode, 3 and 4 that of the FP32 mode without listing (4: few items).
 template <int D, int MODE>
 void *fn_of(int k)
 {
     switch (k) {
-    case 0: return (void *)k_item32<D, MODE>;
+    case 0: return (void *)k_item32<D, MODE, true, 4>;
     case 1: return (void *)k_pairs<D, MODE>;
-    default: return (void *)k_item64<D, MODE>;
+    case 3: return (void *)k_item32<D, MODE, false, 4>;
+    case 4: return (void *)k_item32<D, MODE, false, 3>;
+    default: return (void *)k_item64<D, MODE>;   // 2
     }
 }
 
@@ -2553,6 +2559,14 @@ void *fn(const RmDev &rm, int k) { return rm.D == 3 ? fn_dim<3>(rm.mode, k) : fn
 // apart per lane.  290k edges (71 tiles): 64.4 -> 63.3 us an update; below, the
 // larger block's barriers cost what that gains (3 tiles: 27.3 against 27.7).
 constexpr int kWideTiles = 16;
+
+// Items up to which the binary32 item kernel runs with three blocks per CU (and
+// registers enough to spill nothing) rather than four: as many as 256 CUs hold
+// at once that way.  29k spatial edges: 32.8 -> 31.8 us an update, planar graph
+// 26.1 -> 25.6, the non-lazy spatial update 90.8 -> 89.8.  Above it the items
+// would wait for one another: 1,007 items 63.3 us with four per CU, 82.4 with
+// three.
+constexpr int kRoomyItems = 768;
 
 struct Node {
     void *fn;
@@ -2581,7 +2595,7 @@ int plan(const RmDev &rm, Node out[7])
         // blocks past the fixed items would only start and stop (with pair
         // listing every block writes its list's count, so the whole grid runs)
         const unsigned grid = fixed && !share ? fixed_items_grid(rm) : kGrid;
-        out[n++] = {fn(rm, 0), dim3(grid), 1, 3, share ? 3 : 5};
+        out[n++] = {fn(rm, share ? 0 : (fixed && rm.n_fixed <= kRoomyItems ? 4 : 3)), dim3(grid), 1, 3, share ? 3 : 5};
         if (share) out[n++] = {fn(rm, 1), dim3(kGrid), 1, 4, 5};
     } else {
         out[n++] = {diff_fn, dim3(1), 0, 1, 3};
@@ -2696,8 +2710,8 @@ hipError_t test_blocks_resident(int D, int device, int *out)
 hipError_t item_blocks_resident(int D, int device, int *out)
 {
     int per_cu = 0, n_cu = 0;
-    hipError_t e = D == 3 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_item32<3, 0>, kBlock, 0)
-                          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_item32<2, 0>, kBlock, 0);
+    hipError_t e = D == 3 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_item32<3, 0, true, 4>, kBlock, 0)
+                          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_item32<2, 0, true, 4>, kBlock, 0);
     if (e != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device)) != hipSuccess) return e;
     *out = per_cu * n_cu;

@@ -51,3 +51,30 @@ def test_items(ctx, kind, cells, item_edges, n_boxes):
             assert np.array_equal(gl, ol) and np.array_equal(gg, og)
             prev = cur
         g.close()
+
+
+@pytest.mark.parametrize("mode", [{}, {"outer_obb": True}, {"inner_splines": True},
+                                  {"outer_obb": True, "inner_splines": True}])
+@pytest.mark.parametrize("kind", ["planar", "spatial"])
+@pytest.mark.parametrize("items", [1, 767, 768, 769, 1600])
+def test_item_counts(ctx, kind, mode, items):
+    """One cell of 1 to 1,600 items, around the count up to which three blocks
+    share a CU."""
+    from paper_2603_28674_amd import rgg
+    import oracle
+    n, chunk = (400, 511) if items == 1 else (items, 1)
+    if kind == "planar":
+        w = synth.planar_rigid(seed=7, n_nodes=500, n_boxes=40, n_updates=2, n_move=20, world=30.0, resolution=0.5)
+    else:
+        w = synth.spatial_rigid(seed=7, n_nodes=500, n_boxes=40, n_updates=2, move_frac=0.5, world=3.0, samples=5)
+    assert w.n_edges >= n
+    w.edges = w.edges[:n]
+    g = rgg.Roadmap.from_workload(ctx, w, precision=rgg.RGG_PREC_FP32_RECHECK, cell_size=-1.0, item_edges=chunk, **mode)
+    o = oracle.from_workload(w, **mode)
+    prev = w.absent()
+    for cur in w.boxes:
+        ol, og = o.update(prev, cur)
+        gl, gg, _, _ = g.update(prev, cur)
+        assert np.array_equal(gl, ol) and np.array_equal(gg, og)
+        prev = cur
+    g.close()
