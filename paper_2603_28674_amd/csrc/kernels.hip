@@ -662,7 +662,7 @@ __device__ bool splines_meet64(const RmDev &rm, int64_t e, uint64_t m, const dou
 }
 
 // ------------------------------------------------------------------------
-// k_item: one block per work item (grid cell c, a chunk of at most 256 of
+// k_item: one block per work item (grid cell c, a chunk of at most 512 of
 // its edges; the chunk size is the roadmap's work-item size).
 //
 //   1. every thread owns up to two edges of the item.  The changed entries
@@ -685,10 +685,10 @@ __device__ bool splines_meet64(const RmDev &rm, int64_t e, uint64_t m, const dou
 //   4. inner test of the pairs still open, rows = (pair, sphere whose capsule
 //      met), lanes = configurations: every copy of those spheres.
 //      The end copies settle most pairs that end RED before any exact test or
-//      copy: kernel 49 -> 43 us on 290k spatial edges with 100 changed boxes;
-//      the binary64 kernel, which ran the exact minimum (seven divisions) on
-//      every capsule, 35 -> 22 us on 11.6k planar edges, 49 -> 31 us on 46k
-//      spatial ones.
+//      copy: an update of 290k spatial edges with 100 changed boxes 78.2 ->
+//      75.0 us; in binary64, where every capsule ran the exact minimum (seven
+//      divisions), 47.5 -> 37.1 us on 11.6k planar edges and 70.4 -> 53.3 on
+//      46k spatial ones.
 //   5. per pair C and S; the edge's counter deltas are summed in LDS and
 //      added once per edge.  In FP32 a pair whose decision fell inside the
 //      rounding band is queued and decided in binary64 by the same block

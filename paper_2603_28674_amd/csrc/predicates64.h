@@ -1,8 +1,8 @@
 // The binary64 predicates behind every exact decision of librgg: the update
-// kernels' binary64 re-tests and deferred items, the oriented-box test (always
-// decided in binary64), and the full validation.  Each is one fixed expression order; device code is compiled
-// without FMA contraction, so any IEEE binary64 evaluator of the same
-// expressions reaches the same values.
+// kernels' binary64 tests and re-tests, the oriented-box test (always decided
+// in binary64), and the full validation.  Each is one fixed expression order;
+// device code is compiled without FMA contraction, so any IEEE binary64
+// evaluator of the same expressions reaches the same values.
 #pragma once
 
 #include <hip/hip_runtime.h>
