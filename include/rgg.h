@@ -266,7 +266,10 @@ rgg_status rgg_roadmap_info_get(rgg_roadmap *rm, rgg_roadmap_info *out);
  * applied to `obstacles_new`.  Outputs (each may be NULL): labels [E] host,
  * gray [gray_cap] host (ascending GRAY edge ids), *n_gray, *result.  If
  * n_gray > gray_cap the update is still committed, gray[0..gray_cap) is
- * written and RGG_E_CAPACITY is returned.  Blocks until done. */
+ * written and RGG_E_CAPACITY is returned.  Blocks until done.  The first call
+ * that asks for labels (for ids) page-locks E (8 E) bytes of host memory, held
+ * until rgg_destroy; when there are none, that call copies the output instead,
+ * which takes longer and gives the same. */
 rgg_status rgg_update(rgg_roadmap *rm, int64_t m, const rgg_box *obstacles_old,
                       const rgg_box *obstacles_new, uint8_t *labels, int64_t *gray,
                       int64_t gray_cap, int64_t *n_gray, rgg_update_result *result);
@@ -608,6 +611,12 @@ rgg_status rgg_debug_second_forms(const rgg_roadmap_desc *roadmap, const rgg_rob
  * checksum); *n_edges (may be NULL) receives its edge count.  Same errors as
  * rgg_load's file checks. */
 rgg_status rgg_debug_read_file(const char *path, int64_t *n_edges);
+
+/* For tests: *bytes (may be NULL) receives the page-locked host memory that
+ * the roadmap holds for the outputs of rgg_update; limit >= 0 makes it refuse
+ * to hold more than that from here on, as if no more were to be had (-1: no
+ * limit). */
+rgg_status rgg_debug_pinned(rgg_roadmap *rm, int64_t limit, int64_t *bytes);
 
 const char *rgg_last_error(void);
 const char *rgg_version(void);

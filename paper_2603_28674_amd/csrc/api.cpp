@@ -774,8 +774,6 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
     if ((st = hip_ok(hipMemset(rm->d_labels, 0, std::max<int64_t>(E, 1)), "clear labels")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipHostMalloc((void **)&rm->h_stage, sizeof(rgg_box) * std::max<int64_t>(2 * M, 1)), "pinned staging")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipHostMalloc((void **)&rm->h_res, sizeof(rgg_update_result)), "pinned result")) != RGG_OK) return guard(st);
-    if ((st = hip_ok(hipHostMalloc((void **)&rm->h_labels, (size_t)std::max<int64_t>(E, 1)), "pinned labels")) != RGG_OK) return guard(st);
-    if ((st = hip_ok(hipHostMalloc((void **)&rm->h_gray, sizeof(int64_t) * std::max<int64_t>(E, 1)), "pinned gray list")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipStreamCreateWithFlags(&rm->stream, hipStreamNonBlocking), "stream")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipEventCreateWithFlags(&rm->done, kOrderEventFlags), "event")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipDeviceSynchronize(), "build upload")) != RGG_OK) return guard(st);
@@ -890,6 +888,28 @@ rgg_status enqueue(rgg_roadmap *rm, hipStream_t s, const UpdateArgs &a)
     return RGG_OK;
 }
 
+// Page-locked bytes of a roadmap's host outputs.
+int64_t outputs_pinned(const rgg_roadmap *rm)
+{
+    return (rm->h_labels ? rm->dv.E : 0) + (rm->h_gray ? (int64_t)sizeof(int64_t) * rm->dv.E : 0);
+}
+
+// Makes sure of the pinned array `*p` (E elements) of a host-buffer update's
+// outputs; false when there is no page-locked memory for it.  (Roadmaps that
+// are updated through device buffers, graphs, batches or the server only never
+// hold one.)
+template <typename T>
+bool pinned_output(rgg_roadmap *rm, T **p)
+{
+    if (*p) return true;
+    const int64_t bytes = (int64_t)sizeof(T) * rm->dv.E;
+    if (rm->pin_limit >= 0 && outputs_pinned(rm) + bytes > rm->pin_limit) return false;
+    if (hipHostMalloc((void **)p, (size_t)bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *p = nullptr;
+    return false;
+}
+
 }  // namespace
 
 extern "C" {
@@ -924,7 +944,8 @@ rgg_status rgg_update(rgg_roadmap *rm, int64_t m, const rgg_box *obstacles_old,
     // transfer of its own costs 10 to 15 us each way, and the labels' and the
     // ids' could only be queued once the result was read.  (Updates of 1k / 116k
     // edges: 76 -> 45 us and 133 -> 93 us.)  Many boxes still go up in one
-    // transfer, since one block reads them.
+    // transfer, since one block reads them.  An output that finds no
+    // page-locked memory is written to the device array and copied.
     const rgg_box *boxes = rm->h_stage;
     if (M > 0) {
         memcpy(rm->h_stage, obstacles_old, sizeof(rgg_box) * M);
@@ -937,7 +958,15 @@ rgg_status rgg_update(rgg_roadmap *rm, int64_t m, const rgg_box *obstacles_old,
         }
     }
     const int64_t n_ids = gray ? std::min(gray_cap, E) : 0;
-    UpdateArgs a = {boxes, boxes + M, labels ? rm->h_labels : nullptr, n_ids > 0 ? rm->h_gray : nullptr, n_ids, rm->h_res};
+    const bool want_labels = labels && E > 0, want_ids = n_ids > 0;
+    const bool pin_labels = want_labels && pinned_output(rm, &rm->h_labels);
+    const bool pin_ids = want_ids && pinned_output(rm, &rm->h_gray);
+    UpdateArgs a = {boxes,
+                    boxes + M,
+                    pin_labels ? rm->h_labels : (want_labels ? rm->d_labels : nullptr),
+                    pin_ids ? rm->h_gray : (want_ids ? rm->d_gray : nullptr),
+                    n_ids,
+                    rm->h_res};
     rgg_status st = enqueue(rm, s, a);
     if (st != RGG_OK) return st;
     HIP_OR_FAIL(hipStreamSynchronize(s), "update");
@@ -948,8 +977,11 @@ rgg_status rgg_update(rgg_roadmap *rm, int64_t m, const rgg_box *obstacles_old,
                                   ? "obstacles_old differs from the resident obstacle slots"
                                   : "non-finite or out-of-range box coordinate");
     }
-    if (labels && E > 0) memcpy(labels, rm->h_labels, (size_t)E);
-    if (n_ids > 0) memcpy(gray, rm->h_gray, sizeof(int64_t) * std::min(r.n_gray, n_ids));
+    if (pin_labels) memcpy(labels, rm->h_labels, (size_t)E);
+    else if (want_labels) HIP_OR_FAIL(hipMemcpy(labels, rm->d_labels, (size_t)E, hipMemcpyDeviceToHost), "read labels");
+    const size_t id_bytes = sizeof(int64_t) * (size_t)std::min(r.n_gray, n_ids);
+    if (pin_ids) memcpy(gray, rm->h_gray, id_bytes);
+    else if (id_bytes) HIP_OR_FAIL(hipMemcpy(gray, rm->d_gray, id_bytes, hipMemcpyDeviceToHost), "read gray list");
     if (n_gray) *n_gray = r.n_gray;
     if (gray && r.n_gray > gray_cap)
         return fail(RGG_E_CAPACITY, "gray list has %lld edges, capacity %lld", (long long)r.n_gray, (long long)gray_cap);
@@ -1877,6 +1909,14 @@ rgg_status rgg_load(rgg_context *ctx, const char *path, rgg_roadmap **out)
     if ((st = make_roadmap(ctx, g, grid, p, L.resident.data(), L.cnt.data(), &rm)) != RGG_OK) return st;
     rm->info.build_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     *out = rm;
+    return RGG_OK;
+}
+
+rgg_status rgg_debug_pinned(rgg_roadmap *rm, int64_t limit, int64_t *bytes)
+{
+    if (!rm) return fail(RGG_E_INVALID_ARG, "null roadmap");
+    rm->pin_limit = limit;
+    if (bytes) *bytes = outputs_pinned(rm);
     return RGG_OK;
 }
 

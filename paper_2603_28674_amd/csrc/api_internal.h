@@ -55,8 +55,11 @@ struct rgg_roadmap {
     rgg_box *h_stage = nullptr;       // pinned [2M]
     rgg_box *d_stage = nullptr;       // [2M]
     rgg_update_result *h_res = nullptr;   // pinned
-    uint8_t *h_labels = nullptr;      // pinned [E], written by the label kernel of a host-buffer update
-    int64_t *h_gray = nullptr;        // pinned [E]
+    // pinned [E] each, written by the label kernel of a host-buffer update: from the
+    // first one that asks for the labels (the ids) on, null as long as none did
+    uint8_t *h_labels = nullptr;
+    int64_t *h_gray = nullptr;
+    int64_t pin_limit = -1;           // bytes they may hold together (tests); -1: any number
     rgg_update_result *d_res = nullptr;
     uint8_t *d_labels = nullptr;      // [E]
     int64_t *d_gray = nullptr;        // [E]

@@ -145,7 +145,7 @@ EXPORTS = ["rgg_context_create", "rgg_context_destroy", "rgg_build", "rgg_destro
            "rgg_server_submit", "rgg_server_poll", "rgg_server_poll_timing", "rgg_server_info", "rgg_server_stop", "rgg_labels", "rgg_gray_list",
            "rgg_timing_enable", "rgg_timing_read", "rgg_tune", "rgg_batch_tune", "rgg_save", "rgg_load",
            "rgg_validate", "rgg_validate_async",
-           "rgg_debug_geometry", "rgg_debug_second_forms", "rgg_debug_read_file",
+           "rgg_debug_geometry", "rgg_debug_second_forms", "rgg_debug_read_file", "rgg_debug_pinned",
            "rgg_last_error", "rgg_version"]
 
 _lib = None
@@ -198,6 +198,7 @@ def lib():
         "rgg_debug_geometry": (I32, [P, P, P, I64, I64, P, P, P, P]),
         "rgg_debug_second_forms": (I32, [P, P, P, I64, I64, P, P, P]),
         "rgg_debug_read_file": (I32, [C.c_char_p, C.POINTER(I64)]),
+        "rgg_debug_pinned": (I32, [P, I64, C.POINTER(I64)]),
         "rgg_last_error": (C.c_char_p, []),
         "rgg_version": (C.c_char_p, []),
     }
@@ -593,6 +594,14 @@ def rgg_debug_read_file(path):
     its edge count."""
     n = C.c_int64(0)
     _check(lib().rgg_debug_read_file(os.fsencode(path), C.byref(n)))
+    return n.value
+
+
+def rgg_debug_pinned(rm, limit=-1):
+    """Page-locked bytes that the roadmap's host outputs hold; sets their limit
+    (-1: none)."""
+    n = C.c_int64(0)
+    _check(lib().rgg_debug_pinned(rm, int(limit), C.byref(n)))
     return n.value
 
 
