@@ -298,9 +298,10 @@ typedef struct {
 
 /* Fixes n updates to be launched together: requests naming the same roadmap
  * run in the order given, requests on different roadmaps run as independent
- * branches of one HIP graph (updates of a single roadmap, a plain chain, are
- * launched as their kernels).  Every launch of the graph performs all n updates; the device
- * pointers are fixed at creation.  *out receives the graph. */
+ * branches of one HIP graph (up to three updates of a single roadmap, a short
+ * chain, are launched as their kernels).  Every launch of the graph performs
+ * all n updates; the device pointers are fixed at creation.  *out receives the
+ * graph. */
 rgg_status rgg_graph_create(rgg_context *ctx, int32_t n, const rgg_update_req *reqs,
                             rgg_graph **out);
 rgg_status rgg_graph_launch(rgg_graph *g, void *stream);

@@ -339,13 +339,21 @@ rgg_status tune_search(std::vector<TuneSubject *> &subj, hipStream_t s, int reps
 
 }  // namespace
 
+// Kernels of a single roadmap's updates that rgg_graph_launch launches one by
+// one.  On the host a launch costs 2.5 to 2.8 us, a graph 20 us and little more
+// per update; on the device a graph takes 8 us more, and 1 to 2 us less per
+// update.  Updates of 29k spatial edges, launched against captured: 1 update
+// 31 / 39 us (host 8 / 19), 2: 62 / 69 (15 / 24), 3: 93 / 99 (25 / 26), 4: 125 /
+// 130 (33 / 28), 6: 186 / 190 (49 / 30), 12: 371 / 369 (91 / 39); of 1k edges, 3:
+// 122 / 124, 4: 162 / 162, 12: 484 / 465.  So three updates of three kernels
+// (two of four, with pair listing): from there on the host pays for it.
+constexpr int kChainKernels = 9;
+
 struct rgg_graph {
     int device = 0;
-    // Updates of one roadmap are a chain; a stream runs their kernels in order
-    // by itself, and launching them costs less than launching a graph of them
-    // (a chain of three kernels: 35 us a graph launch, 28 us as launches; on
-    // the host 23 and 12 us).  Only a graph of several roadmaps, whose
-    // branches overlap, is captured.
+    // Updates of one roadmap are a chain, which a stream runs in order by
+    // itself; a chain of up to kChainKernels kernels is launched as they are.
+    // Longer ones, and several roadmaps, whose branches overlap, are captured.
     std::vector<UpdateArgs> chain;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1137,8 +1145,8 @@ rgg_status rgg_graph_create(rgg_context *ctx, int32_t n, const rgg_update_req *r
     HIP_OR_FAIL(hipSetDevice(ctx->device), "hipSetDevice");
     auto *g = new rgg_graph();
     g->device = ctx->device;
-    bool one = true;
-    for (int32_t k = 1; k < n; ++k) one = one && reqs[k].rm == reqs[0].rm;
+    bool one = (int64_t)n * update_kernels(reqs[0].rm->dv) <= kChainKernels;
+    for (int32_t k = 1; k < n && one; ++k) one = reqs[k].rm == reqs[0].rm;
     if (one) {
         if (reqs[0].rm->dv.chunk < 1 || reqs[0].rm->dv.chunk > item_edges_max()) {
             delete g;

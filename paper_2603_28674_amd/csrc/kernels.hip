@@ -2668,6 +2668,12 @@ hipError_t launch_update(const RmDev &rm, const UpdateArgs &a, hipStream_t s, hi
     return hipSuccess;
 }
 
+int update_kernels(const RmDev &rm)
+{
+    Node nodes[7];
+    return plan(rm, nodes);
+}
+
 int item_edges_max() { return kItemCap; }
 
 __global__ void __launch_bounds__(kBlock) k_cell_slots(RmDev rm, int4 *out, int64_t n)

@@ -251,6 +251,9 @@ hipError_t launch_marked(const void *fn, dim3 grid, dim3 block, void **args, hip
 // classify, re-test, labels).  `done` (may be null) marks the end.
 hipError_t launch_update(const RmDev &rm, const UpdateArgs &a, hipStream_t s, hipEvent_t *ev, hipEvent_t done = nullptr);
 
+// How many kernels those are.
+int update_kernels(const RmDev &rm);
+
 // Appends the same kernels to `g` as a chain; `dep` (may be null) is the
 // node they wait for, *last receives the final node.
 hipError_t add_update_nodes(hipGraph_t g, const RmDev &rm, const UpdateArgs &a, hipGraphNode_t dep,
