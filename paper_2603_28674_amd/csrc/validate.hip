@@ -130,7 +130,7 @@ constexpr int kVCull = 16;        // candidates from which a step looks for ones
 constexpr int kVList = 256;          // candidate slots listed; more are found again page by page
 static_assert(kVList % kValBoxes == 0 && kMaxSlots <= 65536, "whole pages are listed, as 16-bit slots");
 
-inline ValLds val_lds(const ValDev &v, int max_active)
+constexpr ValLds val_lds(const ValDev &v, int max_active)
 {
     ValLds l = {};
     const int sincos = v.kind == RGG_PLANAR_ARM ? v.L : (v.kind == RGG_SE3 ? 2 : 1);
@@ -170,6 +170,34 @@ inline ValLds val_lds(const ValDev &v, int max_active)
     l.bytes = 8 * (l.region0 + kVWaves * l.region);
     return l;
 }
+
+// LDS of a CU, which one block may have all of, and the kernel's own variables
+// in it, with room to spare.
+constexpr int kVLds = 160 * 1024, kVStatic = 256;
+
+// The most that any robot, slot count and limit of a call asks for (72,768
+// bytes, of 64 spheres in 3-D): every call's block fits.
+constexpr int val_lds_most()
+{
+    ValDev v = {};
+    int most = 0;
+    auto take = [&](int kind, int D, int L, int dof) {
+        v.kind = kind;
+        v.D = D;
+        v.L = L;
+        v.vstride = 2 * dof + 3;
+        for (v.B = 1; v.B <= (int)(sizeof(VRobot::rad) / sizeof(double)); ++v.B) {
+            v.M = kVTile;
+            const int n = val_lds(v, kValMaxActive).bytes;
+            if (n > most) most = n;
+        }
+    };
+    take(RGG_SE2, 2, 0, 3);
+    take(RGG_SE3, 3, 0, 7);
+    for (int L = 1; L <= (int)(sizeof(VRobot::len) / sizeof(double)); ++L) take(RGG_PLANAR_ARM, 2, L, L);
+    return most;
+}
+static_assert(val_lds_most() == 72768 && val_lds_most() + kVStatic <= kVLds, "a validation block fits a CU");
 
 // What one wavefront works on.
 struct ValCtx {
@@ -802,8 +830,8 @@ hipError_t launch_validate(const ValDev &v, const int64_t *ids, int64_t n, const
     if (n <= 0) return done ? hipEventRecord(done, s) : hipSuccess;
     const ValLds l = val_lds(v, max_active);
     // the blocks that the device holds at once, by registers and by LDS
-    const int64_t fit = (160 * 1024) / (l.bytes + 256), most = v_blocks_per_cu(v.D);
-    const int64_t held = (int64_t)v.n_cu * (fit < 1 ? 1 : (fit > most ? most : fit));
+    const int64_t fit = kVLds / (l.bytes + kVStatic), most = v_blocks_per_cu(v.D);
+    const int64_t held = (int64_t)v.n_cu * (fit > most ? most : fit);
     const int64_t full = (n + kVWaves - 1) / kVWaves;
     const int grid = (int)(full < held ? full : held);
     void *args[] = {(void *)&v,         (void *)&l,       (void *)&ids,     (void *)&n,     (void *)&count,   (void *)&max_level,
