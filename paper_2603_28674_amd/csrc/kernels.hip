@@ -998,7 +998,7 @@ __device__ __forceinline__ void retest_queued(const RmDev &rm, Lds &L, const int
 // for a round (the caller re-tests them).
 template <int D, typename T, int MODE, bool kShare, typename Lds>
 __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_rad2, const int *s_lane, int np,
-                                           uint32_t &n_pairs, uint32_t &n_outer, uint32_t &bytes)
+                                           uint32_t &n_pairs, uint32_t &n_outer, unsigned long long &bytes)
 {
     constexpr bool kF32 = std::is_same<T, float>::value;
     constexpr bool kObb = (MODE & kModeObb) != 0;
@@ -1554,7 +1554,8 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride,
     const int4 item0 = !single && li0 < cap ? items[li0] : make_int4(0, 0, 0, 0);
     const int status = kOne ? RGG_OK : ctl->status;
     // wavefront-uniform counts (kept in scalar registers) and per-lane ones
-    uint32_t n_pairs = 0, visited = 0, cand = 0, n_outer = 0, bytes = 0;
+    uint32_t n_pairs = 0, visited = 0, cand = 0, n_outer = 0;
+    unsigned long long bytes = 0;
     const int n_chg = ctl->n_chg;
     const int n_items = kOne ? cap : min(ctl->n_items, cap);
     const float4 *aabb = reinterpret_cast<const float4 *>(rm.aabb);
@@ -1815,7 +1816,7 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride,
             if (!full) tile0 = round0 = 0;
             if (!covered) continue;
             if (!full) cand += (uint32_t)(__popcll(__ballot(had & 1u)) + __popcll(__ballot(had & 2u)));
-            if (fused && !full) bytes += (uint32_t)__popc(had) * ((2 * D + 1) * B * sizeof(T) + 16);
+            if (fused && !full) bytes += (unsigned long long)__popc(had) * ((2 * D + 1) * B * sizeof(T) + 16);
             __syncthreads();
 #pragma unroll
             for (int h = 0; h < kSlots; ++h) {
@@ -1947,7 +1948,8 @@ __device__ __forceinline__ void share_body(const RmDev &rm)
     const int64_t hi = b < G ? (int64_t)total * (b + 1) / G : 0;
     const float4 *aabb = reinterpret_cast<const float4 *>(rm.aabb);
     const int jfix = rm.p_fixed ? rm.p_fixed / B : 0;
-    uint32_t n_pairs = 0, n_outer = 0, bytes = 0;
+    uint32_t n_pairs = 0, n_outer = 0;
+    unsigned long long bytes = 0;
     for (int64_t r0 = lo; r0 < hi; r0 += kPairCap) {
         const int np = (int)min((int64_t)kPairCap, hi - r0);
         if (tid < np) {
@@ -1984,7 +1986,7 @@ __device__ __forceinline__ void share_body(const RmDev &rm)
         }
         __syncthreads();
         if (tid < np && (tid == 0 || L.edge[tid] != L.edge[tid - 1]))
-            bytes += (uint32_t)((2 * D + 1) * B * sizeof(float) + (jfix ? 0 : 16));
+            bytes += (unsigned long long)((2 * D + 1) * B * sizeof(float) + (jfix ? 0 : 16));
         test_round<D, float, MODE, true>(rm, L, s_rad2, s_lane, np, n_pairs, n_outer, bytes);
         if (L.r64.n) retest_queued<D, MODE>(rm, L, s_lane, n_outer);
     }
