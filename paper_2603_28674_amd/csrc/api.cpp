@@ -62,6 +62,20 @@ int host_threads(int requested)
 
 constexpr int32_t kChunk = 256;   // edges per grid work item by default (one per thread)
 constexpr int64_t kDirectSlots = 1024;   // boxes that a host-buffer update's kernels read from pinned memory
+// Host outputs (9 bytes per edge) up to this many bytes share the boxes' pinned
+// block from the build on; larger ones come with the first call that asks for
+// them, which takes that call about 60 us (116k edges: 218 us instead of 152).
+constexpr int64_t kSmallOutputs = 64 * 1024;
+
+// The host outputs' block: the labels, in whole lines, then the ids.
+int64_t label_room(int64_t E) { return (E + 255) / 256 * 256; }
+int64_t output_bytes(int64_t E) { return label_room(E) + (int64_t)sizeof(int64_t) * E; }
+
+void place_outputs(rgg_roadmap *rm, void *block)
+{
+    rm->h_labels = (uint8_t *)block;
+    rm->h_gray = (int64_t *)(rm->h_labels + label_room(rm->dv.E));
+}
 
 // The fixed items of a grid of several cells (RmDev::fixed); none when there
 // are more than kFixedItems.
@@ -780,7 +794,10 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
     }
     if ((st = hip_ok(hipMemset(dv.blk_stats, 0, sizeof(unsigned long long) * kStatBlocks * kStats), "clear statistics")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipMemset(rm->d_labels, 0, std::max<int64_t>(E, 1)), "clear labels")) != RGG_OK) return guard(st);
-    if ((st = hip_ok(hipHostMalloc((void **)&rm->h_stage, sizeof(rgg_box) * std::max<int64_t>(2 * M, 1)), "pinned staging")) != RGG_OK) return guard(st);
+    const int64_t box_room = ((int64_t)sizeof(rgg_box) * std::max<int64_t>(2 * M, 1) + 255) / 256 * 256;
+    const int64_t outs = output_bytes(E) <= kSmallOutputs ? output_bytes(E) : 0;
+    if ((st = hip_ok(hipHostMalloc((void **)&rm->h_stage, (size_t)(box_room + outs)), "pinned staging")) != RGG_OK) return guard(st);
+    if (outs) place_outputs(rm, (char *)rm->h_stage + box_room);
     if ((st = hip_ok(hipHostMalloc((void **)&rm->h_res, sizeof(rgg_update_result)), "pinned result")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipStreamCreateWithFlags(&rm->stream, hipStreamNonBlocking), "stream")) != RGG_OK) return guard(st);
     if ((st = hip_ok(hipEventCreateWithFlags(&rm->done, kOrderEventFlags), "event")) != RGG_OK) return guard(st);
@@ -896,26 +913,20 @@ rgg_status enqueue(rgg_roadmap *rm, hipStream_t s, const UpdateArgs &a)
     return RGG_OK;
 }
 
-// Page-locked bytes of a roadmap's host outputs.
-int64_t outputs_pinned(const rgg_roadmap *rm)
+// The pinned arrays of the outputs of the host-buffer updates after this one,
+// left out when there is no page-locked memory.  (Larger roadmaps that are
+// updated through device buffers, graphs, batches or the server only never hold
+// any.)
+void pin_outputs(rgg_roadmap *rm)
 {
-    return (rm->h_labels ? rm->dv.E : 0) + (rm->h_gray ? (int64_t)sizeof(int64_t) * rm->dv.E : 0);
-}
-
-// Makes sure of the pinned array `*p` (E elements) of a host-buffer update's
-// outputs; false when there is no page-locked memory for it.  (Roadmaps that
-// are updated through device buffers, graphs, batches or the server only never
-// hold one.)
-template <typename T>
-bool pinned_output(rgg_roadmap *rm, T **p)
-{
-    if (*p) return true;
-    const int64_t bytes = (int64_t)sizeof(T) * rm->dv.E;
-    if (rm->pin_limit >= 0 && outputs_pinned(rm) + bytes > rm->pin_limit) return false;
-    if (hipHostMalloc((void **)p, (size_t)bytes) == hipSuccess) return true;
-    (void)hipGetLastError();
-    *p = nullptr;
-    return false;
+    const int64_t bytes = output_bytes(rm->dv.E);
+    if (rm->pin_limit >= 0 && bytes > rm->pin_limit) return;
+    if (hipHostMalloc(&rm->h_outputs, (size_t)bytes) == hipSuccess) {
+        place_outputs(rm, rm->h_outputs);
+    } else {
+        (void)hipGetLastError();
+        rm->h_outputs = nullptr;
+    }
 }
 
 }  // namespace
@@ -952,8 +963,9 @@ rgg_status rgg_update(rgg_roadmap *rm, int64_t m, const rgg_box *obstacles_old,
     // transfer of its own costs 10 to 15 us each way, and the labels' and the
     // ids' could only be queued once the result was read.  (Updates of 1k / 116k
     // edges: 76 -> 45 us and 133 -> 93 us.)  Many boxes still go up in one
-    // transfer, since one block reads them.  An output that finds no
-    // page-locked memory is written to the device array and copied.
+    // transfer, since one block reads them.  A call that finds no pinned outputs
+    // gets them by copies from the device arrays, and locks the pages for the
+    // next calls while its kernels run.
     const rgg_box *boxes = rm->h_stage;
     if (M > 0) {
         memcpy(rm->h_stage, obstacles_old, sizeof(rgg_box) * M);
@@ -967,16 +979,16 @@ rgg_status rgg_update(rgg_roadmap *rm, int64_t m, const rgg_box *obstacles_old,
     }
     const int64_t n_ids = gray ? std::min(gray_cap, E) : 0;
     const bool want_labels = labels && E > 0, want_ids = n_ids > 0;
-    const bool pin_labels = want_labels && pinned_output(rm, &rm->h_labels);
-    const bool pin_ids = want_ids && pinned_output(rm, &rm->h_gray);
+    const bool pinned = rm->h_labels != nullptr;
     UpdateArgs a = {boxes,
                     boxes + M,
-                    pin_labels ? rm->h_labels : (want_labels ? rm->d_labels : nullptr),
-                    pin_ids ? rm->h_gray : (want_ids ? rm->d_gray : nullptr),
+                    want_labels ? (pinned ? rm->h_labels : rm->d_labels) : nullptr,
+                    want_ids ? (pinned ? rm->h_gray : rm->d_gray) : nullptr,
                     n_ids,
                     rm->h_res};
     rgg_status st = enqueue(rm, s, a);
     if (st != RGG_OK) return st;
+    if (!pinned && (want_labels || want_ids)) pin_outputs(rm);
     HIP_OR_FAIL(hipStreamSynchronize(s), "update");
     const rgg_update_result r = *rm->h_res;
     if (result) *result = r;
@@ -985,11 +997,14 @@ rgg_status rgg_update(rgg_roadmap *rm, int64_t m, const rgg_box *obstacles_old,
                                   ? "obstacles_old differs from the resident obstacle slots"
                                   : "non-finite or out-of-range box coordinate");
     }
-    if (pin_labels) memcpy(labels, rm->h_labels, (size_t)E);
-    else if (want_labels) HIP_OR_FAIL(hipMemcpy(labels, rm->d_labels, (size_t)E, hipMemcpyDeviceToHost), "read labels");
     const size_t id_bytes = sizeof(int64_t) * (size_t)std::min(r.n_gray, n_ids);
-    if (pin_ids) memcpy(gray, rm->h_gray, id_bytes);
-    else if (id_bytes) HIP_OR_FAIL(hipMemcpy(gray, rm->d_gray, id_bytes, hipMemcpyDeviceToHost), "read gray list");
+    if (pinned) {
+        if (want_labels) memcpy(labels, rm->h_labels, (size_t)E);
+        if (id_bytes) memcpy(gray, rm->h_gray, id_bytes);
+    } else {
+        if (want_labels) HIP_OR_FAIL(hipMemcpy(labels, rm->d_labels, (size_t)E, hipMemcpyDeviceToHost), "read labels");
+        if (id_bytes) HIP_OR_FAIL(hipMemcpy(gray, rm->d_gray, id_bytes, hipMemcpyDeviceToHost), "read gray list");
+    }
     if (n_gray) *n_gray = r.n_gray;
     if (gray && r.n_gray > gray_cap)
         return fail(RGG_E_CAPACITY, "gray list has %lld edges, capacity %lld", (long long)r.n_gray, (long long)gray_cap);
@@ -1924,7 +1939,7 @@ rgg_status rgg_debug_pinned(rgg_roadmap *rm, int64_t limit, int64_t *bytes)
 {
     if (!rm) return fail(RGG_E_INVALID_ARG, "null roadmap");
     rm->pin_limit = limit;
-    if (bytes) *bytes = outputs_pinned(rm);
+    if (bytes) *bytes = rm->h_labels ? output_bytes(rm->dv.E) : 0;
     return RGG_OK;
 }
 

@@ -55,11 +55,13 @@ struct rgg_roadmap {
     rgg_box *h_stage = nullptr;       // pinned [2M]
     rgg_box *d_stage = nullptr;       // [2M]
     rgg_update_result *h_res = nullptr;   // pinned
-    // pinned [E] each, written by the label kernel of a host-buffer update: from the
-    // first one that asks for the labels (the ids) on, null as long as none did
+    // pinned [E] each, written by the label kernel of a host-buffer update: at the
+    // end of h_stage's block when they are small, else a block of their own
+    // (h_outputs) from the first call on that asks for either
     uint8_t *h_labels = nullptr;
     int64_t *h_gray = nullptr;
-    int64_t pin_limit = -1;           // bytes they may hold together (tests); -1: any number
+    void *h_outputs = nullptr;
+    int64_t pin_limit = -1;           // bytes that block may hold (tests); -1: any number
     rgg_update_result *d_res = nullptr;
     uint8_t *d_labels = nullptr;      // [E]
     int64_t *d_gray = nullptr;        // [E]
@@ -83,8 +85,7 @@ struct rgg_roadmap {
         for (auto &a : allocs) hipFree(a.first);
         if (h_stage) hipHostFree(h_stage);
         if (h_res) hipHostFree(h_res);
-        if (h_labels) hipHostFree(h_labels);
-        if (h_gray) hipHostFree(h_gray);
+        if (h_outputs) hipHostFree(h_outputs);
         if (done) hipEventDestroy(done);
         if (stream) hipStreamDestroy(stream);
     }
