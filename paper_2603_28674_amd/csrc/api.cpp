@@ -61,7 +61,6 @@ int host_threads(int requested)
 }
 
 constexpr int32_t kChunk = 256;   // edges per grid work item by default (one per thread)
-constexpr int64_t kDirectSlots = 1024;   // boxes that a host-buffer update's kernels read from pinned memory
 // Host outputs (9 bytes per edge) up to this many bytes share the boxes' pinned
 // block from the build on; larger ones come with the first call that asks for
 // them, which takes that call about 60 us (116k edges: 218 us instead of 152).
@@ -546,7 +545,6 @@ int64_t device_bytes_needed(const HostGeometry &g, const HostGrid &grid, const R
     add((size_t)ntiles + 1, 4);
     add((size_t)ntiles, 8);
     add(1, sizeof(Ctl));
-    add((size_t)(2 * M), sizeof(rgg_box));
     add(1, sizeof(rgg_update_result));
     add((size_t)E, 1);
     add((size_t)E, 8);
@@ -732,7 +730,6 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
     if ((st = rm->alloc(&dv.tile_cnt, (size_t)dv.ntiles + 1, "tile counts")) != RGG_OK) return guard(st);
     if ((st = rm->alloc(&dv.tile_state, (size_t)dv.ntiles, "tile states")) != RGG_OK) return guard(st);
     if ((st = rm->alloc(&dv.ctl, 1, "control block")) != RGG_OK) return guard(st);
-    if ((st = rm->alloc(&rm->d_stage, (size_t)(2 * M), "box staging")) != RGG_OK) return guard(st);
     if ((st = rm->alloc(&rm->d_res, 1, "result")) != RGG_OK) return guard(st);
     if ((st = rm->alloc(&rm->d_labels, (size_t)E, "labels")) != RGG_OK) return guard(st);
     if ((st = rm->alloc(&rm->d_gray, (size_t)E, "gray list")) != RGG_OK) return guard(st);
@@ -962,26 +959,23 @@ rgg_status rgg_update(rgg_roadmap *rm, int64_t m, const rgg_box *obstacles_old,
     // labels and the ids to it, so the call is its kernels and one wait: a
     // transfer of its own costs 10 to 15 us each way, and the labels' and the
     // ids' could only be queued once the result was read.  (Updates of 1k / 116k
-    // edges: 76 -> 45 us and 133 -> 93 us.)  Many boxes still go up in one
-    // transfer, since one block reads them.  A call that finds no pinned outputs
-    // gets them by copies from the device arrays, and locks the pages for the
-    // next calls while its kernels run.
-    const rgg_box *boxes = rm->h_stage;
+    // edges: 76 -> 45 us and 133 -> 93 us.  The boxes sent up instead, a small
+    // roadmap's update took 52.5 against 51.4 us with 64 slots, 76.2 against 70.7
+    // with 512, 104 against 99.5 with 1,024 and 240 against 238 with the 4,096
+    // there may be.)  A call that finds no pinned outputs gets them by copies
+    // from the device arrays, and locks the pages for the next calls while its
+    // kernels run.
     if (M > 0) {
         memcpy(rm->h_stage, obstacles_old, sizeof(rgg_box) * M);
         memcpy(rm->h_stage + M, obstacles_new, sizeof(rgg_box) * M);
         rgg_status st = order_after_previous(rm, s);
         if (st != RGG_OK) return st;
-        if (M > kDirectSlots) {
-            HIP_OR_FAIL(hipMemcpyAsync(rm->d_stage, rm->h_stage, sizeof(rgg_box) * 2 * M, hipMemcpyHostToDevice, s), "upload boxes");
-            boxes = rm->d_stage;
-        }
     }
     const int64_t n_ids = gray ? std::min(gray_cap, E) : 0;
     const bool want_labels = labels && E > 0, want_ids = n_ids > 0;
     const bool pinned = rm->h_labels != nullptr;
-    UpdateArgs a = {boxes,
-                    boxes + M,
+    UpdateArgs a = {rm->h_stage,
+                    rm->h_stage + M,
                     want_labels ? (pinned ? rm->h_labels : rm->d_labels) : nullptr,
                     want_ids ? (pinned ? rm->h_gray : rm->d_gray) : nullptr,
                     n_ids,

@@ -53,7 +53,6 @@ struct rgg_roadmap {
     hipStream_t last_stream = nullptr;
     // staging for host-buffer updates
     rgg_box *h_stage = nullptr;       // pinned [2M]
-    rgg_box *d_stage = nullptr;       // [2M]
     rgg_update_result *h_res = nullptr;   // pinned
     // pinned [E] each, written by the label kernel of a host-buffer update: at the
     // end of h_stage's block when they are small, else a block of their own
