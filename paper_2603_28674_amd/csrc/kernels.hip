@@ -2558,9 +2558,12 @@ void *fn(const RmDev &rm, int k) { return rm.D == 3 ? fn_dim<3>(rm.mode, k) : fn
 
 // Label tiles from which k_labels runs in blocks of 1,024 threads: the loads of
 // a tile's counters then come 2 KB in a row per wavefront instead of 128 bytes
-// apart per lane.  290k edges (71 tiles): 64.4 -> 63.3 us an update; below, the
-// larger block's barriers cost what that gains (3 tiles: 27.3 against 27.7).
-constexpr int kWideTiles = 16;
+// apart per lane, at the price of a larger block's barriers.  Updates of planar
+// edges with blocks of 256 and of 1,024: 1 tile 24.0 / 24.8 us, 2: 25.8 / 26.0,
+// 4: 24.8 / 24.8, 8: 24.7 / 24.8, 12: 25.7 / 25.4, 15: 25.4 / 24.9, 20: 25.6 /
+// 25.5, 40: 26.6 / 26.4; spatial ones cross between 8 and 12 tiles too (71
+// tiles: 39.0 / 38.4).
+constexpr int kWideTiles = 12;
 
 // Items up to which the binary32 item kernel runs with three blocks per CU (and
 // registers enough to spill nothing) rather than four: as many as 256 CUs hold
