@@ -589,6 +589,13 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
     dv.mixed = mixed ? 1 : 0;
     dv.E = E;
     dv.M = M;
+    int n_cu = 0;
+    if ((st = hip_ok(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device),
+                     "compute units")) != RGG_OK) {
+        delete rm;
+        return st;
+    }
+    dv.roomy_items = kRoomyPerCu * n_cu;
     dv.band_rel = (float)(p.band_rel > 0.0 ? p.band_rel : 1e-5);
     if (std::isinf(p.band_rel)) dv.band_rel = INFINITY;
     dv.ntiles = (int32_t)std::max<int64_t>(1, (E + kLabelTile - 1) / kLabelTile);
@@ -761,10 +768,6 @@ rgg_status make_roadmap(rgg_context *ctx, const HostGeometry &g, const HostGrid 
         vd.B = B;
         vd.dof = g.dof;
         vd.kind = g.kind;
-        int n_cu = 0;
-        if ((st = hip_ok(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device),
-                         "compute units")) != RGG_OK)
-            return guard(st);
         vd.n_cu = n_cu;
         vd.L = g.L;
         vd.base[0] = g.rob_base[0];

@@ -2537,7 +2537,7 @@ void *fn_of(int k)
     case 0: return (void *)k_item32<D, MODE, true, 4>;
     case 1: return (void *)k_pairs<D, MODE>;
     case 3: return (void *)k_item32<D, MODE, false, 4>;
-    case 4: return (void *)k_item32<D, MODE, false, 3>;
+    case 4: return (void *)k_item32<D, MODE, false, kRoomyPerCu>;
     default: return (void *)k_item64<D, MODE>;   // 2
     }
 }
@@ -2564,14 +2564,6 @@ void *fn(const RmDev &rm, int k) { return rm.D == 3 ? fn_dim<3>(rm.mode, k) : fn
 // 25.5, 40: 26.6 / 26.4; spatial ones cross between 8 and 12 tiles too (71
 // tiles: 39.0 / 38.4).
 constexpr int kWideTiles = 12;
-
-// Items up to which the binary32 item kernel runs with three blocks per CU (and
-// registers enough to spill nothing) rather than four: as many as 256 CUs hold
-// at once that way.  29k spatial edges: 32.8 -> 31.8 us an update, planar graph
-// 26.1 -> 25.6, the non-lazy spatial update 90.8 -> 89.8.  Above it the items
-// would wait for one another: 1,007 items 63.3 us with four per CU, 82.4 with
-// three.
-constexpr int kRoomyItems = 768;
 
 struct Node {
     void *fn;
@@ -2600,7 +2592,8 @@ int plan(const RmDev &rm, Node out[7])
         // blocks past the fixed items would only start and stop (with pair
         // listing every block writes its list's count, so the whole grid runs)
         const unsigned grid = fixed && !share ? fixed_items_grid(rm) : kGrid;
-        out[n++] = {fn(rm, share ? 0 : (fixed && rm.n_fixed <= kRoomyItems ? 4 : 3)), dim3(grid), 1, 3, share ? 3 : 5};
+        const bool roomy = fixed && rm.n_fixed <= rm.roomy_items;
+        out[n++] = {fn(rm, share ? 0 : (roomy ? 4 : 3)), dim3(grid), 1, 3, share ? 3 : 5};
         if (share) out[n++] = {fn(rm, 1), dim3(kGrid), 1, 4, 5};
     } else {
         out[n++] = {diff_fn, dim3(1), 0, 1, 3};
