@@ -116,12 +116,6 @@ __device__ inline int32_t cell_of(double x, double org, double inv, int32_t n)
     return ci >= n ? n : ci;
 }
 
-__device__ inline bool overlap3(const float *lo, const float *hi, const float4 &bl, const float4 &bh)
-{
-    return lo[0] <= bh.x && hi[0] >= bl.x && lo[1] <= bh.y && hi[1] >= bl.y && lo[2] <= bh.z &&
-           hi[2] >= bl.z;
-}
-
 // ------------------------------------------------------------------------
 // binary32 filter: the same quantities, any rounding; only a margin outside
 // the band +-band_rel*s^2 is trusted (s bounds every coordinate of the pair)
@@ -1599,8 +1593,8 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride,
                         // the cell list's slot: one contiguous load, no gather
                         const int4 cs = rm.cell_slot[beg + sl];
                         e[h] = cs.x;
-                        j0[h] = (uint32_t)cs.z;
-                        J[h] = cs.w;
+                        j0[h] = (uint32_t)cs.y;
+                        J[h] = cs.z;
                     } else if (jfix) {
                         J[h] = jfix;
                         j0[h] = (uint32_t)((int64_t)e[h] * jfix);
@@ -1851,9 +1845,11 @@ __device__ __forceinline__ void item_body(const RmDev &rm, int li0, int lstride,
 
 // The binary32 kernel is held to the registers with which kPerCu blocks fit on
 // a CU (four: 128 VGPRs); the binary64 one keeps the compiler's choice.  An
-// update that lists no pairs runs without the listing (kList false): 104.2
-// against 106.5 us for the arm's second forms, 27.1 against 27.9 for 11.6k
-// planar edges.
+// update that lists no pairs runs without the listing (kList false): on three
+// roadmaps and obstacle walks each, 63.4 -> 62.5, 47.6 -> 47.0 and 32.1 -> 31.6
+// us for the arm's second forms (93k edges), 64.0 -> 63.4, 58.0 -> 57.4 and 58.8 ->
+// 58.1 for 290k spatial edges; planar edges and 464k arm edges take the same
+// (28.3, 75.1 -> 75.4).
 template <int D, int MODE, bool kList, int kPerCu>
 __global__ void __launch_bounds__(kBlock, kPerCu) k_item32(RmDev rm)
 {
@@ -2679,7 +2675,6 @@ __global__ void __launch_bounds__(kBlock) k_cell_slots(RmDev rm, int4 *out, int6
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= n) return;
     const int e = rm.cell_edges[k];
-    const float4 *aabb = reinterpret_cast<const float4 *>(rm.aabb);
     const int jfix = rm.p_fixed ? rm.p_fixed / rm.B : 0;
     int j0, J;
     if (jfix) {
@@ -2690,7 +2685,7 @@ __global__ void __launch_bounds__(kBlock) k_cell_slots(RmDev rm, int4 *out, int6
         j0 = (int)(uint32_t)(s0 / rm.B);
         J = (int)((rm.soff[e + 1] - s0) / rm.B);
     }
-    out[k] = make_int4(e, __float_as_int(aabb[2 * (int64_t)e].w), j0, J);
+    out[k] = make_int4(e, j0, J, 0);
 }
 
 hipError_t fill_cell_slots(const RmDev &rm, int4 *out, int64_t n, hipStream_t s)
@@ -2758,15 +2753,10 @@ hipError_t add_update_nodes(hipGraph_t g, const RmDev &rm, const UpdateArgs &a, 
 
 namespace {
 
-// Copies the request table from pinned host memory into device memory: the
-// device reads the host rows itself, so a batched launch needs no copy
-// engine (whose hand-over to the kernels' queue costs more than the copy).
-// One word per thread: every read of host memory is in flight at once.
-static_assert(sizeof(BatchReq) % 4 == 0, "request rows are copied as 32-bit words");
-
 // The kernels of a batched update in order, each handed to `emit(fn, grid,
 // block, args)` (a graph-node adder or a stream launcher).  With `h_tab`
-// (pinned host rows) the diff kernel copies them to `tab`.
+// (pinned host rows) the diff kernel copies them to `tab`, so a launch needs no
+// copy engine, whose hand-over to the kernels' queue costs more than the copy.
 // `after(stage)` follows each kernel: 0 diff, 1 cells, 3 item, 5 labels (count
 // and write).
 template <typename Emit, typename After>

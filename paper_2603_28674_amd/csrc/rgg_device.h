@@ -72,10 +72,9 @@ struct RmDev {
     const int32_t *cell_start;
     const int32_t *cell_edges;
     // per slot of the cell lists (grid roadmaps; null with one cell): the
-    // edge, the bits of its box's largest |coordinate|, its first
-    // configuration / B and its configurations per sphere, so an item's
-    // edges come in one contiguous 16-byte load per slot instead of a
-    // gather through the edge id
+    // edge, its first configuration, its configurations per sphere and a
+    // word of padding, so an item's edges come in one contiguous 16-byte
+    // load per slot instead of a gather through the edge id
     const int4 *cell_slot;
     int64_t items_cap;
     // Fixed items, all visited by every update: with one cell the chunks of
@@ -131,10 +130,12 @@ constexpr int kFixedItems = 1024;  // fixed items of a grid at most: the blocks 
                                    // uncovered item ends in 3 us beside the covered ones; the
                                    // activation it spares takes 4 to 6 us of the diff kernel
 // Up to this many fixed items per CU the binary32 item kernel runs with three
-// blocks per CU (and registers enough to spill nothing) rather than four.  29k
-// spatial edges: 32.8 -> 31.8 us an update, planar graph 26.1 -> 25.6, the
-// non-lazy spatial update 90.8 -> 89.8.  Above it the items would wait for one
-// another: 1,007 items on 256 CUs 63.3 us with four per CU, 82.4 with three.
+// blocks per CU (and registers enough to spill nothing) rather than four.  On
+// three roadmaps and obstacle walks each, 29k spatial edges: 32.1 -> 31.3, 32.9 ->
+// 32.0 and 31.1 -> 30.2 us an update; 116k: 56.8 -> 55.7, 51.7 -> 50.1, 55.5 ->
+// 53.9; 11.6k planar ones: 28.3 -> 27.9, 29.9 -> 29.3, 31.7 -> 31.2.  Above it
+// the items would wait for one another: 1,007 items on 256 CUs 63.3 us with four
+// per CU, 82.4 with three.
 constexpr int kRoomyPerCu = 3;
 constexpr int kMaxSlots = 4096;    // 2*slots changed entries at most
 
@@ -272,8 +273,8 @@ hipError_t launch_labels(const RmDev &rm, const UpdateArgs &a, hipStream_t s);
 
 // Edges a work item of the classify kernels may hold (at most two per thread).
 int item_edges_max();
-// Fills rm.cell_slot (n = the cell lists' length) from the roadmap's edge
-// boxes and sample offsets, on stream s.
+// Fills rm.cell_slot (n = the cell lists' length) from the roadmap's sample
+// offsets, on stream s.
 hipError_t fill_cell_slots(const RmDev &rm, int4 *out, int64_t n, hipStream_t s);
 // Blocks of the binary32 item kernel for dimension D resident on `device` at
 // once (blocks per CU times CUs).
