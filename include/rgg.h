@@ -266,10 +266,11 @@ rgg_status rgg_roadmap_info_get(rgg_roadmap *rm, rgg_roadmap_info *out);
  * applied to `obstacles_new`.  Outputs (each may be NULL): labels [E] host,
  * gray [gray_cap] host (ascending GRAY edge ids), *n_gray, *result.  If
  * n_gray > gray_cap the update is still committed, gray[0..gray_cap) is
- * written and RGG_E_CAPACITY is returned.  Blocks until done.  The first call
+ * written and RGG_E_CAPACITY is returned.  Blocks until done.  The second call
  * that asks for labels or ids page-locks 9 bytes of host memory per edge (up to
- * 64 KB are locked by rgg_build), held until rgg_destroy; when there are none,
- * the outputs are copied instead, which takes longer and gives the same. */
+ * 64 KB are locked by rgg_build), held until rgg_destroy.  Without them, in the
+ * first calls or when there are none, the outputs are copied, which takes longer
+ * and gives the same. */
 rgg_status rgg_update(rgg_roadmap *rm, int64_t m, const rgg_box *obstacles_old,
                       const rgg_box *obstacles_new, uint8_t *labels, int64_t *gray,
                       int64_t gray_cap, int64_t *n_gray, rgg_update_result *result);

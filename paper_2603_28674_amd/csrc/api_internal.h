@@ -56,10 +56,11 @@ struct rgg_roadmap {
     rgg_update_result *h_res = nullptr;   // pinned
     // pinned [E] each, written by the label kernel of a host-buffer update: at the
     // end of h_stage's block when they are small, else a block of their own
-    // (h_outputs) from the first call on that asks for either
+    // (h_outputs) that the second call that asks for either allocates
     uint8_t *h_labels = nullptr;
     int64_t *h_gray = nullptr;
     void *h_outputs = nullptr;
+    bool outputs_asked = false;       // a call without them asked for outputs
     int64_t pin_limit = -1;           // bytes that block may hold (tests); -1: any number
     rgg_update_result *d_res = nullptr;
     uint8_t *d_labels = nullptr;      // [E]
