@@ -10,7 +10,8 @@ each test's own scale (s + R)(R + L)).
 
 A step is one update: every edge of the roadmap is classified (labels[E] and
 the gray list are produced).  Inputs (the roadmap and every obstacle state)
-are resident in HBM before timing starts.  The JSON line reports:
+are resident in HBM before timing starts.  The JSON line, the last and only one on
+stdout, reports (further workloads by their rates and times; in full on stderr):
   value           edges classified per second, pipelined updates (no events)
   stage_ms_*      per-kernel-stage times from HIP events, a separate pass
   latency_*_us    per-update latency (submit -> labels ready) over a second pass
@@ -79,6 +80,56 @@ def parse():
 
 def log(msg):
     print(msg, file=sys.stderr, flush=True)
+
+
+#: What the JSON line keeps of a further workload; the rest goes to stderr.
+SUMMARY = ("edges", "precision", "offered_rate", "achieved_rate", "edges_per_s", "ms_per_update", "ms_per_round",
+           "latency_p50_us", "latency_p99_us", "batched_round_latency_p50_us", "batched_round_latency_p99_us",
+           "status_ok")
+
+
+def rounded(v):
+    """Six significant digits for every float; null for one that JSON has no
+    word for (the cell size of a single cell)."""
+    if isinstance(v, dict):
+        return {k: rounded(x) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [rounded(x) for x in v]
+    if isinstance(v, float):
+        return float(f"{v:.6g}") if np.isfinite(v) else None
+    return v
+
+
+def summary(v):
+    """The rates, times and checks of a section and of its parts."""
+    out = {}
+    for k, x in v.items():
+        if k in SUMMARY:
+            out[k] = x
+        elif isinstance(x, dict) and summary(x):
+            out[k] = summary(x)
+        elif k == "labels_match_gpu_on_sample":
+            out["oracle_equal"] = x
+        elif k == "rates":
+            out[k] = [summary(r) for r in x]
+    return out
+
+
+def headline(line):
+    """The JSON line, a few kilobytes, so that a reader who keeps only the end
+    of the output keeps all of it: the headline workload in full, the further
+    ones by their rates, times and checks.  Every section it shortens goes to
+    stderr whole."""
+    out = dict(line)
+    for k in ("second_forms", "other_workloads", "batched_planar", "serving"):
+        if out.get(k):
+            log(f"[bench] {k}: {json.dumps(rounded(out[k]))}")
+            out[k] = summary(out[k])
+    tune = out["config"].get("autotune")
+    if tune:
+        log(f"[bench] autotune: {json.dumps(rounded(tune))}")
+        out["config"] = dict(out["config"], autotune={k: v for k, v in tune.items() if k != "candidates"})
+    return dict(rounded(out), value=out["value"], ms_per_step=out["ms_per_step"])
 
 
 # Host cores the CPU legs use: the box gives one GPU's job a 16-core share of
@@ -839,7 +890,9 @@ def main():
 
     # pass 3c: the host-buffer entry point (boxes from host memory, labels and
     # gray ids back to host memory), continuing the same sequence: the
-    # PCIe-inclusive rate, reported beside the value, never as it
+    # PCIe-inclusive rate, reported beside the value, never as it.  The first
+    # two calls get their outputs by copies, and the second locks the pages for
+    # the others: reported by themselves
     host_lat = []
     cur_u = first + 4 * K
     n_host = min(K, len(w.boxes) - cur_u)
@@ -847,6 +900,7 @@ def main():
         t1 = time.perf_counter()
         g.update(w.boxes[u - 1], w.boxes[u])
         host_lat.append((time.perf_counter() - t1) * 1e6)
+    host_first, host_lat = (host_lat[:2], host_lat[2:]) if len(host_lat) > 2 else ([], host_lat)
     host_lat = np.array(host_lat) if host_lat else np.array([0.0])
 
     # pass 4: the same kind of updates as HIP graphs (one graph per update,
@@ -915,7 +969,8 @@ def main():
         "graph": graph,
         "validation": validation,
         "host_buffers": {"edges_per_s": E / (host_lat.mean() * 1e-6), "latency_p50_us": float(np.percentile(host_lat, 50)),
-                         "latency_p99_us": float(np.percentile(host_lat, 99)), "updates": int(n_host),
+                         "latency_p99_us": float(np.percentile(host_lat, 99)), "first_us": host_first,
+                         "updates": len(host_lat),
                          "note": "rgg_update: boxes uploaded from host memory, labels and gray ids "
                                  "copied back to host memory; one update at a time"},
         "stage_ms_per_update": st,
@@ -963,7 +1018,7 @@ def main():
         line["serving"] = serving(a)
     if a.copy_calibration:
         line["copy_calibration_bytes"] = copy_calibration(torch)
-    print(json.dumps(line), flush=True)
+    print(json.dumps(headline(line)), flush=True)
 
 
 def copy_calibration(torch):
