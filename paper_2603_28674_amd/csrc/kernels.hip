@@ -1110,8 +1110,11 @@ __device__ __forceinline__ void test_round(const RmDev &rm, Lds &L, const T *s_r
         // ---- outer test, exact part: the queued tests, one per lane.  A
         // capsule that meets probes the copy nearest to where it came
         // closest: S is an existence test, so a copy found to meet settles the
-        // pair (in the copy form; in binary64 with the oriented boxes the
-        // sphere's box is not yet known to meet).
+        // pair.  In binary64 with the oriented boxes the sphere's box is not yet
+        // known to meet, and there is no probe: the end copies settle most pairs
+        // a probe would (with one behind the box test and none of them, an
+        // update of 46k spatial edges took 68.3 us, now 46.4; of 56k arm edges 89.3
+        // and 54.9; of 23k planar ones 47.0 and 28.7).
         constexpr bool kProbe = !kSpl && (kF32 || !kObb);
         const int nq = min(L.nopen, kOpenCap);
         for (int q = tid; q < nq; q += kBlock) {
@@ -2338,7 +2341,7 @@ __device__ inline void load_row(R *dst, const R &src)
 // fields are scalar loads into scalar registers, as a single update's kernel
 // arguments are.  From a copy in LDS every field took vector registers, which
 // this kernel has none to spare of: 116 B of spills per lane in 2-D and 196 in
-// 3-D against 44 and 124 now, 16 planar roadmaps 71.4 -> 66.6 us, 12 spatial
+// 3-D against 52 and 132 now, 16 planar roadmaps 71.4 -> 66.6 us, 12 spatial
 // ones 161 -> 153.  (With three blocks per CU and no spills small batches
 // would gain 1 to 4 us more, but 20 roadmaps of up to 12k nodes lose 4 to 11.)
 __device__ __forceinline__ const RmDev &const_row(const RmDev &rm)
