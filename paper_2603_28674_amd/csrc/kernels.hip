@@ -2561,7 +2561,7 @@ void *fn(const RmDev &rm, int k) { return rm.D == 3 ? fn_dim<3>(rm.mode, k) : fn
 // edges with blocks of 256 and of 1,024: 1 tile 24.0 / 24.8 us, 2: 25.8 / 26.0,
 // 4: 24.8 / 24.8, 8: 24.7 / 24.8, 12: 25.7 / 25.4, 15: 25.4 / 24.9, 20: 25.6 /
 // 25.5, 40: 26.6 / 26.4; spatial ones cross between 8 and 12 tiles too (71
-// tiles: 39.0 / 38.4).
+// tiles: 39.0 / 38.4), the arm's between 12 (38.9 / 39.2) and 14 (36.8 / 36.9).
 constexpr int kWideTiles = 12;
 
 struct Node {
